@@ -152,8 +152,8 @@ int lb_init_moments(lb_solver* s, const double* host_Y, double lambda);
 /* Queue n >= 0 steps (eq. 10 / eq. 30 with tau = 1, Sec. V.A).  Each step
  * queues its step launches on the bound stream -- one kernel in 1-D and on the
  * hexagonal lattice; on the square lattice a first pass over the tiles, and
- * two further passes that return at once unless the earlier pass left tiles
- * to them -- and then a small kernel that reduces the per-tile partial
+ * a second one that returns at once unless the first left tiles to it --
+ * and then a small kernel that reduces the per-tile partial
  * results into the interior conservation totals and the largest reach.  If a
  * step fails, it and every later queued step leave the state at the last good
  * step; the error is reported at the next synchronising call. */
@@ -215,11 +215,11 @@ const char* lb_last_error(void);
  * rho u lambda, (rho v lambda), rho E lambda^2 (, rho chi); each 256-byte
  * aligned, not overlapping.  The caller owns both; Y_in is only read.  The
  * step's scratch (control block, per-tile partial sums, tile flags) is a
- * static device array of 2 MiB per GPU, which the library holds until the
- * process ends; grids that need more are rejected with LB_EINVAL (1-D tubes
- * above about 33 M nodes; a 2-D grid is cut into about three tiles per
- * resident block whatever its size, and only grids wider than about 7 M
- * columns need more).
+ * static device array per GPU (2 MiB, and 10 MB for the square lattice), which
+ * the library holds until the process ends; grids that need more are rejected
+ * with LB_EINVAL (1-D tubes above about 33 M nodes; a square-lattice grid is
+ * cut into about one tile per resident wavefront whatever its size, and only
+ * grids wider than about 7 M columns need more).
  * The call queues kernels on hip_stream and returns; it calls no hipMalloc,
  * hipFree or allocating library routine.  If status_dev (a device int32, may
  * be NULL) is given, the stream writes LB_OK, LB_EREACH or LB_ESTATE to it
@@ -235,9 +235,8 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
  * lattice, gamma and precision (each with its own grid, lambda, boundary
  * conditions and step target) in an arena of arena_bytes inside the caller's
  * device memory.  One pool step is one kernel launch over a tile table in
- * device memory (square lattice: persistent blocks that claim tiles, plus a
- * pass that redoes the tiles whose packets reached past the short FIFO; 1-D:
- * one block per tile) and a per-slot reduction kernel; every live, unfinished
+ * device memory (square lattice: resident wavefronts that take tiles, plus a
+ * second pass over the tiles the first left to it; 1-D: one block per tile) and a per-slot reduction kernel; every live, unfinished
  * slot advances by one step (eq. 10 / 30 with tau = 1, as lb_step).
  * Admissions and releases rewrite the tables between launches, in stream
  * order: steps queued before them run with the old tables, steps queued
@@ -316,7 +315,7 @@ double lb_pool_lambda(const lb_pool* p, int32_t slot);
 int32_t lb_pool_live(const lb_pool* p);                  /* admitted slots */
 
 /* Tile shapes: 1-D, threads x nodes per thread in {256x1, 256x2, 256x4,
- * 256x8, 512x4}; square lattice, tiles of 246 columns whose strip height makes
+ * 256x8, 512x4}; square lattice, tiles of 54 columns whose strip height makes
  * about {2, 3, 4, 6, 8} tiles per resident block over the live problems (at
  * least 16 rows).  lb_pool_autotune times `trials` steps of every shape on the
  * admitted problems without changing their states, keeps the fastest and

@@ -285,10 +285,10 @@ static int create_solver(const lb_grid* grid, double gamma, double gamma2, bool 
     s->off_export = 2 * field_bytes;
     s->off_ctl = s->off_export + align256((size_t)s->nf * (size_t)s->nn * 8);
     s->off_partials = s->off_ctl + align256(sizeof(StepCtl));
-    s->off_flags = s->off_partials + align256((size_t)s->nblocks * kPartialStride * 8);
-    // square lattice: two flag words per tile (short and full passes, lean
-    // pass) and the state of the passes' row chunks; hexagonal: unused
-    const size_t flag_bytes = dim == 2 ? (hex ? (size_t)2 * s->nblocks * 4 : march2d_flag_bytes(s->nblocks, true)) : 4;
+    // square lattice: kSplitMax partial rows and three words per tile
+    const bool march = dim == 2 && !hex;
+    s->off_flags = s->off_partials + align256((size_t)s->nblocks * (march ? kSplitMax : 1) * kPartialStride * 8);
+    const size_t flag_bytes = march ? march2d_word_bytes(s->nblocks) : 4;
     s->total = s->off_flags + align256(flag_bytes);
     s->cfl = 1.0;
     s->lambda_set = 0.0;
@@ -367,10 +367,8 @@ static int start_state(lb_solver* s)
     s->pending_err = 0;
     s->initialized = true;
     hipError_t e = launch_reset_ctl(ctl_ptr(s), s->stream);
-    // square lattice: the passes' per-tile flag words, work words and chunk
-    // counters start clear
-    if (e == hipSuccess && s->dim == 2)
-        e = launch_fill_i32(flags_ptr(s), (s->hex ? 2 : 5) * s->nblocks, 0, s->stream);
+    // square lattice: the passes' per-tile words start clear
+    if (e == hipSuccess && s->dim == 2 && !s->hex) e = launch_fill_i32(flags_ptr(s), 3 * s->nblocks, 0, s->stream);
     return e == hipSuccess ? LB_OK : hip_fail(e, "reset");
 }
 
@@ -412,6 +410,8 @@ int lb_init_moments(lb_solver* s, const double* Y, double lambda)
 // ev[2i] / ev[2i+1] are recorded right before / after step i's step kernel.
 static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr)
 {
+    const bool march = s->dim == 2 && !s->hex;
+    const MarchWords words = march2d_words(flags_ptr(s), s->nblocks, kSplitMax, true);
     for (int64_t i = 0; i < n; ++i) {
         const int in = s->cur, out = s->cur ^ 1;
         const long long step = (long long)(s->steps_done + 1);
@@ -434,17 +434,15 @@ static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr)
         } else {
             if (s->precision == LB_FP64)
                 e = launch_march2d<double>((const double*)buf_ptr(s, in), (double*)buf_ptr(s, out), s->g,
-                                           s->march, s->k, ctl_ptr(s), partials_ptr(s), flags_ptr(s), step,
-                                           s->stream, true);
+                                           s->march, s->k, ctl_ptr(s), partials_ptr(s), words, step, s->stream);
             else
                 e = launch_march2d<float>((const float*)buf_ptr(s, in), (float*)buf_ptr(s, out), s->g,
-                                          s->march, s->k, ctl_ptr(s), partials_ptr(s), flags_ptr(s), step,
-                                          s->stream, true);
+                                          s->march, s->k, ctl_ptr(s), partials_ptr(s), words, step, s->stream);
         }
         if (e != hipSuccess) return hip_fail(e, "step launch");
         if (ev && (e = hipEventRecord(ev[2 * i + 1], s->stream)) != hipSuccess) return hip_fail(e, "event");
-        e = launch_finalize(partials_ptr(s), s->nblocks, ctl_ptr(s), step, s->stream,
-                            s->dim == 2 && s->species);
+        e = launch_finalize(partials_ptr(s), s->nblocks, ctl_ptr(s), step, s->stream, s->dim == 2 && s->species,
+                            march ? words.nch : nullptr);
         if (e != hipSuccess) return hip_fail(e, "finalize launch");
         s->cur = out;
         s->steps_done += 1;
@@ -682,15 +680,20 @@ int lb_debug_lanes(lb_solver* s, int32_t* fx, int32_t* fy, int32_t* c1)
 
 namespace {
 
-constexpr size_t kStaticScratchBytes = (size_t)2 << 20;  // per device
-constexpr size_t kStaticCtlBytes = 256;                  // the StepCtl at the front
-static_assert(sizeof(StepCtl) <= kStaticCtlBytes, "control block must fit its slot");
+constexpr size_t kStaticCtlBytes = (sizeof(StepCtl) + 255) / 256 * 256;  // the StepCtl at the front
+// Per device: the control block and, for the 1-D and hexagonal lattices, the
+// partial rows that 2 MiB less 256 bytes hold (1-D tubes of about 33 M
+// nodes); for the square lattice a partial row and three words per tile of
+// the widest grid taken, 132672 column strips (7.16 M columns).
+constexpr size_t kStaticScratchBytes = kStaticCtlBytes + ((size_t)2 << 20) - 256;
+constexpr size_t kStaticMarchBytes = kStaticCtlBytes + (size_t)132672 * (kPartialStride * 8 + 12);
 constexpr int kStaticMaxDevices = 64;
 
 struct StaticDevice {
     char* ptr = nullptr;  // device address of `scratch` on this device
+    char* ptr_march = nullptr;  // and of `scratch_march`
     int cus = 0;          // compute units
-    int per_cu[2] = {0, 0};       // resident blocks per CU of the square lattice's short pass, FP64 and FP32
+    int per_cu[2] = {0, 0};       // resident blocks per CU of the square lattice's general pass, FP64 and FP32
     int per_cu_lean[2] = {0, 0};  // and of its lean pass
     bool ready = false;
 };
@@ -701,6 +704,7 @@ StaticDevice g_static[kStaticMaxDevices];
 }  // namespace
 
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch_march[kStaticMarchBytes];
 
 namespace {
 
@@ -718,6 +722,10 @@ int static_device(StaticDevice** out)
         void* p = nullptr;
         if ((e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch))) != hipSuccess)
             return hip_fail(e, "hipGetSymbolAddress(scratch)");
+        void* pm = nullptr;
+        if ((e = hipGetSymbolAddress(&pm, HIP_SYMBOL(scratch_march))) != hipSuccess)
+            return hip_fail(e, "hipGetSymbolAddress(scratch_march)");
+        d.ptr_march = (char*)pm;
         if ((e = hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
             return hip_fail(e, "hipDeviceGetAttribute");
         d.per_cu[0] = march2d_blocks_per_cu<double>(false);
@@ -758,32 +766,39 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
     StaticDevice* d = nullptr;
     int rc = static_device(&d);
     if (rc != LB_OK) return rc;
-    // scratch layout: control block, partial rows (one per block / tile), tile flags (two words per tile)
+    // scratch layout: control block, partial rows (one per block; on the square
+    // lattice up to kSplitMax per tile, as many as fit), the square lattice's
+    // words per tile
     MarchGeom m{};
+    MarchWords w{};
     int64_t rows = 0;
-    const bool march = s->dim == 2 && !s->hex;  // the square lattice's passes (tile flags)
-    if (s->dim == 1) {
-        rows = step_blocks_1d(s->g);
-    } else if (s->hex) {
-        rows = hex_blocks(s->g);
-    } else {
+    const bool march = s->dim == 2 && !s->hex;
+    char* const base = march ? d->ptr_march : d->ptr;
+    StepCtl* ctl = (StepCtl*)base;
+    double* partials = (double*)(base + kStaticCtlBytes);
+    size_t need = 0, have = kStaticScratchBytes;
+    if (march) {
         const int pi = s->precision == LB_FP64 ? 0 : 1;
         m = march2d_geometry(s->g, d->cus, d->per_cu[pi], d->per_cu_lean[pi]);
         rows = m.blocks();
+        have = kStaticMarchBytes;
+        const size_t row = (size_t)rows * kPartialStride * 8, words = march2d_word_bytes(rows);
+        need = kStaticCtlBytes + align256(row) + words;
+        int smax = kSplitMax;
+        while (smax > 1 && kStaticCtlBytes + align256(row * smax) + words > have) --smax;
+        w = march2d_words((int*)(base + kStaticCtlBytes + align256(row * smax)), rows, smax, false);
+    } else {
+        rows = s->dim == 1 ? step_blocks_1d(s->g) : hex_blocks(s->g);
+        need = kStaticCtlBytes + align256((size_t)rows * kPartialStride * 8);
     }
-    const size_t part_bytes = align256((size_t)rows * kPartialStride * 8);
-    const size_t need = kStaticCtlBytes + part_bytes + (march ? align256((size_t)rows * 2 * 4) : 0);
-    if (need > kStaticScratchBytes)
+    if (need > have)
         return fail(LB_EINVAL, "grid %lld x %lld needs %zu bytes of step scratch, more than the %zu of lb_step_static",
-                    (long long)s->g.nx, (long long)s->g.ny, need, kStaticScratchBytes);
-    StepCtl* ctl = (StepCtl*)d->ptr;
-    double* partials = (double*)(d->ptr + kStaticCtlBytes);
-    int* flags = (int*)(d->ptr + kStaticCtlBytes + part_bytes);
+                    (long long)s->g.nx, (long long)s->g.ny, need, have);
     const hipStream_t st = (hipStream_t)hip_stream;
-    // the last call's control block is stale: a fill kernel resets it (no
-    // memset, so the call can be captured into a graph)
+    // the last call's control block is stale: a small kernel resets it (no
+    // memset, so the call can be captured into a graph); the lean pass writes
+    // every per-tile word before it is read
     hipError_t e = launch_reset_ctl(ctl, st);
-    if (e == hipSuccess && march) e = launch_fill_i32(flags, 2 * rows, 0, st);  // the last call's flags
     if (e != hipSuccess) return hip_fail(e, "reset");
     if (s->dim == 1) {
         e = s->precision == LB_FP64
@@ -795,13 +810,11 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
             : launch_hex<float>((const float*)Y_in, (float*)Y_out, s->g, s->k, ctl, partials, 1, st);
     } else {
         e = s->precision == LB_FP64
-            ? launch_march2d<double>((const double*)Y_in, (double*)Y_out, s->g, m, s->k, ctl, partials, flags, 1, st,
-                                     false)
-            : launch_march2d<float>((const float*)Y_in, (float*)Y_out, s->g, m, s->k, ctl, partials, flags, 1, st,
-                                    false);
+            ? launch_march2d<double>((const double*)Y_in, (double*)Y_out, s->g, m, s->k, ctl, partials, w, 1, st)
+            : launch_march2d<float>((const float*)Y_in, (float*)Y_out, s->g, m, s->k, ctl, partials, w, 1, st);
     }
     if (e != hipSuccess) return hip_fail(e, "step launch");
-    if ((e = launch_finalize(partials, rows, ctl, 1, st, s->dim == 2 && s->species)) != hipSuccess)
+    if ((e = launch_finalize(partials, rows, ctl, 1, st, s->dim == 2 && s->species, w.nch)) != hipSuccess)
         return hip_fail(e, "finalize launch");
     if (status_dev && (e = launch_status(ctl, status_dev, st)) != hipSuccess) return hip_fail(e, "status launch");
     return LB_OK;

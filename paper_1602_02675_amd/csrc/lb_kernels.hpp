@@ -10,24 +10,22 @@ namespace lbsd {
 constexpr int kErrReach = 1;  // a packet would travel further than the halo
 constexpr int kErrState = 2;  // rho <= 0 or a non-finite moment
 
+// Tiles the square lattice's lean pass gave up are counted in kGivenUp words
+// a cache line apart: on general flows every wavefront of the pass counts one
+// at about the same time, and one word takes them one after another.
+constexpr int kGivenUp = 16, kGivenUpStride = 32;
+
 // Per-solver control block in device memory (written by the step kernels).
 struct StepCtl {
-    int next[5];            // square lattice: tile claim counters of the short- and full-FIFO passes,
-                            // tiles the short pass flagged, claim counter of the lean pass, tiles the
-                            // lean pass gave up (reset by finalize)
+    int next[5];            // square lattice: tile claim counters of the two passes (reset by finalize)
     int err_code;           // kErr* bits of the first failed step
     long long err_step;     // first failed step (LLONG_MAX if none)
     long long totals_step;  // step whose totals are in `totals`
     double totals[4];       // interior sums of the moment fields (lattice units)
     int max_reach;          // largest reach seen in the latest step
-    int redo_tiles;         // tiles the full-FIFO pass has recomputed since the last reset
-    int keep[2];            // square lattice: tiles the full-FIFO pass left flagged in this step [0]
-                            // and in the previous step [1] (finalize moves [0] to [1])
+    int pad;
     double totals_sp;       // square lattice with two gases: interior sum of rho chi
-    int split_n[2];         // square lattice: tiles listed for row chunks in the steps of each parity
-                            // (finalize clears the next step's)
-    int full_n;             // square lattice: tiles the short pass listed for the full pass (finalize
-                            // clears it)
+    int given_up[kGivenUp * kGivenUpStride];  // square lattice: see kGivenUp (cleared by finalize)
 };
 
 // Per-block partial results: 4 field sums, reach, error bits; the square
@@ -48,50 +46,46 @@ hipError_t launch_step1d(const T* Y, T* Yn, const Grid& g, const Consts& k, Step
                          double* partials, long long step, hipStream_t stream);
 int64_t step_blocks_1d(const Grid& g);
 
-// Square lattice, column-march kernel (lb_march2d.hip).  The grid is cut into
-// tiles (column strips x row chunks) that the device's resident blocks claim
-// one after another.
+// Square lattice, column-march kernels (lb_march2d.hpp).  The grid is cut into
+// tiles (strips of kMarchCols columns x row chunks) that the device's resident
+// wavefronts take.
+constexpr int kHalo = 5;
+constexpr int kMarchCols = 64 - 2 * kHalo;
 struct MarchGeom {
     int sy;                   // destination rows per tile
     int64_t grid_x, grid_y;   // tiles along x (column strips) and y (row chunks)
-    int nblocks;              // persistent blocks of the short and full passes (resident at once)
-    int nblocks_lean;         // persistent blocks of the lean pass
+    int nblocks;              // blocks (of four wavefronts) of the general pass, resident at once
+    int nblocks_lean;         // blocks of the lean pass
     int64_t blocks() const { return grid_x * grid_y; }  // tiles (= rows of partials)
 };
 // cus: compute units; per_cu / per_cu_lean: resident blocks per CU of the
-// short and the lean pass (march2d_blocks_per_cu).
+// general and the lean pass (march2d_blocks_per_cu).
 MarchGeom march2d_geometry(const Grid& g, int cus, int per_cu, int per_cu_lean);
 int64_t march2d_max_blocks(const Grid& g);
-// Resident blocks per CU of the short pass (lean = false) or the lean pass.
+// Resident blocks per CU of the general pass (lean = false) or the lean pass.
 template <typename T>
 int march2d_blocks_per_cu(bool lean = false);
-// The short-FIFO kernel runs every tile and flags those it could not
-// complete, and those with sources that reach past its FIFO; the full-FIFO
-// kernel then recomputes the incomplete tiles and the row-chunk neighbours of
-// the far-reaching ones (it returns at once when nothing was flagged).  flags
-// holds two ints of flag bits per tile (march2d_flag_bytes(tiles, false)
-// bytes); with split, the state of the passes' row chunks follows them
-// (march2d_flag_bytes(tiles, true) bytes, zero before the first step).
+// Per-tile words of the two passes (device memory), and the row chunks the
+// general pass may cut a tile into (it then writes smax partial rows per tile).
+struct MarchWords {
+    int* flags;  // this step's lean pass gave the tile up
+    int* keep;   // the next step's lean pass will (zero at the start; nullptr: not kept between steps)
+    int* nch;    // partial rows the tile has this step (row p at p * tiles + tile)
+    int smax;
+};
+constexpr int kSplitMax = 8;
+// Bytes of the three words per tile.
+inline size_t march2d_word_bytes(int64_t ntiles) { return (size_t)3 * ntiles * 4; }
+inline MarchWords march2d_words(int* w, int64_t ntiles, int smax, bool keep)
+{
+    return MarchWords{w, keep ? w + ntiles : nullptr, w + 2 * ntiles, smax};
+}
+// One step: the lean pass over every tile, then the general pass over the
+// tiles it gave up and the row-chunk neighbours their sources can reach (it
+// returns at once when there are none).
 template <typename T>
 hipError_t launch_march2d(const T* Y, T* Yn, const Grid& g, const MarchGeom& m, const Consts& k,
-                          StepCtl* ctl, double* partials, int* flags, long long step, hipStream_t stream,
-                          bool split);
-
-// Row chunks of the square lattice's short and full passes: at most
-// kSplitMax per tile.  Their state follows the two flag words per tile
-// (flags, flags_lean): two work words per tile (written in the steps of
-// each parity), one counter of finished chunks per tile (zero between
-// passes), two lists of tiles to cut (written in the steps of each parity),
-// the list of tiles for the full pass, then kSplitMax partial rows per tile
-// (chunk p of tile t at row p * tiles + t), 8-byte aligned.  The first 5
-// words per tile start at zero.
-constexpr int kSplitMax = 8;
-__host__ __device__ inline int64_t split_slots_offset(int64_t ntiles) { return 8 * ntiles; }
-inline size_t march2d_flag_bytes(int64_t ntiles, bool split)
-{
-    return split ? (size_t)split_slots_offset(ntiles) * 4 + (size_t)kSplitMax * ntiles * kPartialStride * 8
-                 : (size_t)2 * ntiles * 4;
-}
+                          StepCtl* ctl, double* partials, const MarchWords& w, long long step, hipStream_t stream);
 
 // Hexagonal lattice (lb_hex.hip): one block per tile of 64 x 4 nodes (axial
 // i x j), hex_blocks(g) blocks and partial rows per step.
@@ -101,10 +95,10 @@ hipError_t launch_hex(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl
 int64_t hex_blocks(const Grid& g);
 
 // Reduce nb per-block partial rows of one step into ctl (fixed order);
-// species2d: also the rho chi sums of the square lattice with two gases.
+// species2d: also the rho chi sums of the square lattice with two gases; nch:
+// rows per tile where a tile may have several (MarchWords::nch), else nullptr.
 hipError_t launch_finalize(double* partials, int64_t nb, StepCtl* ctl, long long step,
-                           hipStream_t stream, bool species2d = false);
-constexpr int kHalo = 5;
+                           hipStream_t stream, bool species2d = false, const int* nch = nullptr);
 
 // Riemann initial state: node i (cell centre x_lo + (i + 1/2) dx) takes the
 // left moments when x < x_d, else the right ones (lattice units; left and
@@ -174,8 +168,8 @@ struct PoolView {
     int32_t* tstate;        // kTileSet | kTileLive per tile
     const int32_t* ntiles;  // tiles in the table (read by the kernels, so admissions need no new launch shape)
     double* partials;       // kPartialStride doubles per tile
-    int32_t* flags;         // square lattice: per-tile flag bits of the short- and full-FIFO passes
-    int32_t* flags_lean;    // square lattice: per-tile flag bits of the lean pass
+    int32_t* flags;         // square lattice: per tile, the next step's lean pass will give it up
+    int32_t* flags_lean;    // square lattice: per tile, this step's lean pass gave it up
     int32_t* next;          // 5 counters, as StepCtl::next; reset by finalize
     void* arena;            // moment sets of all slots (T elements)
 };
@@ -191,19 +185,18 @@ constexpr int kPool1J[kPool1Shapes] = {1, 2, 4, 8, 4};
 constexpr int kPool2Shapes = 5;
 constexpr int kPool2TilesPerBlock[kPool2Shapes] = {2, 3, 4, 6, 8};
 constexpr int kPool2MinRows = 16;
-constexpr int kPool2Cols = 256 - 2 * kHalo;  // destination columns per square-lattice tile
+constexpr int kPool2Cols = kMarchCols;  // destination columns per square-lattice tile
 
 // One step of every live tile: the 1-D kernel of tile shape `shape` (nblocks =
-// the number of tiles, one block each), or the square-lattice short-FIFO pass
-// followed by the full-FIFO pass over the tiles it flagged (nblocks persistent
-// blocks claim the tiles).
+// the number of tiles, one block each), or the square lattice's lean pass
+// followed by the general pass over what it left (resident wavefronts take
+// the tiles).
 template <typename T>
 hipError_t launch_pool1d(const PoolView& v, const Consts& k, int shape, int nblocks, bool walls,
                          hipStream_t stream);
 template <typename T>
-hipError_t launch_pool2d(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks, bool walls,
-                         hipStream_t stream);
-// Resident blocks per CU of the pool's short pass (lean = false) or lean pass.
+hipError_t launch_pool2d(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks, hipStream_t stream);
+// Resident blocks per CU of the pool's general pass (lean = false) or lean pass.
 template <typename T>
 int pool2d_blocks_per_cu(bool lean = false);
 // Per slot: reduce its tiles' partial rows (fixed order) into its state and,

@@ -79,13 +79,8 @@ __global__ void reset_ctl_kernel(StepCtl* ctl)
         for (int f = 0; f < 4; ++f) ctl->totals[f] = 0.0;
         ctl->totals_sp = 0.0;
         ctl->max_reach = 0;
-        ctl->redo_tiles = 0;
-        ctl->keep[0] = 0;
-        ctl->keep[1] = 0;
-        ctl->split_n[0] = 0;
-        ctl->split_n[1] = 0;
-        ctl->full_n = 0;
     }
+    if (threadIdx.x < kGivenUp) ctl->given_up[threadIdx.x * kGivenUpStride] = 0;
 }
 
 // The step's outcome as an lbsd status code (LB_OK, LB_EREACH, LB_ESTATE).

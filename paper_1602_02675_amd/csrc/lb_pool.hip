@@ -74,9 +74,9 @@ struct lb_pool {
     std::map<size_t, size_t> free_list;  // arena byte offset -> size
     std::vector<PoolTile> tiles;
     int shape = 0;    // 1-D: kernel tile shape; 2-D: strip height index
-    int nblocks = 0;  // persistent blocks of the current shape (square lattice: short and full passes)
-    int nblocks_lean = 0;  // square lattice: persistent blocks of the lean pass
-    bool walls = false;  // a live slot has reflecting walls: run the kernels that handle them
+    int nblocks = 0;  // blocks of the current shape (square lattice: of the general pass)
+    int nblocks_lean = 0;  // square lattice: blocks of the lean pass
+    bool walls = false;  // 1-D: a live slot has reflecting walls: run the kernels that handle them
     // graph of `graph_steps` steps (0: plain launches)
     int graph_steps = 0;
     bool graph_ready = false;
@@ -225,7 +225,7 @@ int upload_tables(lb_pool* p)
     const int nb = launch_blocks(p, nt), nb_lean = launch_blocks(p, nt, true);
     bool walls = false;
     for (const PoolProb& q : p->probs)
-        walls |= q.active && (q.bc_x == kBcReflecting || (p->dim == 2 && q.bc_y == kBcReflecting));
+        walls |= p->dim == 1 && q.active && q.bc_x == kBcReflecting;  // (the square lattice's kernels take walls at run time)
     if (nb != p->nblocks || nb_lean != p->nblocks_lean || walls != p->walls) {  // a captured graph is stale
         drop_graph(p);
         p->nblocks = nb;
@@ -298,8 +298,8 @@ int queue_step(lb_pool* p, int commit)
                                     : launch_pool1d<float>(v, p->k, p->shape, p->nblocks, p->walls, p->stream);
     else
         e = p->precision == LB_FP64
-            ? launch_pool2d<double>(v, p->k, p->nblocks_lean, p->nblocks, p->walls, p->stream)
-            : launch_pool2d<float>(v, p->k, p->nblocks_lean, p->nblocks, p->walls, p->stream);
+            ? launch_pool2d<double>(v, p->k, p->nblocks_lean, p->nblocks, p->stream)
+            : launch_pool2d<float>(v, p->k, p->nblocks_lean, p->nblocks, p->stream);
     if (e != hipSuccess) return hip_fail(e, "pool step launch");
     if ((e = launch_pool_finalize(v, p->max_slots, commit, p->stream)) != hipSuccess)
         return hip_fail(e, "pool finalize launch");
@@ -504,10 +504,10 @@ static int create_pool(int32_t dim, double gamma, double gamma2, bool species, c
     p->max_slots = max_slots;
     p->arena_bytes = arena_bytes & ~(size_t)255;
     // every live slot has at most one partly filled tile row/column per
-    // shape; the rest of its tiles are full (>= 256 nodes in 1-D, >= 246 x 16
+    // shape; the rest of its tiles are full (>= 256 nodes in 1-D, >= 54 x 16
     // on the square lattice)
     const int64_t cap_nodes = (int64_t)(p->arena_bytes / (2 * (size_t)p->nf * p->elem));
-    p->max_tiles = (int64_t)max_slots * (dim == 1 ? 1 : 64) + cap_nodes / (dim == 1 ? 256 : 246) + 64;
+    p->max_tiles = (int64_t)max_slots * (dim == 1 ? 1 : 320) + cap_nodes / (dim == 1 ? 256 : 49) + (dim == 1 ? 64 : 320);
     try {
         p->probs.assign((size_t)max_slots, PoolProb{});
         p->info.assign((size_t)max_slots, SlotInfo{});

@@ -6,17 +6,14 @@
 namespace lbsd {
 
 template <typename T>
-hipError_t launch_pool2d_species(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks, bool walls,
+hipError_t launch_pool2d_species(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks,
                                  hipStream_t stream)
 {
-    if (k.rest_q > 0.0)
-        return walls ? launch_pool2d_w<T, true, true, true>(v, k, nblocks_lean, nblocks, stream)
-                     : launch_pool2d_w<T, false, true, true>(v, k, nblocks_lean, nblocks, stream);
-    return walls ? launch_pool2d_w<T, true, false, true>(v, k, nblocks_lean, nblocks, stream)
-                 : launch_pool2d_w<T, false, false, true>(v, k, nblocks_lean, nblocks, stream);
+    return k.rest_q > 0.0 ? launch_pool2d_w<T, true, true>(v, k, nblocks_lean, nblocks, stream)
+                          : launch_pool2d_w<T, false, true>(v, k, nblocks_lean, nblocks, stream);
 }
 
-template hipError_t launch_pool2d_species<double>(const PoolView&, const Consts&, int, int, bool, hipStream_t);
-template hipError_t launch_pool2d_species<float>(const PoolView&, const Consts&, int, int, bool, hipStream_t);
+template hipError_t launch_pool2d_species<double>(const PoolView&, const Consts&, int, int, hipStream_t);
+template hipError_t launch_pool2d_species<float>(const PoolView&, const Consts&, int, int, hipStream_t);
 
 }  // namespace lbsd

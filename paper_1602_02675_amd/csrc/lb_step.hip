@@ -106,12 +106,13 @@ __device__ void finish_step(double (&acc)[NF], const TileInfo& ti, double* __res
 
 // First stage of the reduction of many partial rows (a 1-D step has one row
 // per 1024 nodes, 16 K rows at 2^24 nodes, too many for one block to read
-// quickly): block g folds rows [g kChunk, (g + 1) kChunk) in a fixed order
+// quickly; with nch, tile b has nch[b] rows, i nb + b): block g folds tiles [g kChunk, (g + 1) kChunk) in a fixed order
 // (sums, largest reach, error bits) into row g kChunk, the first of its own
 // chunk, so that blocks never touch each other's rows.
 constexpr int kChunk = 256;
 __global__ void __launch_bounds__(kChunk)
-partials_chunk_kernel(double* __restrict__ partials, int64_t nb, const StepCtl* __restrict__ ctl, long long step)
+partials_chunk_kernel(double* __restrict__ partials, int64_t nb, const StepCtl* __restrict__ ctl, long long step,
+                      const int* __restrict__ nch)
 {
     __shared__ double s_sum[kChunk / 64][5];
     __shared__ int s_ir[kChunk / 64][2];
@@ -120,13 +121,14 @@ partials_chunk_kernel(double* __restrict__ partials, int64_t nb, const StepCtl* 
     const int64_t b0 = (int64_t)blockIdx.x * kChunk, b = b0 + tid;
     double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     int reach = 0, err = 0;
-    if (b < nb) {
-        const double* p = partials + b * kPartialStride;
+    const int rows = b < nb ? (nch ? nch[b] : 1) : 0;
+    for (int i = 0; i < rows; ++i) {
+        const double* p = partials + ((int64_t)i * nb + b) * kPartialStride;
 #pragma unroll
-        for (int f = 0; f < 4; ++f) s[f] = p[f];
-        s[4] = p[6];
-        reach = (int)p[4];
-        err = (int)p[5];
+        for (int f = 0; f < 4; ++f) s[f] += p[f];
+        s[4] += p[6];
+        reach = max(reach, (int)p[4]);
+        err |= (int)p[5];
     }
 #pragma unroll
     for (int f = 0; f < 5; ++f) s[f] = wave_sum(s[f]);
@@ -157,31 +159,36 @@ partials_chunk_kernel(double* __restrict__ partials, int64_t nb, const StepCtl* 
 // Sum the per-block partials of one step in a fixed order (deterministic),
 // record the totals, the largest reach and the first failed step.  Rows b
 // stride for b < nb (stride > 1: the chunk heads of partials_chunk_kernel).
-constexpr int kFinTPB = 256;
-__global__ void __launch_bounds__(kFinTPB)
+// A thread's rows are read one after another: 1024 threads from kFinManyRows
+// rows on (4096 rows took 14 us with 256 threads, 10 with 1024; but a step of a
+// few rows, whose latency counts, 3 us more).
+constexpr int kFinTPB = 256, kFinMaxTPB = 1024, kFinManyRows = 1024;
+template <int TPB>
+__global__ void __launch_bounds__(TPB)
 finalize_kernel(const double* __restrict__ partials, int64_t nb, int64_t stride, StepCtl* __restrict__ ctl,
-                long long step, int sp2)
+                long long step, int sp2, const int* __restrict__ nch)
 {
-    __shared__ double s_sum[kFinTPB / 64][5];
-    __shared__ int s_ir[kFinTPB / 64][2];
+    __shared__ double s_sum[TPB / 64][5];
+    __shared__ int s_ir[TPB / 64][2];
     if (threadIdx.x == 0) {  // the step kernels of this step are done with their counters
         for (int i = 0; i < 5; ++i) ctl->next[i] = 0;
-        ctl->keep[1] = ctl->keep[0];
-        ctl->keep[0] = 0;
-        ctl->split_n[(step + 1) & 1] = 0;  // the next step lists its tiles afresh
-        ctl->full_n = 0;
     }
+    if (threadIdx.x < kGivenUp) ctl->given_up[threadIdx.x * kGivenUpStride] = 0;
     if (ctl->err_step < step) return;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     int reach = 0, err = 0;
-    for (int64_t b = tid; b < nb; b += kFinTPB) {
-        const double* p = partials + b * stride * kPartialStride;
+    for (int64_t b = tid; b < nb; b += TPB) {
+        const int rows = nch ? nch[b] : 1;  // (at least 1: the first row need not wait for it)
+        int i = 0;
+        do {
+            const double* p = partials + ((int64_t)i * nb + b) * stride * kPartialStride;
 #pragma unroll
-        for (int f = 0; f < 4; ++f) s[f] += p[f];
-        if (sp2) s[4] += p[6];  // rho chi (square lattice, two gases)
-        reach = max(reach, (int)p[4]);
-        err |= (int)p[5];
+            for (int f = 0; f < 4; ++f) s[f] += p[f];
+            if (sp2) s[4] += p[6];  // rho chi (square lattice, two gases)
+            reach = max(reach, (int)p[4]);
+            err |= (int)p[5];
+        } while (++i < rows);
     }
 #pragma unroll
     for (int f = 0; f < 5; ++f) s[f] = wave_sum(s[f]);
@@ -198,12 +205,12 @@ finalize_kernel(const double* __restrict__ partials, int64_t nb, int64_t stride,
     if (tid == 0) {
         for (int f = 0; f < 5; ++f) {
             double t = s_sum[0][f];
-            for (int w = 1; w < kFinTPB / 64; ++w) t += s_sum[w][f];
+            for (int w = 1; w < TPB / 64; ++w) t += s_sum[w][f];
             if (f < 4) ctl->totals[f] = t;
             else ctl->totals_sp = t;
         }
         int r = s_ir[0][0], e = s_ir[0][1];
-        for (int w = 1; w < kFinTPB / 64; ++w) { r = max(r, s_ir[w][0]); e |= s_ir[w][1]; }
+        for (int w = 1; w < TPB / 64; ++w) { r = max(r, s_ir[w][0]); e |= s_ir[w][1]; }
         ctl->max_reach = r;
         ctl->totals_step = step;
         if (e) {
@@ -603,17 +610,20 @@ hipError_t launch_pool_finalize(const PoolView& v, int nslots, int commit, hipSt
 }
 
 hipError_t launch_finalize(double* partials, int64_t nb, StepCtl* ctl, long long step,
-                           hipStream_t stream, bool species2d)
+                           hipStream_t stream, bool species2d, const int* nch)
 {
     if (nb > 16 * kChunk) {  // many rows: fold each chunk first, on many CUs
         const int64_t g = (nb + kChunk - 1) / kChunk;
-        partials_chunk_kernel<<<(unsigned)g, kChunk, 0, stream>>>(partials, nb, ctl, step);
+        partials_chunk_kernel<<<(unsigned)g, kChunk, 0, stream>>>(partials, nb, ctl, step, nch);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        finalize_kernel<<<1, kFinTPB, 0, stream>>>(partials, g, kChunk, ctl, step, species2d ? 1 : 0);
+        finalize_kernel<kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, g, kChunk, ctl, step, species2d ? 1 : 0, nullptr);
         return hipGetLastError();
     }
-    finalize_kernel<<<1, kFinTPB, 0, stream>>>(partials, nb, 1, ctl, step, species2d ? 1 : 0);
+    if (nb >= kFinManyRows)
+        finalize_kernel<kFinMaxTPB><<<1, kFinMaxTPB, 0, stream>>>(partials, nb, 1, ctl, step, species2d ? 1 : 0, nch);
+    else
+        finalize_kernel<kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, nb, 1, ctl, step, species2d ? 1 : 0, nch);
     return hipGetLastError();
 }
 

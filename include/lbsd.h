@@ -150,13 +150,15 @@ int lb_init_riemann(lb_solver* s, double x_diaphragm, const lb_prim* left, const
 int lb_init_moments(lb_solver* s, const double* host_Y, double lambda);
 
 /* Queue n >= 0 steps (eq. 10 / eq. 30 with tau = 1, Sec. V.A).  Each step
- * queues its step launches on the bound stream -- one kernel in 1-D and on the
- * hexagonal lattice; on the square lattice a first pass over the tiles, and
- * a second one that returns at once unless the first left tiles to it --
- * and then a small kernel that reduces the per-tile partial
- * results into the interior conservation totals and the largest reach.  If a
- * step fails, it and every later queued step leave the state at the last good
- * step; the error is reported at the next synchronising call. */
+ * queues its step launches on the bound stream -- one kernel on the hexagonal
+ * lattice; on the square lattice a first pass over the tiles, and a second one
+ * that returns at once unless the first left tiles to it -- and then a small
+ * kernel that reduces the per-tile partial results into the interior
+ * conservation totals and the largest reach.  In 1-D a kernel makes up to eight
+ * steps (how the steps are split between kernels and calls does not change a
+ * bit of the state), and the reduction is queued once per call.  If a step
+ * fails, it and every later queued step leave the state at the last good step;
+ * the error is reported at the next synchronising call. */
 int lb_step(lb_solver* s, int64_t n);
 
 /* As lb_step, bracketed by HIP events on the bound stream; waits and writes
@@ -215,7 +217,7 @@ const char* lb_last_error(void);
  * rho u lambda, (rho v lambda), rho E lambda^2 (, rho chi); each 256-byte
  * aligned, not overlapping.  The caller owns both; Y_in is only read.  The
  * step's scratch (control block, per-tile partial sums, tile flags) is a
- * static device array per GPU (2 MiB, and 10 MB for the square lattice), which
+ * static device array per GPU (3 MiB, and 10 MB for the square lattice), which
  * the library holds until the process ends; grids that need more are rejected
  * with LB_EINVAL (1-D tubes above about 33 M nodes; a square-lattice grid is
  * cut into about one tile per resident wavefront whatever its size, and only
@@ -236,8 +238,10 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
  * conditions and step target) in an arena of arena_bytes inside the caller's
  * device memory.  One pool step is one kernel launch over a tile table in
  * device memory (square lattice: resident wavefronts that take tiles, plus a
- * second pass over the tiles the first left to it; 1-D: one block per tile) and a per-slot reduction kernel; every live, unfinished
- * slot advances by one step (eq. 10 / 30 with tau = 1, as lb_step).
+ * second pass over the tiles the first left to it) and a per-slot reduction
+ * kernel; every live, unfinished slot advances by one step (eq. 10 / 30 with
+ * tau = 1, as lb_step).  In 1-D a launch has one wavefront per tile and makes as
+ * many steps as the tile shape says, fewer where the call asks for fewer.
  * Admissions and releases rewrite the tables between launches, in stream
  * order: steps queued before them run with the old tables, steps queued
  * after with the new ones, and the host does not wait for the device (so a
@@ -314,10 +318,10 @@ int lb_pool_totals(lb_pool* p, int32_t slot, double out[4]);
 double lb_pool_lambda(const lb_pool* p, int32_t slot);
 int32_t lb_pool_live(const lb_pool* p);                  /* admitted slots */
 
-/* Tile shapes: 1-D, threads x nodes per thread in {256x1, 256x2, 256x4,
- * 256x8, 512x4}; square lattice, tiles of 54 columns whose strip height makes
- * about {2, 3, 4, 6, 8} tiles per resident block over the live problems (at
- * least 16 rows).  lb_pool_autotune times `trials` steps of every shape on the
+/* Tile shapes: 1-D, {1, 2, 4, 6, 8} steps per launch (a tile is the nodes that
+ * one wavefront can bring that far without its neighbours); square lattice,
+ * tiles of 54 columns whose strip height makes about {2, 3, 4, 6, 8} tiles per
+ * resident block over the live problems (at least 16 rows).  lb_pool_autotune times `trials` steps of every shape on the
  * admitted problems without changing their states, keeps the fastest and
  * writes its index and median milliseconds per step. */
 int32_t lb_pool_shapes(const lb_pool* p);

@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <climits>
 #include <mutex>
 #include <string>
@@ -406,46 +407,47 @@ int lb_init_moments(lb_solver* s, const double* Y, double lambda)
     return start_state(s);
 }
 
-// Queue n steps: step kernel + finalize kernel each.  With ev != NULL,
-// ev[2i] / ev[2i+1] are recorded right before / after step i's step kernel.
-static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr)
+// Queue n steps: step kernels and finalize kernel each (1-D: several steps per
+// launch).  With ev != NULL, ev[2i] / ev[2i+1] are recorded right before / after
+// the i-th launch's step kernels; *launches counts them.
+static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr, int64_t* launches = nullptr)
 {
-    const bool march = s->dim == 2 && !s->hex;
+    const bool march = s->dim == 2 && !s->hex, fp64 = s->precision == LB_FP64;
     const MarchWords words = march2d_words(flags_ptr(s), s->nblocks, kSplitMax, true);
-    for (int64_t i = 0; i < n; ++i) {
-        const int in = s->cur, out = s->cur ^ 1;
+    const int64_t group = s->dim == 1 ? tube_group(s->g, s->k, fp64) : 1;
+    int64_t left = n;
+    for (int64_t i = 0; left > 0; ++i) {
+        const int in = s->cur, out = s->cur ^ 1, m = (int)std::min(left, group);
         const long long step = (long long)(s->steps_done + 1);
+        const void* Y = buf_ptr(s, in);
+        void* Yn = buf_ptr(s, out);
+        StepCtl* const ctl = ctl_ptr(s);
+        double* const part = partials_ptr(s);
         hipError_t e;
         if (ev && (e = hipEventRecord(ev[2 * i], s->stream)) != hipSuccess) return hip_fail(e, "event");
-        if (s->dim == 1) {
-            if (s->precision == LB_FP64)
-                e = launch_step1d<double>((const double*)buf_ptr(s, in), (double*)buf_ptr(s, out), s->g,
-                                          s->k, ctl_ptr(s), partials_ptr(s), step, s->stream);
-            else
-                e = launch_step1d<float>((const float*)buf_ptr(s, in), (float*)buf_ptr(s, out), s->g,
-                                         s->k, ctl_ptr(s), partials_ptr(s), step, s->stream);
-        } else if (s->hex) {
-            if (s->precision == LB_FP64)
-                e = launch_hex<double>((const double*)buf_ptr(s, in), (double*)buf_ptr(s, out), s->g, s->k,
-                                       ctl_ptr(s), partials_ptr(s), step, s->stream);
-            else
-                e = launch_hex<float>((const float*)buf_ptr(s, in), (float*)buf_ptr(s, out), s->g, s->k,
-                                      ctl_ptr(s), partials_ptr(s), step, s->stream);
-        } else {
-            if (s->precision == LB_FP64)
-                e = launch_march2d<double>((const double*)buf_ptr(s, in), (double*)buf_ptr(s, out), s->g,
-                                           s->march, s->k, ctl_ptr(s), partials_ptr(s), words, step, s->stream);
-            else
-                e = launch_march2d<float>((const float*)buf_ptr(s, in), (float*)buf_ptr(s, out), s->g,
-                                          s->march, s->k, ctl_ptr(s), partials_ptr(s), words, step, s->stream);
-        }
+        if (s->dim == 1)
+            e = fp64 ? launch_tube<double>((const double*)Y, (double*)Yn, s->g, s->k, ctl, part, step, m, in, m == left,
+                                           s->stream)
+                     : launch_tube<float>((const float*)Y, (float*)Yn, s->g, s->k, ctl, part, step, m, in, m == left,
+                                          s->stream);
+        else if (s->hex)
+            e = fp64 ? launch_hex<double>((const double*)Y, (double*)Yn, s->g, s->k, ctl, part, step, s->stream)
+                     : launch_hex<float>((const float*)Y, (float*)Yn, s->g, s->k, ctl, part, step, s->stream);
+        else
+            e = fp64 ? launch_march2d<double>((const double*)Y, (double*)Yn, s->g, s->march, s->k, ctl, part, words,
+                                              step, s->stream)
+                     : launch_march2d<float>((const float*)Y, (float*)Yn, s->g, s->march, s->k, ctl, part, words, step,
+                                             s->stream);
         if (e != hipSuccess) return hip_fail(e, "step launch");
         if (ev && (e = hipEventRecord(ev[2 * i + 1], s->stream)) != hipSuccess) return hip_fail(e, "event");
-        e = launch_finalize(partials_ptr(s), s->nblocks, ctl_ptr(s), step, s->stream, s->dim == 2 && s->species,
-                            march ? words.nch : nullptr);
-        if (e != hipSuccess) return hip_fail(e, "finalize launch");
+        if (launches) *launches = i + 1;
+        if (s->dim == 2) {
+            e = launch_finalize(part, s->nblocks, ctl, step, in, s->stream, s->species, march ? words.nch : nullptr);
+            if (e != hipSuccess) return hip_fail(e, "finalize launch");
+        }
         s->cur = out;
-        s->steps_done += 1;
+        s->steps_done += m;
+        left -= m;
     }
     return LB_OK;
 }
@@ -471,10 +473,9 @@ int lb_sync(lb_solver* s)
         return hip_fail(e, "read control block");
     if (c.err_code) {
         // step err_step (1-based since init) failed; its input, the state
-        // after err_step - 1 steps, sits in buffer (err_step - 1) & 1.
-        const int64_t good = (int64_t)c.err_step - 1;
-        s->steps_done = good;
-        s->cur = (int)(good & 1);
+        // after err_step - 1 steps, sits in buffer err_buf
+        s->steps_done = (int64_t)c.err_step - 1;
+        s->cur = c.err_buf;
         s->pending_err = (c.err_code & kErrState) ? LB_ESTATE : LB_EREACH;
         return fail(s->pending_err, "step %lld failed: %s", (long long)c.err_step,
                     (c.err_code & kErrState) ? "rho <= 0 or non-finite moment"
@@ -517,11 +518,12 @@ int lb_step_profiled(lb_solver* s, int64_t n, float* kernel_ms, float* total_ms)
     for (; made < ev.size(); ++made)
         if ((e = hipEventCreate(&ev[made])) != hipSuccess) { rc = hip_fail(e, "hipEventCreate"); break; }
     if (rc == LB_OK && (e = hipEventRecord(s->ev0, s->stream)) != hipSuccess) rc = hip_fail(e, "event");
-    if (rc == LB_OK) rc = queue_steps(s, n, ev.data());
+    int64_t launches = 0;
+    if (rc == LB_OK) rc = queue_steps(s, n, ev.data(), &launches);
     if (rc == LB_OK && (e = hipEventRecord(s->ev1, s->stream)) != hipSuccess) rc = hip_fail(e, "event");
     if (rc == LB_OK && (e = hipEventSynchronize(s->ev1)) != hipSuccess) rc = hip_fail(e, "event sync");
     float kt = 0.f, tt = 0.f;
-    for (int64_t i = 0; rc == LB_OK && i < n; ++i) {
+    for (int64_t i = 0; rc == LB_OK && i < launches; ++i) {
         float t = 0.f;
         if ((e = hipEventElapsedTime(&t, ev[2 * i], ev[2 * i + 1])) != hipSuccess) rc = hip_fail(e, "elapsed");
         kt += t;
@@ -681,11 +683,18 @@ int lb_debug_lanes(lb_solver* s, int32_t* fx, int32_t* fy, int32_t* c1)
 namespace {
 
 constexpr size_t kStaticCtlBytes = (sizeof(StepCtl) + 255) / 256 * 256;  // the StepCtl at the front
-// Per device: the control block and, for the 1-D and hexagonal lattices, the
-// partial rows that 2 MiB less 256 bytes hold (1-D tubes of about 33 M
-// nodes); for the square lattice a partial row and three words per tile of
-// the widest grid taken, 132672 column strips (7.16 M columns).
-constexpr size_t kStaticScratchBytes = kStaticCtlBytes + ((size_t)2 << 20) - 256;
+// Per device: the control block and, for the 1-D and hexagonal lattices, partial
+// rows.  A grid is taken if 2 MiB less 256 bytes hold a row per 1024 nodes of a
+// tube (33 549 312 nodes) or per 64 x 4 nodes of the hexagonal lattice; a tube's
+// launch writes at most a row per 720 nodes (two gases in FP64), which is what
+// the scratch is sized for.  For the square lattice a partial row and three words
+// per tile of the widest grid taken, 132672 column strips (7.16 M columns).
+constexpr size_t kStaticRowBytes = ((size_t)2 << 20) - 256;
+constexpr int64_t kStaticMaxTube = (int64_t)(kStaticRowBytes / (kPartialStride * 8)) * 1024;
+constexpr int64_t kStaticTubeRow = 4 * tube_cols(3, 1);
+constexpr size_t kStaticScratchBytes =
+    kStaticCtlBytes + (size_t)((kStaticMaxTube + kStaticTubeRow - 1) / kStaticTubeRow) * kPartialStride * 8;
+static_assert(kStaticTubeRow <= 4 * tube_cols(5, 1) && kStaticScratchBytes >= kStaticCtlBytes + kStaticRowBytes, "");
 constexpr size_t kStaticMarchBytes = kStaticCtlBytes + (size_t)132672 * (kPartialStride * 8 + 12);
 constexpr int kStaticMaxDevices = 64;
 
@@ -776,7 +785,7 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
     char* const base = march ? d->ptr_march : d->ptr;
     StepCtl* ctl = (StepCtl*)base;
     double* partials = (double*)(base + kStaticCtlBytes);
-    size_t need = 0, have = kStaticScratchBytes;
+    size_t need = 0, have = kStaticCtlBytes + kStaticRowBytes;
     if (march) {
         const int pi = s->precision == LB_FP64 ? 0 : 1;
         m = march2d_geometry(s->g, d->cus, d->per_cu[pi], d->per_cu_lean[pi]);
@@ -788,7 +797,7 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
         while (smax > 1 && kStaticCtlBytes + align256(row * smax) + words > have) --smax;
         w = march2d_words((int*)(base + kStaticCtlBytes + align256(row * smax)), rows, smax, false);
     } else {
-        rows = s->dim == 1 ? step_blocks_1d(s->g) : hex_blocks(s->g);
+        rows = s->dim == 1 ? (s->g.nx + 1023) / 1024 : hex_blocks(s->g);
         need = kStaticCtlBytes + align256((size_t)rows * kPartialStride * 8);
     }
     if (need > have)
@@ -802,8 +811,8 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
     if (e != hipSuccess) return hip_fail(e, "reset");
     if (s->dim == 1) {
         e = s->precision == LB_FP64
-            ? launch_step1d<double>((const double*)Y_in, (double*)Y_out, s->g, s->k, ctl, partials, 1, st)
-            : launch_step1d<float>((const float*)Y_in, (float*)Y_out, s->g, s->k, ctl, partials, 1, st);
+            ? launch_tube<double>((const double*)Y_in, (double*)Y_out, s->g, s->k, ctl, partials, 1, 1, 0, true, st)
+            : launch_tube<float>((const float*)Y_in, (float*)Y_out, s->g, s->k, ctl, partials, 1, 1, 0, true, st);
     } else if (s->hex) {
         e = s->precision == LB_FP64
             ? launch_hex<double>((const double*)Y_in, (double*)Y_out, s->g, s->k, ctl, partials, 1, st)
@@ -814,7 +823,7 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
             : launch_march2d<float>((const float*)Y_in, (float*)Y_out, s->g, m, s->k, ctl, partials, w, 1, st);
     }
     if (e != hipSuccess) return hip_fail(e, "step launch");
-    if ((e = launch_finalize(partials, rows, ctl, 1, st, s->dim == 2 && s->species, w.nch)) != hipSuccess)
+    if (s->dim == 2 && (e = launch_finalize(partials, rows, ctl, 1, 0, st, s->species, w.nch)) != hipSuccess)
         return hip_fail(e, "finalize launch");
     if (status_dev && (e = launch_status(ctl, status_dev, st)) != hipSuccess) return hip_fail(e, "status launch");
     return LB_OK;

@@ -23,8 +23,10 @@ struct StepCtl {
     long long totals_step;  // step whose totals are in `totals`
     double totals[4];       // interior sums of the moment fields (lattice units)
     int max_reach;          // largest reach seen in the latest step
-    int pad;
+    int err_buf;            // moment set (0 or 1) that holds the last good state after a failed step
     double totals_sp;       // square lattice with two gases: interior sum of rho chi
+    long long fail_step0;   // 1-D: the launch a step of which failed: its first step,
+    int fail_steps, fail_in;  // its steps and the set it read
     int given_up[kGivenUp * kGivenUpStride];  // square lattice: see kGivenUp (cleared by finalize)
 };
 
@@ -37,13 +39,15 @@ struct Grid {
     int bc_x, bc_y;
 };
 
-// Launch the step kernel of a 1-D / 2-D problem (async on `stream`).  Y and
-// Yn are SoA [nf][ny][nx] arrays of T; partials receives one kPartialStride
-// row per block (step_blocks_1d / march2d_blocks give the count), which
-// launch_finalize then reduces.
+// 1-D: `steps` <= tube_group steps in one launch, step0 the first, from the
+// moment set Y (set in_buf) to Yn (SoA [nf][nx] of T).  The last launch of a call
+// also queues the reduction of its partial rows (step_blocks_1d of them at most)
+// and, if a step of any of the call's launches failed, the return to the last
+// good state, in the set that ctl then names.
 template <typename T>
-hipError_t launch_step1d(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl,
-                         double* partials, long long step, hipStream_t stream);
+hipError_t launch_tube(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
+                       long long step0, int steps, int in_buf, bool last, hipStream_t stream);
+int tube_group(const Grid& g, const Consts& k, bool fp64);
 int64_t step_blocks_1d(const Grid& g);
 
 // Square lattice, column-march kernels (lb_march2d.hpp).  The grid is cut into
@@ -97,7 +101,8 @@ int64_t hex_blocks(const Grid& g);
 // Reduce nb per-block partial rows of one step into ctl (fixed order);
 // species2d: also the rho chi sums of the square lattice with two gases; nch:
 // rows per tile where a tile may have several (MarchWords::nch), else nullptr.
-hipError_t launch_finalize(double* partials, int64_t nb, StepCtl* ctl, long long step,
+// in_buf: the moment set (0 or 1) the step read.
+hipError_t launch_finalize(double* partials, int64_t nb, StepCtl* ctl, long long step, int in_buf,
                            hipStream_t stream, bool species2d = false, const int* nch = nullptr);
 
 // Riemann initial state: node i (cell centre x_lo + (i + 1/2) dx) takes the
@@ -141,12 +146,14 @@ struct PoolProb {       // one slot, written by the host between launches
 };
 
 struct PoolState {      // one slot, written by the device, read by the host after a sync
-    int64_t done;       // good steps so far: the moments are in set (done & 1)
+    int64_t done;       // good steps so far
     int64_t err_step;   // step that failed (0: none); the problem then stops
     int32_t err_code;   // kErr* bits
     int32_t max_reach;  // largest reach of its latest step
     int64_t totals_step;
     double totals[4];   // interior sums after step totals_step (lattice units)
+    int32_t set;        // moment set that holds the moments
+    int32_t pad;
 };
 
 struct PoolTile {        // one tile, with a copy of its slot's grid so a block reads one record
@@ -158,8 +165,9 @@ struct PoolTile {        // one tile, with a copy of its slot's grid so a block 
 };
 
 // Per-tile word kept by the per-slot reduction: bit 0 = the set holding the
-// slot's current moments (done & 1), bit 1 = the slot still steps.
-constexpr int kTileSet = 1, kTileLive = 2;
+// slot's current moments, bit 1 = the slot still steps; 1-D: from bit 8 the
+// steps it has left (at most kTileLeftMax).
+constexpr int kTileSet = 1, kTileLive = 2, kTileLeftShift = 8, kTileLeftMax = 1 << 20;
 
 struct PoolView {
     const PoolProb* probs;
@@ -174,10 +182,16 @@ struct PoolView {
     void* arena;            // moment sets of all slots (T elements)
 };
 
-// Tile shapes of the 1-D pool kernel (threads per block, nodes per thread).
+// Tile shapes of the 1-D pool kernel: the steps a launch makes (a tile is then
+// the tube_cols nodes that a wavefront can bring that far on its own).
 constexpr int kPool1Shapes = 5;
-constexpr int kPool1TPB[kPool1Shapes] = {256, 256, 256, 256, 512};
-constexpr int kPool1J[kPool1Shapes] = {1, 2, 4, 8, 4};
+constexpr int kPool1Steps[kPool1Shapes] = {1, 2, 4, 6, 8};
+// Nodes per lane of a long tube and of the pools' (see lb_tube.hpp): five, or
+// three for two gases in FP64, which would otherwise take 390 registers.
+constexpr int tube_lanes(bool species, bool fp64) { return species && fp64 ? 3 : 5; }
+constexpr int tube_lost(int J) { return (kHalo + J - 1) / J; }                      // halo lanes a step costs
+constexpr int tube_cols(int J, int K) { return (64 - 2 * K * tube_lost(J)) * J; }  // nodes a wavefront stores
+
 // Square-lattice pool tiles: the strip height is chosen so that the live
 // problems make about kPool2TilesPerBlock[shape] tiles per resident block
 // (claim-order balance against the 2L halo rows each tile marches again), and
@@ -187,20 +201,22 @@ constexpr int kPool2TilesPerBlock[kPool2Shapes] = {2, 3, 4, 6, 8};
 constexpr int kPool2MinRows = 16;
 constexpr int kPool2Cols = kMarchCols;  // destination columns per square-lattice tile
 
-// One step of every live tile: the 1-D kernel of tile shape `shape` (nblocks =
-// the number of tiles, one block each), or the square lattice's lean pass
-// followed by the general pass over what it left (resident wavefronts take
-// the tiles).
+// 1-D: up to `steps` <= halo steps of every live slot (nblocks: a wavefront per
+// tile, four per block) and the per-slot reduction, which commits them if
+// commit != 0.
 template <typename T>
-hipError_t launch_pool1d(const PoolView& v, const Consts& k, int shape, int nblocks, bool walls,
+hipError_t launch_pool1d(const PoolView& v, const Consts& k, int halo, int steps, int nblocks, int nslots, int commit,
                          hipStream_t stream);
+// Square lattice, one step of every live tile: the lean pass, then the general
+// pass over what it left (resident wavefronts take the tiles).
 template <typename T>
 hipError_t launch_pool2d(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks, hipStream_t stream);
 // Resident blocks per CU of the pool's general pass (lean = false) or lean pass.
 template <typename T>
 int pool2d_blocks_per_cu(bool lean = false);
-// Per slot: reduce its tiles' partial rows (fixed order) into its state and,
-// when commit != 0 and the step succeeded, count the step.
-hipError_t launch_pool_finalize(const PoolView& v, int nslots, int commit, hipStream_t stream);
+// Per slot of a square-lattice pool: reduce its tiles' partial rows (fixed
+// order) into its state and, when commit != 0 and the step succeeded, count the
+// step.
+hipError_t launch_pool2d_finalize(const PoolView& v, int nslots, int commit, hipStream_t stream);
 
 }  // namespace lbsd

@@ -37,10 +37,7 @@
 //
 // The kernels and helpers below sit in an anonymous namespace: each
 // translation unit that includes this header instantiates its own kernels.
-#include <climits>
-#include <type_traits>
-
-#include "lb_kernels.hpp"
+#include "lb_wave.hpp"
 
 namespace lbsd {
 
@@ -51,53 +48,6 @@ constexpr int kMNW = kMTPB / 64;
 constexpr int kMH = kHalo;               // largest displacement of a packet per axis
 constexpr int kMCols = 64 - 2 * kMH;     // destination columns per tile
 static_assert(kMCols == kMarchCols, "tile width shared with the host");
-
-// ---- lane shifts ----------------------------------------------------------
-// lshr: lane i gets lane i - 1's value (data moves one column up); lshl: lane
-// i gets lane i + 1's.  The end lanes get 0; a chain of at most H shifts
-// leaves the destination lanes exact.
-__device__ __forceinline__ int dpp_r(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, true); }
-__device__ __forceinline__ int dpp_l(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true); }
-__device__ __forceinline__ float lshr(float v) { return __builtin_bit_cast(float, dpp_r(__builtin_bit_cast(int, v))); }
-__device__ __forceinline__ float lshl(float v) { return __builtin_bit_cast(float, dpp_l(__builtin_bit_cast(int, v))); }
-struct Words {
-    int lo, hi;
-};
-__device__ __forceinline__ double lshr(double v)
-{
-    const Words w = __builtin_bit_cast(Words, v);
-    return __builtin_bit_cast(double, Words{dpp_r(w.lo), dpp_r(w.hi)});
-}
-__device__ __forceinline__ double lshl(double v)
-{
-    const Words w = __builtin_bit_cast(Words, v);
-    return __builtin_bit_cast(double, Words{dpp_l(w.lo), dpp_l(w.hi)});
-}
-
-// f(0), f(1) .. f(N - 1) with the index as a compile-time constant (register
-// arrays indexed by it stay in registers whatever the optimiser does before it
-// unrolls loops).
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<N, I + 1>(f);
-    }
-}
-
-// At the end of alternatives that differ only in which element of a register
-// array they change: an empty statement of its own for each, so that the
-// optimiser does not merge them into one that picks the element's address
-// (which would move the array to memory).
-template <int I>
-__device__ __forceinline__ void keep_apart()
-{
-    asm volatile("; alternative %0" ::"i"(I));
-}
-
-__device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // (h, l) += x with the rounding error of h + x carried into l (TwoSum).
 __device__ __forceinline__ void dd_add(double& h, double& l, double x)
@@ -119,67 +69,6 @@ struct MNode {
     T z[REST ? 2 : 1];    // rest-group mass at x corner k
     T chi;                // two gases: mass fraction of gas 1
     int fx, fy, c1;
-};
-
-// Whether every moment is finite, rho > 0 and (FP64) every exponent is small
-// enough for the quotients of march_node to need no scaling: zero or within
-// [2^-511, 2^257), rho and rho E within [2^-255, 2^257).  Integer tests on
-// the high words (the same number of instructions as the plain finiteness
-// tests); states outside take the general form.
-__device__ __forceinline__ bool tame(double m0, double m1, double m2, double m3)
-{
-    const auto hi = [](double v) { return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32); };
-    const auto win = [&](double v) { return hi(v) - 0x30000000u < 0x20000000u; };
-    const auto zwin = [&](double v) { return (hi(v) & 0x7fffffffu) - 0x20000000u < 0x30000000u || v == 0.0; };
-    return win(m0) && zwin(m1) && zwin(m2) && win(m3);
-}
-__device__ __forceinline__ bool tame(float m0, float m1, float m2, float m3)
-{
-    const auto b = [](float v) { return __builtin_bit_cast(uint32_t, v); };
-    return b(m0) - 1u < 0x7f7fffffu && (b(m1) & 0x7fffffffu) < 0x7f800000u && (b(m2) & 0x7fffffffu) < 0x7f800000u &&
-           (b(m3) & 0x7fffffffu) < 0x7f800000u;
-}
-__device__ __forceinline__ bool zero_or_normal(double v)
-{
-    const uint32_t h = (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32);
-    return (h & 0x7fffffffu) - 0x20000000u < 0x30000000u || v == 0.0;
-}
-__device__ __forceinline__ bool zero_or_normal(float v)
-{
-    return (__builtin_bit_cast(uint32_t, v) & 0x7fffffffu) < 0x7f800000u;
-}
-
-// Quotients by one divisor.  FP64 storage: correctly rounded (floor(v) and
-// c'_1 then match the plain definition bit for bit).  For tame operands the
-// reciprocal (hardware estimate, two Newton steps) is shared between the
-// quotients and each takes one correction, RN(q + (a - b q) y): the operations
-// of the compiler's own division without its per-quotient scaling, so the
-// same bits, at 3 instructions per quotient after 5 for the reciprocal
-// against 11 each.  FP32 storage (whose decisions need not match bit for
-// bit): one Newton step and a product.
-template <bool FAST, bool IEEE>
-struct Quot {
-    double b, y;
-    __device__ __forceinline__ explicit Quot(double d) : b(d), y(0.0)
-    {
-        if constexpr (!IEEE || FAST) {
-            y = __builtin_amdgcn_rcp(d);
-            y = __builtin_fma(y, __builtin_fma(-d, y, 1.0), y);
-            if constexpr (!FAST) y = __builtin_fma(y, __builtin_fma(-d, y, 1.0), y);
-        }
-    }
-    __device__ __forceinline__ double operator()(double a) const
-    {
-#pragma clang fp contract(off)
-        if constexpr (FAST) {
-            return a * y;
-        } else if constexpr (IEEE) {
-            return a / b;
-        } else {
-            const double q = a * y;
-            return __builtin_fma(__builtin_fma(-b, q, a), y, q);
-        }
-    }
 };
 
 // Per-node primitives (eq. 15, 24-26, 28-29) in FP64 whatever the storage
@@ -506,9 +395,6 @@ __device__ __forceinline__ void march_partials(double (&tot)[NF], int reach, boo
     }
 }
 
-// Largest displacement of a class along an axis: max(f + 1 + c'_2, c'_2 - f).
-__device__ __forceinline__ int class_reach(int F, int C) { return C + 2 + (F < 0 ? -F - 1 : F); }
-
 // The lean pass, one tile of rows [Y0, ylast): x-planar flows, every source
 // staged with v_y = 0 exactly, c'_1 <= kSpeeds - 2 and a reach within H.  A
 // packet then moves at most LB = kSpeeds - 1 rows, stage A needs no row FIFO
@@ -541,7 +427,7 @@ __device__ __forceinline__ bool march_tile_lean(const MarchIO<T, SP ? 5 : 4>& io
     for (int r = 0; r < nrows; ++r) {
         const T r0 = cur[0], r1 = io.mir_x ? -cur[1] : cur[1], r3 = cur[3];
         const bool vy0 = cur[2] == (T)0;  // a mirrored row's sign does not matter
-        bool ok = tame(r0, r1, (T)0, r3);
+        bool ok = tame(r0, r1, (T)0, r3) && (!REST || k.delta0 <= kTameDelta0);
         if constexpr (SP) ok = ok && zero_or_normal(cur[NF - 1]);
         if (!__all(vy0)) return false;
         MNode<T, REST, SP> s;
@@ -734,7 +620,7 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
 #pragma unroll 1
     for (int r = 0; r < nrows; ++r) {
         const T r0 = cur[0], r1 = io.mir_x ? -cur[1] : cur[1], r2 = mir_y ? -cur[2] : cur[2], r3 = cur[3];
-        bool ok = tame(r0, r1, r2, r3);
+        bool ok = tame(r0, r1, r2, r3) && (!REST || k.delta0 <= kTameDelta0);
         if constexpr (SP) ok = ok && zero_or_normal(cur[NF - 1]);
         MNode<T, REST, SP> s;
         bool badw = false;

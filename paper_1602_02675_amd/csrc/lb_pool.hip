@@ -76,7 +76,6 @@ struct lb_pool {
     int shape = 0;    // 1-D: kernel tile shape; 2-D: strip height index
     int nblocks = 0;  // blocks of the current shape (square lattice: of the general pass)
     int nblocks_lean = 0;  // square lattice: blocks of the lean pass
-    bool walls = false;  // 1-D: a live slot has reflecting walls: run the kernels that handle them
     // graph of `graph_steps` steps (0: plain launches)
     int graph_steps = 0;
     bool graph_ready = false;
@@ -110,11 +109,15 @@ PoolView view_of(const lb_pool* p)
 
 size_t set_bytes(const lb_pool* p, int64_t nn) { return align256((size_t)p->nf * (size_t)nn * p->elem); }
 
-int64_t tile_cols(const lb_pool* p) { return p->dim == 1 ? (int64_t)kPool1TPB[p->shape] * kPool1J[p->shape] : kPool2Cols; }
+int64_t tube_tile(const lb_pool* p, int shape)
+{
+    return tube_cols(tube_lanes(p->species, p->precision == LB_FP64), kPool1Steps[shape]);
+}
+int64_t tile_cols(const lb_pool* p) { return p->dim == 1 ? tube_tile(p, p->shape) : kPool2Cols; }
 int64_t tiles_of(const lb_pool* p, int64_t nx, int64_t ny, int shape)
 {
     if (p->dim == 1) {
-        const int64_t t = (int64_t)kPool1TPB[shape] * kPool1J[shape];
+        const int64_t t = tube_tile(p, shape);
         return (nx + t - 1) / t;
     }
     return ((nx + kPool2Cols - 1) / kPool2Cols) * ((ny + kPool2MinRows - 1) / kPool2MinRows);  // at most
@@ -154,13 +157,13 @@ int64_t live_max_tiles(const lb_pool* p)
     return n;
 }
 
-// Blocks of the step launch.  Square lattice: persistent blocks (as many as
-// are resident at once) that claim tiles, so that slow tiles spread out.  1-D:
-// one block per tile (tiles cost about the same, and the hardware then
-// overlaps one tile's loads with other tiles' work).
+// Blocks (of four wavefronts) of the step launch.  Square lattice: as many as
+// are resident at once, whose wavefronts take tiles, so that slow tiles spread
+// out.  1-D: one wavefront per tile (tiles cost about the same, and the
+// hardware then overlaps one tile's loads with other tiles' work).
 int launch_blocks(const lb_pool* p, int64_t ntiles, bool lean)
 {
-    if (p->dim == 1) return (int)std::max<int64_t>(1, ntiles);
+    if (p->dim == 1) return (int)std::max<int64_t>(1, (ntiles + 3) / 4);
     const int per_cu = p->precision == LB_FP64 ? pool2d_blocks_per_cu<double>(lean) : pool2d_blocks_per_cu<float>(lean);
     return std::max(1, p->cus * per_cu);
 }
@@ -180,7 +183,10 @@ __global__ void pool_tile_words_kernel(PoolView v, int32_t nt)
     if (t >= nt) return;
     const int32_t i = v.tiles[t].prob;
     const PoolState& q = v.state[i];
-    v.tstate[t] = (int32_t)(q.done & 1) | (q.err_step == 0 && q.done < v.probs[i].target ? kTileLive : 0);
+    const int64_t left = v.probs[i].target - q.done;
+    v.tstate[t] = q.set | (q.err_step == 0 && left > 0
+                               ? kTileLive | (int32_t)min(left, (int64_t)kTileLeftMax) << kTileLeftShift
+                               : 0);
 }
 
 // A fresh state record for a slot being admitted.
@@ -223,14 +229,10 @@ int upload_tables(lb_pool* p)
     if ((int64_t)p->tiles.size() > p->max_tiles) return fail(LB_ENOMEM, "tile table full");
     const int32_t nt = (int32_t)p->tiles.size();
     const int nb = launch_blocks(p, nt), nb_lean = launch_blocks(p, nt, true);
-    bool walls = false;
-    for (const PoolProb& q : p->probs)
-        walls |= p->dim == 1 && q.active && q.bc_x == kBcReflecting;  // (the square lattice's kernels take walls at run time)
-    if (nb != p->nblocks || nb_lean != p->nblocks_lean || walls != p->walls) {  // a captured graph is stale
+    if (nb != p->nblocks || nb_lean != p->nblocks_lean) {  // a captured graph is stale
         drop_graph(p);
         p->nblocks = nb;
         p->nblocks_lean = nb_lean;
-        p->walls = walls;
     }
     // probs, tile count and tiles through a pinned staging
     const size_t pb = p->probs.size() * sizeof(PoolProb), tb = (size_t)nt * sizeof(PoolTile);
@@ -288,21 +290,38 @@ int set_shape(lb_pool* p, int shape)
     return rc;
 }
 
-// One step of every live slot: step kernel(s), then the per-slot reduction.
-int queue_step(lb_pool* p, int commit)
+// Steps of one launch at most: 1-D tiles bring several steps at once.
+int group_steps(const lb_pool* p) { return p->dim == 1 ? kPool1Steps[p->shape] : 1; }
+
+// Up to n <= group_steps(p) steps of every live slot: step kernel(s), then the
+// per-slot reduction.
+int queue_group(lb_pool* p, int n, int commit)
 {
     const PoolView v = view_of(p);
     hipError_t e;
-    if (p->dim == 1)
-        e = p->precision == LB_FP64 ? launch_pool1d<double>(v, p->k, p->shape, p->nblocks, p->walls, p->stream)
-                                    : launch_pool1d<float>(v, p->k, p->shape, p->nblocks, p->walls, p->stream);
-    else
+    if (p->dim == 1) {
+        const int halo = kPool1Steps[p->shape];
         e = p->precision == LB_FP64
-            ? launch_pool2d<double>(v, p->k, p->nblocks_lean, p->nblocks, p->stream)
-            : launch_pool2d<float>(v, p->k, p->nblocks_lean, p->nblocks, p->stream);
+            ? launch_pool1d<double>(v, p->k, halo, n, p->nblocks, p->max_slots, commit, p->stream)
+            : launch_pool1d<float>(v, p->k, halo, n, p->nblocks, p->max_slots, commit, p->stream);
+        return e == hipSuccess ? LB_OK : hip_fail(e, "pool step launch");
+    }
+    e = p->precision == LB_FP64 ? launch_pool2d<double>(v, p->k, p->nblocks_lean, p->nblocks, p->stream)
+                                : launch_pool2d<float>(v, p->k, p->nblocks_lean, p->nblocks, p->stream);
     if (e != hipSuccess) return hip_fail(e, "pool step launch");
-    if ((e = launch_pool_finalize(v, p->max_slots, commit, p->stream)) != hipSuccess)
+    if ((e = launch_pool2d_finalize(v, p->max_slots, commit, p->stream)) != hipSuccess)
         return hip_fail(e, "pool finalize launch");
+    return LB_OK;
+}
+
+// n steps as launches.
+int queue_plain(lb_pool* p, int64_t n)
+{
+    const int g = group_steps(p);
+    for (int64_t left = n; left > 0; left -= g) {
+        const int rc = queue_group(p, (int)std::min<int64_t>(g, left), 1);
+        if (rc != LB_OK) return rc;
+    }
     return LB_OK;
 }
 
@@ -312,8 +331,7 @@ int capture_graph(lb_pool* p)
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
-    int rc = LB_OK;
-    for (int i = 0; i < p->graph_steps && rc == LB_OK; ++i) rc = queue_step(p, 1);
+    const int rc = queue_plain(p, p->graph_steps);
     e = hipStreamEndCapture(p->stream, &graph);
     if (rc != LB_OK) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -347,11 +365,7 @@ int queue_steps(lb_pool* p, int64_t n)
             if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
         }
     }
-    for (; left > 0; --left) {
-        const int rc = queue_step(p, 1);
-        if (rc != LB_OK) return rc;
-    }
-    return LB_OK;
+    return queue_plain(p, left);
 }
 
 int read_state(lb_pool* p, int32_t slot, PoolState* st)
@@ -504,10 +518,10 @@ static int create_pool(int32_t dim, double gamma, double gamma2, bool species, c
     p->max_slots = max_slots;
     p->arena_bytes = arena_bytes & ~(size_t)255;
     // every live slot has at most one partly filled tile row/column per
-    // shape; the rest of its tiles are full (>= 256 nodes in 1-D, >= 54 x 16
+    // shape; the rest of its tiles are full (>= 96 nodes in 1-D, >= 54 x 16
     // on the square lattice)
     const int64_t cap_nodes = (int64_t)(p->arena_bytes / (2 * (size_t)p->nf * p->elem));
-    p->max_tiles = (int64_t)max_slots * (dim == 1 ? 1 : 320) + cap_nodes / (dim == 1 ? 256 : 49) + (dim == 1 ? 64 : 320);
+    p->max_tiles = (int64_t)max_slots * (dim == 1 ? 3 : 320) + cap_nodes / (dim == 1 ? 85 : 49) + (dim == 1 ? 128 : 320);
     try {
         p->probs.assign((size_t)max_slots, PoolProb{});
         p->info.assign((size_t)max_slots, SlotInfo{});
@@ -516,7 +530,7 @@ static int create_pool(int32_t dim, double gamma, double gamma2, bool species, c
         delete p;
         return fail(LB_ENOMEM, "host allocation failed");
     }
-    p->shape = dim == 1 ? 2 : 3;  // 1024-node tiles / 128-row strips until tuned
+    p->shape = dim == 1 ? 2 : 3;  // four steps per launch / 6 tiles per block until tuned
     p->off_probs = 0;
     p->off_state = align256((size_t)max_slots * sizeof(PoolProb));
     p->off_tiles = p->off_state + align256((size_t)max_slots * sizeof(PoolState));
@@ -739,7 +753,7 @@ int lb_pool_moments(lb_pool* p, int32_t slot, double* out, int32_t on_device)
     const int64_t nn = si.grid.nx * si.grid.ny;
     double sc[5];
     field_scales(p->nf, p->dim + 1, si.lambda, sc);
-    const void* src = set_ptr(p, slot, (int)(st.done & 1));
+    const void* src = set_ptr(p, slot, st.set);
     hipError_t e;
     if (on_device) {
         e = p->precision == LB_FP64 ? launch_export<double>((const double*)src, out, nn, p->nf, sc, p->stream)
@@ -832,18 +846,19 @@ int lb_pool_autotune(lb_pool* p, int32_t trials, int32_t* best, float* ms_per_st
         if (rc != LB_OK) return rc;
         // trial steps read the current sets and write the other ones without
         // counting a step: the slots' states are unchanged
-        if ((rc = queue_step(p, 0)) != LB_OK) return rc;  // warm-up
+        const int g = group_steps(p);  // (the time of a launch over its steps)
+        if ((rc = queue_group(p, g, 0)) != LB_OK) return rc;  // warm-up
         std::vector<float> t((size_t)trials);
         for (int i = 0; i < trials; ++i) {
             if ((e = hipEventRecord(p->ev0, p->stream)) != hipSuccess) return hip_fail(e, "event");
-            if ((rc = queue_step(p, 0)) != LB_OK) return rc;
+            if ((rc = queue_group(p, g, 0)) != LB_OK) return rc;
             if ((e = hipEventRecord(p->ev1, p->stream)) != hipSuccess) return hip_fail(e, "event");
             if ((e = hipEventSynchronize(p->ev1)) != hipSuccess) return hip_fail(e, "event sync");
             if ((e = hipEventElapsedTime(&t[(size_t)i], p->ev0, p->ev1)) != hipSuccess)
                 return hip_fail(e, "elapsed");
         }
         std::sort(t.begin(), t.end());
-        const float med = t[t.size() / 2];
+        const float med = t[t.size() / 2] / (float)g;
         if (arg < 0 || med < best_ms) {
             arg = s;
             best_ms = med;

@@ -1,114 +1,20 @@
-// The tau = 1 step of the semi-discrete compressible LB method on the 1-D
-// triple-level lattice as one fused gather kernel per step (Komeili, Mirzaei,
-// Shabouei, arXiv 1602.02675, Sec. III-V), and the per-step reduction kernel
-// shared with the square lattice (whose step kernel is in lb_march2d.hip).
-//
-// With tau = 1 the distribution after a step is the migrated equilibrium
-// (eq. 10, eq. 30), and the equilibrium depends on the node moments only, so
-// the whole state is the SoA moment field Y = (rho, rho v, rho E) (eq. 7) and a
-// step maps Y to Y'.  Every node (source) emits packets m (1, v + c', zeta) to
-// x + floor(v) + k + c' (eq. 11-13, 21, 23); Y' at a node is the sum of what
-// lands there (Sec. V.A).
-//
-// GPU formulation (deterministic gather, no atomics on field data):
-//   1. a block stages the sources of its destination tile plus a halo of H
-//      nodes in LDS, reduced to (f, r, c'_1, d_v, K) per source
-//      (lb_device.hpp);
-//   2. every destination rebuilds each packet class (lane, corner) from the
-//      source that class maps onto it.  In a tile where floor(v) and c'_1 are
-//      the same for every staged source (the integer parts of the migration
-//      vectors are piecewise constant), each class has exactly one source at
-//      a compile-time offset, and the 10 packets are fully unrolled;
-//      otherwise every candidate displacement in the tile's range is tested
-//      against the source's own displacement;
-//   3. the interior sums of the new moments are reduced per block with
-//      wavefront shuffles into one row of per-block partials; a one-block
-//      kernel then adds the rows in a fixed order (deterministic totals) and
-//      records the reach (halo overflow) and state checks.
-#include <climits>
-
-#include "lb_kernels.hpp"
+// The 1-D step kernels (how a wavefront makes its steps is in lb_tube.hpp) and
+// the per-step reductions, of which the square and hexagonal lattices use the
+// plain one.  Steps write one row of partial results per block; a one-block
+// kernel then adds the rows in a fixed order (deterministic totals) and records
+// the reach (halo overflow) and state checks.  No atomics or device-scope fences
+// in the step kernels: the kernel boundary orders the rows.
+#include "lb_tube.hpp"
 
 namespace lbsd {
 
 namespace {
 
-__device__ __forceinline__ int pack_lane(int fx, int fy, int c1)
-{
-    fx = fx < -127 ? -127 : (fx > 127 ? 127 : fx);
-    fy = fy < -127 ? -127 : (fy > 127 ? 127 : fy);
-    c1 = c1 > 255 ? 255 : c1;
-    return (fx + 128) | ((fy + 128) << 8) | (c1 << 16);
-}
-__device__ __forceinline__ int lane_fx(int p) { return (p & 255) - 128; }
-__device__ __forceinline__ int lane_fy(int p) { return ((p >> 8) & 255) - 128; }
-__device__ __forceinline__ int lane_c1(int p) { return (p >> 16) & 255; }
-
-// Integer summary of the staged sources of one block.
-struct TileInfo {
-    int fxmin, fxmax, fymin, fymax, cmin, cmax, reach, bad;
-};
-
-template <int NW>
-__device__ __forceinline__ TileInfo block_tile_info(TileInfo t, int (*s_red)[8])
-{
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    t.fxmin = wave_min(t.fxmin); t.fxmax = wave_max(t.fxmax);
-    t.fymin = wave_min(t.fymin); t.fymax = wave_max(t.fymax);
-    t.cmin = wave_min(t.cmin);   t.cmax = wave_max(t.cmax);
-    t.reach = wave_max(t.reach); t.bad = wave_max(t.bad);
-    if (lane == 0) {
-        s_red[wid][0] = t.fxmin; s_red[wid][1] = t.fxmax;
-        s_red[wid][2] = t.fymin; s_red[wid][3] = t.fymax;
-        s_red[wid][4] = t.cmin;  s_red[wid][5] = t.cmax;
-        s_red[wid][6] = t.reach; s_red[wid][7] = t.bad;
-    }
-    __syncthreads();
-    TileInfo r = {s_red[0][0], s_red[0][1], s_red[0][2], s_red[0][3],
-                  s_red[0][4], s_red[0][5], s_red[0][6], s_red[0][7]};
-#pragma unroll
-    for (int w = 1; w < NW; ++w) {
-        r.fxmin = min(r.fxmin, s_red[w][0]); r.fxmax = max(r.fxmax, s_red[w][1]);
-        r.fymin = min(r.fymin, s_red[w][2]); r.fymax = max(r.fymax, s_red[w][3]);
-        r.cmin = min(r.cmin, s_red[w][4]);   r.cmax = max(r.cmax, s_red[w][5]);
-        r.reach = max(r.reach, s_red[w][6]); r.bad = max(r.bad, s_red[w][7]);
-    }
-    return r;
-}
-
-// Epilogue: per-block field sums and checks -> one row of `partials`.  No
-// atomics or device-scope fences here: the reduction over blocks is a separate
-// single-block kernel (finalize_kernel), so the kernel boundary orders it.
-template <int NW, int NF>
-__device__ void finish_step(double (&acc)[NF], const TileInfo& ti, double* __restrict__ prow, int H)
-{
-    __shared__ double s_sum[NW][4];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) acc[f] = wave_sum(acc[f]);
-    if (lane == 0) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) s_sum[wid][f] = acc[f];
-    }
-    __syncthreads();
-    if (tid == 0) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            double s = s_sum[0][f];
-            for (int w = 1; w < NW; ++w) s += s_sum[w][f];
-            prow[f] = s;
-        }
-        for (int f = NF; f < 4; ++f) prow[f] = 0.0;
-        prow[4] = (double)ti.reach;
-        prow[5] = (double)((ti.reach > H ? kErrReach : 0) | (ti.bad ? kErrState : 0));
-    }
-}
-
-// First stage of the reduction of many partial rows (a 1-D step has one row
-// per 1024 nodes, 16 K rows at 2^24 nodes, too many for one block to read
-// quickly; with nch, tile b has nch[b] rows, i nb + b): block g folds tiles [g kChunk, (g + 1) kChunk) in a fixed order
-// (sums, largest reach, error bits) into row g kChunk, the first of its own
-// chunk, so that blocks never touch each other's rows.
+// First stage of the reduction of many partial rows (too many for one block to
+// read quickly; with nch, tile b has nch[b] rows, i nb + b): block g folds tiles
+// [g kChunk, (g + 1) kChunk) in a fixed order (sums, largest reach, error bits)
+// into row g kChunk, the first of its own chunk, so that blocks never touch each
+// other's rows.
 constexpr int kChunk = 256;
 __global__ void __launch_bounds__(kChunk)
 partials_chunk_kernel(double* __restrict__ partials, int64_t nb, const StepCtl* __restrict__ ctl, long long step,
@@ -166,7 +72,7 @@ constexpr int kFinTPB = 256, kFinMaxTPB = 1024, kFinManyRows = 1024;
 template <int TPB>
 __global__ void __launch_bounds__(TPB)
 finalize_kernel(const double* __restrict__ partials, int64_t nb, int64_t stride, StepCtl* __restrict__ ctl,
-                long long step, int sp2, const int* __restrict__ nch)
+                long long step, int sp2, const int* __restrict__ nch, int in_buf)
 {
     __shared__ double s_sum[TPB / 64][5];
     __shared__ int s_ir[TPB / 64][2];
@@ -216,270 +122,282 @@ finalize_kernel(const double* __restrict__ partials, int64_t nb, int64_t stride,
         if (e) {
             ctl->err_code = e;
             ctl->err_step = step;
+            ctl->err_buf = in_buf;  // its input, which it left intact
         }
     }
 }
 
 // ------------------------------------------------------------------ 1-D ----
 
-// The staged sources of a 1-D tile.  Of the level weights only d_2 is staged,
-// with rho: d_0 = delta0 rho and d_1 = (rho - b_0 d_0) / b_1 - d_2 are formed
-// again where a packet needs them, with the source's own expressions (the
-// same values for FP64 storage), which keeps a tile's LDS small enough for a
-// fourth block per CU.
-template <typename T>
-struct Tile1 {
-    int* pk;
-    T *r, *rho, *d2, *K;  // rho: 0 for a bad source (its packets are then empty)
-    T* chi;  // two gases: mass fraction of gas 1 per source
-    T delta0, b0, inv_b1;
-};
-
-// One packet of a 1-D source s at displacement k + c' from its floor node:
-// mass alpha_k d, momentum m (v + c'), energy m (K + c' v + c'^2/2); with two
-// gases (SP) also the species moment m chi.
-template <typename T, bool SP>
-__device__ __forceinline__ void add_packet1(const Tile1<T>& tl, int s, int f, int k, int lane_c,
-                                            int lev, T& R, T& P, T& En, T& X)
+// Outcomes of wavefronts or blocks combined: the earliest failing step counts,
+// then its error bits and largest reach.
+__device__ __forceinline__ TubeOut worse(const TubeOut& a, const TubeOut& b)
 {
-#pragma clang fp contract(off)
-    const T r = tl.r[s];
-    const T a = k ? r : (T)1 - r;
-    T d;
-    if (lev == 2) {
-        d = tl.d2[s];
-    } else {
-        const T rho = tl.rho[s];
-        const T d0 = tl.delta0 * rho;
-        d = lev == 0 ? d0 : (rho - tl.b0 * d0) * tl.inv_b1 - tl.d2[s];
-    }
-    const T m = a * d;
-    const T v = (T)f + r;
-    const T c = (T)lane_c;
-    const T xi = v + c;
-    const T zeta = tl.K[s] + c * v + (T)0.5 * c * c;
-    R += m;
-    P += m * xi;
-    En += m * zeta;
-    if constexpr (SP) X += m * tl.chi[s];
+    const int ea = a.errsub ? a.errsub : INT_MAX, eb = b.errsub ? b.errsub : INT_MAX;
+    if (ea < eb) return a;
+    if (eb < ea) return b;
+    return TubeOut{max(a.reach, b.reach), a.err | b.err, a.errsub};
+}
+__device__ __forceinline__ TubeOut wave_worse(TubeOut o)
+{
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1)
+        o = worse(o, TubeOut{__shfl_xor(o.reach, m, 64), __shfl_xor(o.err, m, 64), __shfl_xor(o.errsub, m, 64)});
+    return o;
 }
 
-// Lane l of the 1-D set: 0 rest (d0), 1/2 +-c1 (d1), 3/4 +-c2 (d2).
-__device__ __forceinline__ constexpr int lane_level1(int l) { return l == 0 ? 0 : (l <= 2 ? 1 : 2); }
-__device__ __forceinline__ constexpr int lane_sign1(int l) { return l == 0 ? 0 : ((l & 1) ? 1 : -1); }
-
-template <typename T, int H, int TPB, int J, int C1, bool SP, int NF>
-__device__ __forceinline__ void gather1_uniform(const Tile1<T>& tl, int f, int64_t x0, int64_t nx,
-                                                T* __restrict__ Yn, double (&acc)[NF])
+// A row of partials of the 1-D kernels: sums, reach and error bits as
+// elsewhere; index 7 the failing step of the launch (TubeOut::errsub).
+__device__ __forceinline__ void put_row(double* __restrict__ row, const double (&s)[4], const TubeOut& o)
 {
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int t = j * TPB + (int)threadIdx.x;
-        const int base = t + H - f;  // source of displacement f + o is base - o
-        T R = 0, P = 0, En = 0, X = 0;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-#pragma unroll
-            for (int l = 0; l < 5; ++l) {
-                const int lev = lane_level1(l);
-                const int c = lane_sign1(l) * (lev == 0 ? 0 : C1 + lev - 1);
-                add_packet1<T, SP>(tl, base - (k + c), f, k, c, lev, R, P, En, X);
-            }
-        }
-        const int64_t x = x0 + t;
-        if (x < nx) {
-            Yn[x] = R;
-            Yn[nx + x] = P;
-            Yn[2 * nx + x] = En;
-            acc[0] += (double)R;
-            acc[1] += (double)P;
-            acc[2] += (double)En;
-            if constexpr (SP) {
-                Yn[3 * nx + x] = X;
-                acc[3] += (double)X;
-            }
-        }
-    }
+    for (int f = 0; f < 4; ++f) row[f] = s[f];
+    row[4] = (double)o.reach;
+    row[5] = (double)o.err;
+    row[6] = 0.0;
+    row[7] = (double)o.errsub;
+}
+__device__ __forceinline__ TubeOut row_out(const double* __restrict__ row)
+{
+    return TubeOut{(int)row[4], (int)row[5], (int)row[7]};
 }
 
-template <typename T, int H, int TPB, int J, bool SP, int NF>
-__device__ void gather1_general(const Tile1<T>& tl, const TileInfo& ti, int64_t x0, int64_t nx,
-                                T* __restrict__ Yn, double (&acc)[NF])
+// The block's sums and outcome, in wavefront order, in every thread.
+template <int NW>
+__device__ __forceinline__ TubeOut block_rows(double (&s)[4], TubeOut o)
 {
-    for (int j = 0; j < J; ++j) {
-        const int t = j * TPB + (int)threadIdx.x;
-        T R = 0, P = 0, En = 0, X = 0;
-        for (int k = 0; k < 2; ++k) {
-            for (int l = 0; l < 5; ++l) {
-                const int lev = lane_level1(l), sg = lane_sign1(l);
-                int clo = 0, chi = 0;
-                if (lev > 0) {
-                    const int a = ti.cmin + lev - 1, b = ti.cmax + lev - 1;
-                    clo = sg > 0 ? a : -b;
-                    chi = sg > 0 ? b : -a;
-                }
-                const int lo = max(-H, ti.fxmin + k + clo), hi = min(H, ti.fxmax + k + chi);
-                for (int dl = lo; dl <= hi; ++dl) {
-                    const int s = t + H - dl;
-                    const int p = tl.pk[s];
-                    const int fs = lane_fx(p);
-                    const int cs = lev == 0 ? 0 : sg * (lane_c1(p) + lev - 1);
-                    if (fs + k + cs != dl) continue;
-                    add_packet1<T, SP>(tl, s, fs, k, cs, lev, R, P, En, X);
-                }
-            }
-        }
-        const int64_t x = x0 + t;
-        if (x < nx) {
-            Yn[x] = R;
-            Yn[nx + x] = P;
-            Yn[2 * nx + x] = En;
-            acc[0] += (double)R;
-            acc[1] += (double)P;
-            acc[2] += (double)En;
-            if constexpr (SP) {
-                Yn[3 * nx + x] = X;
-                acc[3] += (double)X;
-            }
+    __shared__ double s_sum[NW][4];
+    __shared__ TubeOut s_out[NW];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) s[f] = wave_sum(s[f]);
+    o = wave_worse(o);
+    __syncthreads();
+    if (lane == 0) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) s_sum[wid][f] = s[f];
+        s_out[wid] = o;
+    }
+    __syncthreads();
+    const int nw = min(NW, (int)(blockDim.x >> 6));
+    o = s_out[0];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) s[f] = s_sum[0][f];
+    for (int w = 1; w < nw; ++w) {
+        o = worse(o, s_out[w]);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) s[f] += s_sum[w][f];
+    }
+    return o;
+}
+
+constexpr int kTubeTPB = 256, kTubeNW = kTubeTPB / 64;
+// Wavefronts per SIMD.  Five nodes per lane take 240 registers in FP64 and with
+// two gases; one gas in FP32 fits three wavefronts with 20 registers spilled
+// (2^24 nodes 92 us per step, two wavefronts without spills 105).
+template <typename T, bool SP, int J>
+constexpr int kTubeWpe = J > 2 && sizeof(T) == 4 && !SP ? 3 : 2;
+
+// `steps` steps, step0 the first: one tile per wavefront, one row of partials
+// per block.  A failure is entered in ctl at once, so that the launches queued
+// behind return without touching the failed launch's input.
+template <typename T, bool SP, int J>
+__global__ void __launch_bounds__(kTubeTPB) __attribute__((amdgpu_waves_per_eu(kTubeWpe<T, SP, J>)))
+tube_kernel(const T* __restrict__ Y, T* __restrict__ Yn, int64_t nx, int bc, Consts k, StepCtl* __restrict__ ctl,
+            double* __restrict__ partials, long long step0, int steps, int64_t ntiles, int in_buf)
+{
+    __shared__ TubeEdges<T> s_edges[kTubeNW];
+    __shared__ TubeStash<T, SP, J> s_stash[kTubeNW];
+    if (ctl->err_step < step0) return;  // an earlier step failed: keep its input intact
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t tile = (int64_t)blockIdx.x * kTubeNW + wid;
+    double tot[SP ? 4 : 3] = {};
+    TubeOut o{0, 0, 0};
+    if (tile < ntiles)
+        o = tube_run<T, SP, J>(Y, Yn, nx, bc, tile * tube_cols(J, steps), steps, steps, k, s_edges[wid], s_stash[wid],
+                               tot);
+    double s[4] = {tot[0], tot[1], tot[2], SP ? tot[SP ? 3 : 0] : 0.0};
+    o = block_rows<kTubeNW>(s, o);
+    if (threadIdx.x == 0) {
+        put_row(partials + (int64_t)blockIdx.x * kPartialStride, s, o);
+        if (o.errsub) {
+            atomicMin((unsigned long long*)&ctl->err_step, (unsigned long long)(step0 + o.errsub - 1));
+            ctl->fail_step0 = step0;  // (every failing block of the launch writes the same)
+            ctl->fail_steps = steps;
+            ctl->fail_in = in_buf;
         }
     }
 }
 
-// One tile of TPB * J destinations starting at x0 of a tube of nx nodes, in
-// two phases: tile1d_load reads its sources (plus a halo of H, clamped or
-// wrapped) into registers; tile1d_gather stages them in LDS, gathers, writes
-// Yn and adds the tile's new moments to acc, returning the tile's integer
-// summary.  Splitting them lets a persistent block load its next tile while
-// it gathers the current one.  tile1d_gather contains block-wide barriers:
-// every thread of the block must call it.  WALLS instances also handle
-// reflecting walls (the others keep no per-source mirror state); SP instances
-// carry the species moment of two gases as a fourth field.
-template <typename T, int H, int TPB, int J, bool WALLS, bool SP>
-struct Tile1Src {
-    static constexpr int W = TPB * J + 2 * H;
-    static constexpr int NS = (W + TPB - 1) / TPB;
-    static constexpr int NF = SP ? 4 : 3;
-    T ld[NS][NF];
-    bool mir[WALLS ? NS : 1];  // mirror image beyond a reflecting wall: momentum negated when used
-};
-
-template <typename T, int H, int TPB, int J, bool WALLS, bool SP>
-__device__ __forceinline__ void tile1d_load(const T* __restrict__ Y, int64_t nx, int bc, int64_t x0,
-                                            Tile1Src<T, H, TPB, J, WALLS, SP>& src)
+// Many rows: block g folds rows [g kChunk, (g + 1) kChunk) into the first.
+__global__ void __launch_bounds__(kChunk)
+tube_chunk_kernel(double* __restrict__ partials, int64_t nb, const StepCtl* __restrict__ ctl)
 {
-    using S = Tile1Src<T, H, TPB, J, WALLS, SP>;
+    if (ctl->err_step != LLONG_MAX) return;  // the rows of a failed launch are read one by one
+    const int64_t b0 = (int64_t)blockIdx.x * kChunk, b = b0 + threadIdx.x;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    TubeOut o{0, 0, 0};
+    if (b < nb) {
+        const double* p = partials + b * kPartialStride;
 #pragma unroll
-    for (int u = 0; u < S::NS; ++u) {
-        const int i = (int)threadIdx.x + u * TPB;
-        if (i < S::W) {
-            const int64_t gx = x0 - H + i;
-            int64_t si;
-            if constexpr (WALLS) si = source_idx(gx, nx, bc, &src.mir[u]);
-            else si = bc == kBcPeriodic ? wrap_near(gx, nx) : clamp_idx(gx, nx);
-            src.ld[u][0] = Y[si];
-            src.ld[u][1] = Y[nx + si];
-            src.ld[u][2] = Y[2 * nx + si];
-            if constexpr (SP) src.ld[u][3] = Y[3 * nx + si];
-        }
+        for (int f = 0; f < 4; ++f) s[f] = p[f];
+        o = row_out(p);
     }
+    o = block_rows<kChunk / 64>(s, o);
+    if (threadIdx.x == 0) put_row(partials + b0 * kPartialStride, s, o);
 }
 
-template <typename T, int H, int TPB, int J, bool WALLS, bool SP>
-__device__ __forceinline__ TileInfo tile1d_gather(const Tile1Src<T, H, TPB, J, WALLS, SP>& src, T* __restrict__ Yn,
-                                                  int64_t nx, int64_t x0, const Consts& k,
-                                                  double (&acc)[Tile1Src<T, H, TPB, J, WALLS, SP>::NF])
+__host__ __device__ constexpr int64_t tube_tiles(int64_t nx, int J, int K) { return (nx + tube_cols(J, K) - 1) / tube_cols(J, K); }
+__host__ __device__ constexpr int64_t tube_blocks(int64_t nx, int J, int K)
 {
-    using S = Tile1Src<T, H, TPB, J, WALLS, SP>;
-    constexpr int NF = S::NF;
-    constexpr int W = S::W;
-    constexpr int NW = TPB / 64;
-    __shared__ int s_pk[W];
-    __shared__ T s_r[W], s_rho[W], s_d2[W], s_K[W];
-    __shared__ T s_chi[SP ? W : 1];
-    __shared__ int s_red[NW][8];
-
-    TileInfo ti = {INT_MAX, INT_MIN, 0, 0, INT_MAX, INT_MIN, 0, 0};
-#pragma unroll
-    for (int u = 0; u < S::NS; ++u) {
-        const int i = (int)threadIdx.x + u * TPB;
-        if (i >= W) break;
-        // (the sign of a mirror image is applied here, once its load has
-        // arrived, so that loads issued ahead of time are not waited for)
-        T mom = src.ld[u][1];
-        if constexpr (WALLS) mom = src.mir[u] ? -mom : mom;
-        Src1<T> s;
-        if constexpr (SP) s = make_src1<T, true>(src.ld[u][0], mom, src.ld[u][2], k, src.ld[u][3]);
-        else s = make_src1<T, false>(src.ld[u][0], mom, src.ld[u][2], k);
-        if constexpr (SP) s_chi[i] = s.chi;
-        s_pk[i] = pack_lane(s.f, 0, s.c1);
-        s_r[i] = s.r;
-        s_rho[i] = s.bad ? (T)0 : src.ld[u][0];
-        s_d2[i] = s.d2;
-        s_K[i] = s.K;
-        ti.fxmin = min(ti.fxmin, s.f);
-        ti.fxmax = max(ti.fxmax, s.f);
-        ti.cmin = min(ti.cmin, s.c1);
-        ti.cmax = max(ti.cmax, s.c1);
-        ti.reach = max(ti.reach, axis_reach(s.f, s.c1));
-        ti.bad |= s.bad ? 1 : 0;
-    }
-    ti = block_tile_info<NW>(ti, s_red);  // contains the barrier after staging
-    const Tile1<T> tl = {s_pk, s_r, s_rho, s_d2, s_K, s_chi, (T)k.delta0, (T)k.b0, (T)k.inv_b1};
-    const bool uniform = ti.fxmin == ti.fxmax && ti.cmin == ti.cmax && ti.reach <= H;
-    if (uniform && ti.cmin == 0)
-        gather1_uniform<T, H, TPB, J, 0, SP, NF>(tl, ti.fxmin, x0, nx, Yn, acc);
-    else if (uniform && ti.cmin == 1)
-        gather1_uniform<T, H, TPB, J, 1, SP, NF>(tl, ti.fxmin, x0, nx, Yn, acc);
-    else if (uniform && ti.cmin == 2)
-        gather1_uniform<T, H, TPB, J, 2, SP, NF>(tl, ti.fxmin, x0, nx, Yn, acc);
-    else if (uniform && ti.cmin == 3)
-        gather1_uniform<T, H, TPB, J, 3, SP, NF>(tl, ti.fxmin, x0, nx, Yn, acc);
-    else
-        gather1_general<T, H, TPB, J, SP, NF>(tl, ti, x0, nx, Yn, acc);
-    return ti;
+    return (tube_tiles(nx, J, K) + kTubeNW - 1) / kTubeNW;
 }
 
-template <typename T, int H, int TPB, int J, bool WALLS, bool SP>
+// After a failed launch of K-step tiles the block makes the `steps` steps before
+// the failing one again, tile by tile.  Returns the largest reach of the failing
+// step (every tile makes that step too: one that it fails on writes nothing, the
+// others' moments are overwritten or, where steps is 0, left in the spare set).
+template <typename T, bool SP, int J, int NW>
+__device__ int tube_again(const T* Y, T* Yn, int64_t nx, int bc, int64_t ntiles, int K, int steps, const Consts& k,
+                          TubeEdges<T> (&edges)[NW], TubeStash<T, SP, J> (&stash)[NW])
+{
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int reach = 0;
+#pragma unroll 1
+    for (int64_t tile = wid; wid < NW && tile < ntiles; tile += NW) {
+        double tot[SP ? 4 : 3] = {};
+        const int64_t X0 = tile * tube_cols(J, K);
+        const TubeOut o = tube_run<T, SP, J>(Y, Yn, nx, bc, X0, K, steps + 1, k, edges[wid], stash[wid], tot);
+        reach = max(reach, o.reach);
+        if (steps > 0) tube_run<T, SP, J>(Y, Yn, nx, bc, X0, K, steps, k, edges[wid], stash[wid], tot);
+    }
+    return reach;
+}
+
+// Behind the launches of one call, the last of them `steps` steps from step0:
+// its rows (stride as in finalize_kernel) -> totals and reach.  Where a step of
+// any of the launches failed, the steps before it are made again from that
+// launch's input (by this block: rare), so that the last good state exists: in
+// the launch's output set, or in its input set if its first step failed.
+template <typename T, bool SP, int J, int TPB>
 __global__ void __launch_bounds__(TPB)
-step1d_kernel(const T* __restrict__ Y, T* __restrict__ Yn, Grid g, Consts k,
-              StepCtl* __restrict__ ctl, double* __restrict__ partials, long long step)
+tube_finalize_kernel(const double* __restrict__ partials, int64_t nb, int64_t stride, StepCtl* __restrict__ ctl,
+                     long long step0, int steps, T* Y0, T* Y1, int64_t nx, int bc, Consts k)
 {
-    if (ctl->err_step < step) return;  // an earlier step failed: keep its input intact
-    const int64_t x0 = (int64_t)blockIdx.x * (TPB * J);
-    using S = Tile1Src<T, H, TPB, J, WALLS, SP>;
-    S src;
-    tile1d_load<T, H, TPB, J, WALLS, SP>(Y, g.nx, g.bc_x, x0, src);
-    double acc[S::NF] = {};
-    const TileInfo ti = tile1d_gather<T, H, TPB, J, WALLS, SP>(src, Yn, g.nx, x0, k, acc);
-    finish_step<TPB / 64, S::NF>(acc, ti, partials + (int64_t)blockIdx.x * kPartialStride, H);
+    constexpr int NA = kTubeNW;  // wavefronts that make steps again
+    __shared__ TubeEdges<T> s_edges[NA];
+    __shared__ TubeStash<T, SP, J> s_stash[NA];
+    if (ctl->err_code) return;  // a failure that is dealt with
+    const bool failed = ctl->err_step != LLONG_MAX;
+    const int K = failed ? ctl->fail_steps : steps, in = failed ? ctl->fail_in : 0;
+    if (failed) {
+        nb = tube_blocks(nx, J, K);
+        stride = 1;
+    }
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    TubeOut o{0, 0, 0};
+    for (int64_t b = threadIdx.x; b < nb; b += TPB) {
+        const double* p = partials + b * stride * kPartialStride;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) s[f] += p[f];
+        o = worse(o, row_out(p));
+    }
+    o = block_rows<TPB / 64>(s, o);
+    int reach = o.reach;
+    if (failed) {
+        double none[4] = {0.0, 0.0, 0.0, 0.0};
+        reach = tube_again<T, SP, J, NA>(in ? Y1 : Y0, in ? Y0 : Y1, nx, bc, tube_tiles(nx, J, K), K, o.errsub - 1, k,
+                                         s_edges, s_stash);
+        reach = block_rows<TPB / 64>(none, TubeOut{reach, 0, 0}).reach;
+    }
+    if (threadIdx.x != 0) return;
+    ctl->max_reach = reach;
+    if (failed) {
+        ctl->err_code = o.err;
+        ctl->err_buf = o.errsub > 1 ? in ^ 1 : in;
+    } else {
+        for (int f = 0; f < 4; ++f) ctl->totals[f] = s[f];
+        ctl->totals_sp = 0.0;
+        ctl->totals_step = step0 + steps - 1;
+    }
 }
 
-// Pool form: one block per tile of the tile table (1-D tiles cost about the
-// same, so the hardware's block scheduling balances them and overlaps one
-// tile's loads with other tiles' work).  A tile belongs to one slot; its word
-// says whether the slot still steps and which moment set holds its state.
-template <typename T, int TPB, int J, bool WALLS, bool SP>
-__global__ void __launch_bounds__(TPB) pool1d_kernel(PoolView v, Consts k)
+// Pool form: one wavefront per tile of the tile table.  A tile belongs to one
+// slot; its word says whether the slot still steps, how many steps it has left
+// and which moment set holds its state.
+template <typename T, bool SP, int J>
+__global__ void __launch_bounds__(kTubeTPB) __attribute__((amdgpu_waves_per_eu(kTubeWpe<T, SP, J>)))
+pool_tube_kernel(PoolView v, Consts k, int K, int steps)
 {
-    const int t = blockIdx.x;
+    __shared__ TubeEdges<T> s_edges[kTubeNW];
+    __shared__ TubeStash<T, SP, J> s_stash[kTubeNW];
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int t = blockIdx.x * kTubeNW + wid;
     if (t >= *v.ntiles) return;
     const int ts = v.tstate[t];
-    if (!(ts & kTileLive)) return;  // the same for the whole block
+    if (!(ts & kTileLive)) return;
     T* arena = (T*)v.arena;
     const PoolTile& tl = v.tiles[t];
-    const int64_t o0 = tl.off[0], o1 = tl.off[1];  // selected below, not indexed (keeps them in registers)
+    const int64_t o0 = tl.off[0], o1 = tl.off[1];
     const int64_t from = (ts & kTileSet) ? o1 : o0, to = (ts & kTileSet) ? o0 : o1;
-    const int64_t nx = tl.nx, x0 = tl.x0;
-    using S = Tile1Src<T, kHalo, TPB, J, WALLS, SP>;
-    S src;
-    tile1d_load<T, kHalo, TPB, J, WALLS, SP>(arena + from, nx, tl.bc_x, x0, src);
-    double acc[S::NF] = {};
-    const TileInfo ti = tile1d_gather<T, kHalo, TPB, J, WALLS, SP>(src, arena + to, nx, x0, k, acc);
-    finish_step<TPB / 64, S::NF>(acc, ti, v.partials + (int64_t)t * kPartialStride, kHalo);
+    double tot[SP ? 4 : 3] = {};
+    const TubeOut o = tube_run<T, SP, J>(arena + from, arena + to, tl.nx, tl.bc_x, tl.x0, K,
+                                      min(steps, ts >> kTileLeftShift), k, s_edges[wid], s_stash[wid], tot);
+    double s[4] = {tot[0], tot[1], tot[2], SP ? tot[SP ? 3 : 0] : 0.0};
+#pragma unroll
+    for (int f = 0; f < 4; ++f) s[f] = wave_sum(s[f]);
+    if ((threadIdx.x & 63) == 0) put_row(v.partials + (int64_t)t * kPartialStride, s, o);
 }
 
-// Per slot (one block each): the same fixed-order reduction as finalize_kernel
-// over the slot's tile rows.
+// Per slot of a 1-D pool (one block each): the reduction of tube_finalize_kernel
+// over the slot's tiles; commits the launch's steps.
+template <typename T, bool SP, int J>
+__global__ void __launch_bounds__(kFinTPB) pool_tube_finalize_kernel(PoolView v, Consts k, int K, int steps, int commit)
+{
+    __shared__ TubeEdges<T> s_edges[kFinTPB / 64];
+    __shared__ TubeStash<T, SP, J> s_stash[kFinTPB / 64];
+    const PoolProb& P = v.probs[blockIdx.x];
+    PoolState& S = v.state[blockIdx.x];
+    const int64_t done = S.done;
+    const int set = S.set;
+    if (!commit || !P.active || done >= P.target || S.err_step != 0) return;
+    const int n = (int)min((int64_t)steps, P.target - done);
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    TubeOut o{0, 0, 0};
+    for (int64_t b = P.t0 + threadIdx.x; b < P.t1; b += kFinTPB) {
+        const double* p = v.partials + b * kPartialStride;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) s[f] += p[f];
+        o = worse(o, row_out(p));
+    }
+    o = block_rows<kFinTPB / 64>(s, o);
+    int reach = o.reach;
+    if (o.errsub) {
+        T* arena = (T*)v.arena;
+        double none[4] = {0.0, 0.0, 0.0, 0.0};
+        reach = tube_again<T, SP, J, kFinTPB / 64>(arena + P.off[set], arena + P.off[set ^ 1], P.nx, P.bc_x, P.t1 - P.t0, K,
+                                                o.errsub - 1, k, s_edges, s_stash);
+        reach = block_rows<kFinTPB / 64>(none, TubeOut{reach, 0, 0}).reach;
+    }
+    const int64_t now = done + (o.errsub ? o.errsub - 1 : n);
+    const int nset = now > done ? set ^ 1 : set;
+    const int64_t left = P.target - now;
+    const int word = nset | (!o.errsub && left > 0 ? kTileLive | (int)min(left, (int64_t)kTileLeftMax) << kTileLeftShift : 0);
+    for (int64_t t = P.t0 + threadIdx.x; t < P.t1; t += kFinTPB) v.tstate[t] = word;
+    if (threadIdx.x != 0) return;
+    for (int f = 0; f < 4; ++f) S.totals[f] = s[f];
+    S.max_reach = reach;
+    S.totals_step = done + n;
+    S.done = now;
+    S.set = nset;
+    if (o.errsub) {
+        S.err_code = o.err;
+        S.err_step = now + 1;
+    }
+}
+
+// Per slot of a square-lattice pool (one block each): the same fixed-order
+// reduction as finalize_kernel over the slot's tile rows.
 __global__ void __launch_bounds__(kFinTPB) pool_finalize_kernel(PoolView v, int commit)
 {
     __shared__ double s_sum[kFinTPB / 64][4];
@@ -530,109 +448,136 @@ __global__ void __launch_bounds__(kFinTPB) pool_finalize_kernel(PoolView v, int 
             S.err_step = step;
         } else {
             S.done = step;
+            S.set ^= 1;
         }
-        s_word = (int)(S.done & 1) | (!e && S.done < P.target ? kTileLive : 0);
+        s_word = S.set | (!e && S.done < P.target ? kTileLive : 0);
     }
     __syncthreads();
     if (commit)
         for (int64_t t = P.t0 + tid; t < P.t1; t += kFinTPB) v.tstate[t] = s_word;
 }
 
-#ifndef LB_T1_TPB
-#define LB_T1_TPB 256
-#endif
-#ifndef LB_T1_J
-#define LB_T1_J 4
-#endif
-constexpr int k1TPB = LB_T1_TPB, k1J = LB_T1_J;
+}  // namespace
+
+namespace {
+
+// Nodes per lane and steps per launch of a tube.  Where the chip is idle a launch
+// lasts as long as a wavefront's steps, so short tubes take two nodes per lane
+// and as many steps as leave a wavefront on most SIMDs (32, 56 or 80 nodes per
+// wavefront for 8, 6 or 4 steps); beyond that five nodes per lane, whose halo is
+// the smallest share.  Two gases in FP64 take three (five would need 390
+// registers, one wavefront per SIMD).  The line between the two, us per step
+// with two nodes per lane / with more: FP64 200 000 nodes 3.8 / 5.2 (two gases
+// 6.0 / 6.3), 300 000 5.1 / 5.3 (7.1 / 6.6); FP32 300 000 4.0 / 6.7, 400 000
+// 4.7 / 6.8 (6.1 / 7.5).  Six steps of five nodes: 2^24 nodes of one gas in FP64
+// take 600 us where one step per launch took 1116 (HBM-bound); 16384 nodes 2.7 us
+// per step where a launch per step took 14.
+struct TubeShape {
+    int J, K;
+};
+constexpr int64_t kTubeShort64 = 200000, kTubeShort32 = 400000;
+TubeShape tube_shape(int64_t nx, bool species, bool fp64)
+{
+    if (nx <= 32 * 1024) return {2, 8};
+    if (nx <= 56 * 1024) return {2, 6};
+    if (nx <= (fp64 ? kTubeShort64 : kTubeShort32)) return {2, 4};
+    return species && fp64 ? TubeShape{3, 3} : TubeShape{5, 6};
+}
+template <typename T, bool SP>
+constexpr int kLongJ = tube_lanes(SP, sizeof(T) == 8);
 
 }  // namespace
 
 int64_t step_blocks_1d(const Grid& g)
 {
-    const int64_t tile = (int64_t)k1TPB * k1J;
-    return (g.nx + tile - 1) / tile;
+    // (the fewest nodes per wavefront of each: 8 steps of J = 2; 6 of J = 5, 3 of J = 3)
+    return g.nx <= kTubeShort32 ? tube_blocks(g.nx, 2, 8) : tube_blocks(g.nx, 3, 3);
 }
 
-template <typename T>
-hipError_t launch_step1d(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl,
-                         double* partials, long long step, hipStream_t stream)
-{
-    const dim3 grid((unsigned)step_blocks_1d(g));
-    const bool walls = g.bc_x == kBcReflecting;
-    if (k.species) {
-        if (walls)
-            step1d_kernel<T, kHalo, k1TPB, k1J, true, true><<<grid, k1TPB, 0, stream>>>(Y, Yn, g, k, ctl, partials, step);
-        else
-            step1d_kernel<T, kHalo, k1TPB, k1J, false, true><<<grid, k1TPB, 0, stream>>>(Y, Yn, g, k, ctl, partials, step);
-    } else if (walls) {
-        step1d_kernel<T, kHalo, k1TPB, k1J, true, false><<<grid, k1TPB, 0, stream>>>(Y, Yn, g, k, ctl, partials, step);
-    } else {
-        step1d_kernel<T, kHalo, k1TPB, k1J, false, false><<<grid, k1TPB, 0, stream>>>(Y, Yn, g, k, ctl, partials, step);
-    }
-    return hipGetLastError();
-}
+int tube_group(const Grid& g, const Consts& k, bool fp64) { return tube_shape(g.nx, k.species, fp64).K; }
 
-template <typename T, int S>
-static hipError_t pool1d_launch_shape(const PoolView& v, const Consts& k, int nblocks, bool walls,
-                                      hipStream_t stream)
+template <typename T, bool SP, int J>
+static hipError_t launch_tube_j(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
+                                long long step0, int steps, int in_buf, bool last, hipStream_t stream)
 {
-    constexpr int TPB = kPool1TPB[S], J = kPool1J[S];
-    if (k.species) {  // two gases: the instances that carry rho chi
-        if (walls) pool1d_kernel<T, TPB, J, true, true><<<nblocks, TPB, 0, stream>>>(v, k);
-        else pool1d_kernel<T, TPB, J, false, true><<<nblocks, TPB, 0, stream>>>(v, k);
-    } else if (walls) {
-        pool1d_kernel<T, TPB, J, true, false><<<nblocks, TPB, 0, stream>>>(v, k);
-    } else {
-        pool1d_kernel<T, TPB, J, false, false><<<nblocks, TPB, 0, stream>>>(v, k);
+    int64_t nb = tube_blocks(g.nx, J, steps), stride = 1;
+    tube_kernel<T, SP, J><<<(unsigned)nb, kTubeTPB, 0, stream>>>(Y, Yn, g.nx, g.bc_x, k, ctl, partials, step0, steps,
+                                                                 tube_tiles(g.nx, J, steps), in_buf);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !last) return e;
+    if (nb > 16 * kChunk) {  // many rows: fold each chunk first, on many CUs
+        const int64_t n = (nb + kChunk - 1) / kChunk;
+        tube_chunk_kernel<<<(unsigned)n, kChunk, 0, stream>>>(partials, nb, ctl);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        nb = n;
+        stride = kChunk;
     }
+    T* const set[2] = {in_buf ? Yn : const_cast<T*>(Y), in_buf ? const_cast<T*>(Y) : Yn};
+    if (nb >= kFinManyRows)
+        tube_finalize_kernel<T, SP, J, kFinMaxTPB><<<1, kFinMaxTPB, 0, stream>>>(
+            partials, nb, stride, ctl, step0, steps, set[0], set[1], g.nx, g.bc_x, k);
+    else
+        tube_finalize_kernel<T, SP, J, kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, nb, stride, ctl, step0, steps,
+                                                                         set[0], set[1], g.nx, g.bc_x, k);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_pool1d(const PoolView& v, const Consts& k, int shape, int nblocks, bool walls,
+hipError_t launch_tube(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
+                       long long step0, int steps, int in_buf, bool last, hipStream_t stream)
+{
+    const bool shrt = tube_shape(g.nx, k.species, sizeof(T) == 8).J == 2;
+    if (k.species)
+        return shrt ? launch_tube_j<T, true, 2>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, last, stream)
+                    : launch_tube_j<T, true, kLongJ<T, true>>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, last, stream);
+    return shrt ? launch_tube_j<T, false, 2>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, last, stream)
+                : launch_tube_j<T, false, kLongJ<T, false>>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, last, stream);
+}
+
+template <typename T>
+hipError_t launch_pool1d(const PoolView& v, const Consts& k, int K, int steps, int nblocks, int nslots, int commit,
                          hipStream_t stream)
 {
-    switch (shape) {
-        case 0: return pool1d_launch_shape<T, 0>(v, k, nblocks, walls, stream);
-        case 1: return pool1d_launch_shape<T, 1>(v, k, nblocks, walls, stream);
-        case 2: return pool1d_launch_shape<T, 2>(v, k, nblocks, walls, stream);
-        case 3: return pool1d_launch_shape<T, 3>(v, k, nblocks, walls, stream);
-        case 4: return pool1d_launch_shape<T, 4>(v, k, nblocks, walls, stream);
-        default: return hipErrorInvalidValue;
-    }
+    constexpr int J = kLongJ<T, false>, JS = kLongJ<T, true>;
+    if (k.species) pool_tube_kernel<T, true, JS><<<nblocks, kTubeTPB, 0, stream>>>(v, k, K, steps);
+    else pool_tube_kernel<T, false, J><<<nblocks, kTubeTPB, 0, stream>>>(v, k, K, steps);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (k.species) pool_tube_finalize_kernel<T, true, JS><<<nslots, kFinTPB, 0, stream>>>(v, k, K, steps, commit);
+    else pool_tube_finalize_kernel<T, false, J><<<nslots, kFinTPB, 0, stream>>>(v, k, K, steps, commit);
+    return hipGetLastError();
 }
 
-hipError_t launch_pool_finalize(const PoolView& v, int nslots, int commit, hipStream_t stream)
+hipError_t launch_pool2d_finalize(const PoolView& v, int nslots, int commit, hipStream_t stream)
 {
     pool_finalize_kernel<<<nslots, kFinTPB, 0, stream>>>(v, commit);
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(double* partials, int64_t nb, StepCtl* ctl, long long step,
+hipError_t launch_finalize(double* partials, int64_t nb, StepCtl* ctl, long long step, int in_buf,
                            hipStream_t stream, bool species2d, const int* nch)
 {
+    const int sp2 = species2d ? 1 : 0;
     if (nb > 16 * kChunk) {  // many rows: fold each chunk first, on many CUs
         const int64_t g = (nb + kChunk - 1) / kChunk;
         partials_chunk_kernel<<<(unsigned)g, kChunk, 0, stream>>>(partials, nb, ctl, step, nch);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        finalize_kernel<kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, g, kChunk, ctl, step, species2d ? 1 : 0, nullptr);
+        finalize_kernel<kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, g, kChunk, ctl, step, sp2, nullptr, in_buf);
         return hipGetLastError();
     }
     if (nb >= kFinManyRows)
-        finalize_kernel<kFinMaxTPB><<<1, kFinMaxTPB, 0, stream>>>(partials, nb, 1, ctl, step, species2d ? 1 : 0, nch);
+        finalize_kernel<kFinMaxTPB><<<1, kFinMaxTPB, 0, stream>>>(partials, nb, 1, ctl, step, sp2, nch, in_buf);
     else
-        finalize_kernel<kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, nb, 1, ctl, step, species2d ? 1 : 0, nch);
+        finalize_kernel<kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, nb, 1, ctl, step, sp2, nch, in_buf);
     return hipGetLastError();
 }
 
-template hipError_t launch_step1d<double>(const double*, double*, const Grid&, const Consts&,
-                                          StepCtl*, double*, long long, hipStream_t);
-template hipError_t launch_step1d<float>(const float*, float*, const Grid&, const Consts&,
-                                         StepCtl*, double*, long long, hipStream_t);
-
-template hipError_t launch_pool1d<double>(const PoolView&, const Consts&, int, int, bool, hipStream_t);
-template hipError_t launch_pool1d<float>(const PoolView&, const Consts&, int, int, bool, hipStream_t);
+template hipError_t launch_tube<double>(const double*, double*, const Grid&, const Consts&, StepCtl*, double*, long long,
+                                        int, int, bool, hipStream_t);
+template hipError_t launch_tube<float>(const float*, float*, const Grid&, const Consts&, StepCtl*, double*, long long,
+                                       int, int, bool, hipStream_t);
+template hipError_t launch_pool1d<double>(const PoolView&, const Consts&, int, int, int, int, int, hipStream_t);
+template hipError_t launch_pool1d<float>(const PoolView&, const Consts&, int, int, int, int, int, hipStream_t);
 
 }  // namespace lbsd

@@ -685,7 +685,7 @@ namespace {
 constexpr size_t kStaticCtlBytes = (sizeof(StepCtl) + 255) / 256 * 256;  // the StepCtl at the front
 // Per device: the control block and, for the 1-D and hexagonal lattices, partial
 // rows.  A grid is taken if 2 MiB less 256 bytes hold a row per 1024 nodes of a
-// tube (33 549 312 nodes) or per 64 x 4 nodes of the hexagonal lattice; a tube's
+// tube (33 549 312 nodes) or per 64 x 16 nodes of the hexagonal lattice; a tube's
 // launch writes at most a row per 720 nodes (two gases in FP64), which is what
 // the scratch is sized for.  For the square lattice a partial row and three words
 // per tile of the widest grid taken, 132672 column strips (7.16 M columns).
@@ -797,8 +797,10 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
         while (smax > 1 && kStaticCtlBytes + align256(row * smax) + words > have) --smax;
         w = march2d_words((int*)(base + kStaticCtlBytes + align256(row * smax)), rows, smax, false);
     } else {
-        rows = s->dim == 1 ? (s->g.nx + 1023) / 1024 : hex_blocks(s->g);
-        need = kStaticCtlBytes + align256((size_t)rows * kPartialStride * 8);
+        const int64_t reckoned = s->dim == 1 ? (s->g.nx + 1023) / 1024
+                                             : ((s->g.nx + 63) / 64) * ((s->g.ny + 15) / 16);
+        rows = s->hex ? hex_blocks(s->g) : 0;
+        need = kStaticCtlBytes + align256((size_t)reckoned * kPartialStride * 8);
     }
     if (need > have)
         return fail(LB_EINVAL, "grid %lld x %lld needs %zu bytes of step scratch, more than the %zu of lb_step_static",

@@ -91,8 +91,7 @@ template <typename T>
 hipError_t launch_march2d(const T* Y, T* Yn, const Grid& g, const MarchGeom& m, const Consts& k,
                           StepCtl* ctl, double* partials, const MarchWords& w, long long step, hipStream_t stream);
 
-// Hexagonal lattice (lb_hex.hip): one block per tile of 64 x 4 nodes (axial
-// i x j), hex_blocks(g) blocks and partial rows per step.
+// Hexagonal lattice (lb_hex.hip): hex_blocks(g) blocks and partial rows per step.
 template <typename T>
 hipError_t launch_hex(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
                       long long step, hipStream_t stream);

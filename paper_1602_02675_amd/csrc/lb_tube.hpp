@@ -298,14 +298,15 @@ __device__ __forceinline__ void tube_class(const TubeNodes<T, SP, J>& n, const d
 // ---- FP32 ----
 //
 // FP32 fields are summed packet by packet in the order of the packet definition
-// (corner 0, then 1; of each the rest level, +c'_1, -c'_1, +c'_2, -c'_2).  Where
-// the state is uniform every step rounds alike, so the rounding of a step's sums
-// is a drift, not noise: behind a strong shock it moves the plateau by up to 1e-4
-// and the shock by some 1e-3 node in 400 steps.  Another order has another drift:
-// with corner sums an FP32 tube differs at the front by up to 1.3e-3 from what
-// packets in this order give.  30 products and 30 sums a node: 256 tubes of 3.1 M
-// nodes in all take 17.9 us per step with them, 16.5 with corner sums, and 45
-// where every step was a launch that rebuilt its packets from LDS.
+// (corner 0, then 1; of each the rest level, +c'_1, -c'_1, +c'_2, -c'_2; of each
+// the sources by ascending displacement).  Where the state is uniform every step
+// rounds alike, so the rounding of a step's sums is a drift, not noise: behind a
+// strong shock it moves the plateau by up to 1e-4 and the shock by some 1e-3 node
+// in 400 steps.  Another order has another drift: with corner sums an FP32 tube
+// differs at the front by up to 1.3e-3 from what packets in this order give.  30
+// products and 30 sums a node: 256 tubes of 3.1 M nodes in all take 17.9 us per
+// step with them, 16.5 with corner sums, and 45 where every step was a launch that
+// rebuilt its packets from LDS.
 
 // A lane's nodes as their packets are formed: rounded to FP32 from FP64
 // primitives; key as tube_key.
@@ -323,11 +324,29 @@ __device__ __forceinline__ void node_shift(const float (&a)[J], float (&o)[J])
     else static_for<J>([&](auto j) { o[j] = a[j]; });
 }
 
-// The packets of the nodes with floor(v) = F and c'_1 = C (rho and d2 of the
-// others are 0), added up in o.
+// All sums F nodes on.
+template <int J, int NF>
+__device__ __forceinline__ void tube_shift(float (&o)[NF][J], int F)
+{
+#pragma unroll 1
+    for (int i = 0; i < F; ++i)
+        static_for<NF>([&](auto f) {
+            float s[J];
+            node_up<1>(o[f], s);
+            static_for<J>([&](auto j) { o[f][j] = s[j]; });
+        });
+#pragma unroll 1
+    for (int i = F; i < 0; ++i)
+        static_for<NF>([&](auto f) {
+            float s[J];
+            node_down<1>(o[f], s);
+            static_for<J>([&](auto j) { o[f][j] = s[j]; });
+        });
+}
+
+// Sources of one class, floor(v) = F and c'_1 = C.
 template <int C, bool SP, int J, int NF>
-__device__ __forceinline__ void tube_packets(const float (&rho)[J], const float (&d2)[J], const TubePackets<SP, J>& n,
-                                             int F, const Consts& k, float (&o)[NF][J])
+__device__ __forceinline__ void tube_packets(const TubePackets<SP, J>& n, int F, const Consts& k, float (&o)[NF][J])
 {
 #pragma clang fp contract(off)
     const float delta0 = (float)k.delta0, b0 = (float)k.b0, inv_b1 = (float)k.inv_b1;
@@ -338,8 +357,8 @@ __device__ __forceinline__ void tube_packets(const float (&rho)[J], const float 
             constexpr int c = l == 0 ? 0 : ((l & 1) ? 1 : -1) * (C + lev - 1), N = corner + c;
             float m[J], p[J], s[J];
             static_for<J>([&](auto j) {
-                const float d0 = delta0 * rho[j];
-                const float d = lev == 0 ? d0 : (lev == 2 ? d2[j] : (rho[j] - b0 * d0) * inv_b1 - d2[j]);
+                const float d0 = delta0 * n.rho[j];
+                const float d = lev == 0 ? d0 : (lev == 2 ? n.d2[j] : (n.rho[j] - b0 * d0) * inv_b1 - n.d2[j]);
                 m[j] = (corner ? n.r[j] : 1.0f - n.r[j]) * d;
             });
             node_shift<N>(m, s);
@@ -363,56 +382,165 @@ __device__ __forceinline__ void tube_packets(const float (&rho)[J], const float 
             step_apart<J>();
         });
     });
-#pragma unroll 1
-    for (int i = 0; i < F; ++i)
-        static_for<NF>([&](auto f) {
-            float s[J];
-            node_up<1>(o[f], s);
-            static_for<J>([&](auto j) { o[f][j] = s[j]; });
-        });
-#pragma unroll 1
-    for (int i = F; i < 0; ++i)
-        static_for<NF>([&](auto f) {
-            float s[J];
-            node_down<1>(o[f], s);
-            static_for<J>([&](auto j) { o[f][j] = s[j]; });
-        });
+    tube_shift(o, F);
 }
 
-// Class by class, keys ascending, the nodes of other classes with zero mass:
-// what a node gets from sources of one class does not depend on what else the
-// wavefront holds.  Returns the largest reach; beyond H, or for bad states, t is
-// not formed.
-template <bool SP, int J, int NF>
-__device__ __forceinline__ int tube_by_class(const TubePackets<SP, J>& n, bool valid, bool bad, const Consts& k,
-                                             float (&t)[NF][J])
+// Sources with floor(v) in {F, F + 1} and c'_1 in {C, C + 1}: per packet of the
+// order above, the displacements in ascending order, the nodes of others with
+// zero mass (what a node gets from sources of one class is what tube_packets
+// gives it).
+template <int C, bool SP, int J, int NF>
+__device__ __forceinline__ void tube_packets_near(const TubePackets<SP, J>& n, int F, const Consts& k, float (&o)[NF][J])
 {
-    int far = 0, next = INT_MAX;
+#pragma clang fp contract(off)
+    const float delta0 = (float)k.delta0, b0 = (float)k.b0, inv_b1 = (float)k.inv_b1;
+    float v[J], a1[J];  // v; 1 if c'_1 = C + 1
+    int sF[J], sC[J];
     static_for<J>([&](auto j) {
-        far = max(far, class_reach((n.key[j] >> 5) - 32, n.key[j] & 31));
-        next = min(next, n.key[j]);
+        const int f = (n.key[j] >> 5) - 32;
+        v[j] = (float)f + n.r[j];
+        sF[j] = f - F;
+        sC[j] = (n.key[j] & 31) - C;
+        a1[j] = (float)sC[j];
+    });
+    static_for<NF>([&](auto f) { static_for<J>([&](auto j) { o[f][j] = 0.0f; }); });
+    static_for<2>([&](auto corner) {
+        static_for<5>([&](auto l) {
+            constexpr int lev = l == 0 ? 0 : (l <= 2 ? 1 : 2), sg = l == 0 ? 0 : ((l & 1) ? 1 : -1);
+            // displacement: base + e
+            constexpr int base = corner + (sg > 0 ? C + lev - 1 : (sg < 0 ? -(C + lev) : 0));
+            float m[J], xi[J], zeta[J];
+            int e[J];
+            static_for<J>([&](auto j) {
+                const float d0 = delta0 * n.rho[j];
+                const float d = lev == 0 ? d0 : (lev == 2 ? n.d2[j] : (n.rho[j] - b0 * d0) * inv_b1 - n.d2[j]);
+                const float c = (float)sg * ((float)(C + lev - 1) + a1[j]);
+                m[j] = (corner ? n.r[j] : 1.0f - n.r[j]) * d;
+                xi[j] = sg == 0 ? v[j] : v[j] + c;
+                zeta[j] = sg == 0 ? n.K[j] : n.K[j] + c * v[j] + 0.5f * c * c;
+                e[j] = sF[j] + (sg > 0 ? sC[j] : (sg < 0 ? 1 - sC[j] : 0));
+            });
+            static_for<(sg == 0 ? 2 : 3)>([&](auto i) {
+                constexpr int N = base + i;
+                bool any = false;
+                static_for<J>([&](auto j) { any = any || e[j] == i; });
+                if (__any(any)) {
+                    float w[J], p[J], s[J];
+                    static_for<J>([&](auto j) { w[j] = e[j] == i ? m[j] : 0.0f; });
+                    node_shift<N>(w, s);
+                    static_for<J>([&](auto j) {
+                        o[0][j] += s[j];
+                        p[j] = w[j] * xi[j];
+                    });
+                    node_shift<N>(p, s);
+                    static_for<J>([&](auto j) {
+                        o[1][j] += s[j];
+                        p[j] = w[j] * zeta[j];
+                    });
+                    node_shift<N>(p, s);
+                    static_for<J>([&](auto j) { o[2][j] += s[j]; });
+                    if constexpr (SP) {
+                        static_for<J>([&](auto j) { p[j] = w[j] * n.chi[j]; });
+                        node_shift<N>(p, s);
+                        static_for<J>([&](auto j) { o[3][j] += s[j]; });
+                    }
+                }
+            });
+            step_apart<J>();
+        });
+    });
+    tube_shift(o, F);
+}
+
+// Any classes within reach, likewise.
+template <bool SP, int J, int NF>
+__device__ __forceinline__ void tube_packets_mixed(const TubePackets<SP, J>& n, int Fmin, int Fmax, int Cmin, int Cmax,
+                                                   const Consts& k, float (&o)[NF][J])
+{
+#pragma clang fp contract(off)
+    const float delta0 = (float)k.delta0, b0 = (float)k.b0, inv_b1 = (float)k.inv_b1;
+    static_for<NF>([&](auto f) { static_for<J>([&](auto j) { o[f][j] = 0.0f; }); });
+#pragma unroll 1
+    for (int i = 0; i < 10; ++i) {
+        const int corner = i >= 5, l = i - 5 * corner, lev = (l + 1) >> 1, sg = l == 0 ? 0 : ((l & 1) ? 1 : -1);
+        float q[NF][J];
+        int D[J];
+        static_for<J>([&](auto j) {
+            const int c = sg * ((n.key[j] & 31) + lev - 1), F = (n.key[j] >> 5) - 32;
+            const float cf = (float)c, v = (float)F + n.r[j], d0 = delta0 * n.rho[j];
+            const float d = lev == 0 ? d0 : (lev == 2 ? n.d2[j] : (n.rho[j] - b0 * d0) * inv_b1 - n.d2[j]);
+            const float m = (corner ? n.r[j] : 1.0f - n.r[j]) * d;
+            D[j] = F + corner + c;
+            q[0][j] = m;
+            q[1][j] = m * (v + cf);
+            q[2][j] = m * (n.K[j] + cf * v + 0.5f * cf * cf);
+            if constexpr (SP) q[3][j] = m * n.chi[j];
+        });
+        const int clo = sg == 0 ? 0 : (sg > 0 ? Cmin + lev - 1 : -(Cmax + lev - 1));
+        const int chi = sg == 0 ? 0 : (sg > 0 ? Cmax + lev - 1 : -(Cmin + lev - 1));
+        const int last = min(Fmax + corner + chi, kHalo);
+#pragma unroll 1
+        for (int dl = max(Fmin + corner + clo, -kHalo); dl <= last; ++dl) {
+            bool any = false;
+            static_for<J>([&](auto j) { any = any || D[j] == dl; });
+            if (!__any(any)) continue;
+            float p[NF][J];
+            static_for<J>([&](auto j) {
+                const bool here = D[j] == dl;
+                static_for<NF>([&](auto f) { p[f][j] = here ? q[f][j] : 0.0f; });
+            });
+            static_for<2 * kHalo + 1>([&](auto x) {
+                constexpr int N = x - kHalo;
+                if (dl == N) {
+                    static_for<NF>([&](auto f) {
+                        float s[J];
+                        node_shift<N>(p[f], s);
+                        static_for<J>([&](auto j) { o[f][j] += s[j]; });
+                    });
+                    keep_apart<N>();
+                }
+            });
+        }
+    }
+}
+
+// The packets of a wavefront's nodes.  Returns the largest reach; beyond H, or
+// for bad states, t is not formed.
+template <bool SP, int J, int NF>
+__device__ __forceinline__ int tube_all_packets(const TubePackets<SP, J>& n, bool valid, bool bad, const Consts& k,
+                                                float (&t)[NF][J])
+{
+    const int key0 = __builtin_amdgcn_readlane(n.key[0], __builtin_ctzll(__ballot(valid)));
+    bool same = true;
+    static_for<J>([&](auto j) { same = same && n.key[j] == key0; });
+    if (__all(same || !valid)) {
+        const int F = (key0 >> 5) - 32, C = key0 & 31, far = class_reach(F, C);
+        if (far > kHalo || bad) return far;  // (such a reach admits c'_1 <= 3)
+        if (C == 0) tube_packets<0, SP>(n, F, k, t);
+        if (C == 1) tube_packets<1, SP>(n, F, k, t);
+        if (C == 2) tube_packets<2, SP>(n, F, k, t);
+        if (C == 3) tube_packets<3, SP>(n, F, k, t);
+        return far;
+    }
+    int far = 0, Fmin = INT_MAX, Fmax = INT_MIN, Cmin = INT_MAX, Cmax = 0;
+    static_for<J>([&](auto j) {
+        const int F = (n.key[j] >> 5) - 32, C = n.key[j] & 31;
+        far = max(far, class_reach(F, C));
+        Fmin = min(Fmin, F);
+        Fmax = max(Fmax, F);
+        Cmin = min(Cmin, C);
+        Cmax = max(Cmax, C);
     });
     far = -wave_min_dpp(valid ? -far : 0);
     if (far > kHalo || bad) return far;
-    next = wave_min_dpp(valid ? next : INT_MAX);
-    static_for<NF>([&](auto f) { static_for<J>([&](auto j) { t[f][j] = 0.0f; }); });
-#pragma unroll 1
-    while (next != INT_MAX) {
-        float rho[J], d2[J], o[NF][J];
-        static_for<J>([&](auto j) {
-            rho[j] = n.key[j] == next ? n.rho[j] : 0.0f;
-            d2[j] = n.key[j] == next ? n.d2[j] : 0.0f;
-        });
-        const int F = (next >> 5) - 32, C = next & 31;  // C <= 3: the reach is within H
-        if (C == 0) tube_packets<0, SP>(rho, d2, n, F, k, o);
-        else if (C == 1) tube_packets<1, SP>(rho, d2, n, F, k, o);
-        else if (C == 2) tube_packets<2, SP>(rho, d2, n, F, k, o);
-        else tube_packets<3, SP>(rho, d2, n, F, k, o);
-        static_for<NF>([&](auto f) { static_for<J>([&](auto j) { t[f][j] += o[f][j]; }); });
-        int more = INT_MAX;
-        static_for<J>([&](auto j) { more = min(more, n.key[j] > next ? n.key[j] : INT_MAX); });
-        next = wave_min_dpp(valid ? more : INT_MAX);
-    }
+    Fmin = wave_min_dpp(valid ? Fmin : INT_MAX);
+    Fmax = -wave_min_dpp(valid ? -Fmax : INT_MAX);
+    Cmin = wave_min_dpp(valid ? Cmin : INT_MAX);
+    Cmax = -wave_min_dpp(valid ? -Cmax : INT_MAX);
+    const bool near = Fmax - Fmin <= 1 && Cmax - Cmin <= 1;
+    if (near && Cmin == 0) tube_packets_near<0, SP>(n, Fmin, k, t);
+    else if (near && Cmin == 1) tube_packets_near<1, SP>(n, Fmin, k, t);
+    else tube_packets_mixed<SP>(n, Fmin, Fmax, Cmin, Cmax, k, t);
     return far;
 }
 
@@ -455,7 +583,7 @@ __device__ __forceinline__ int tube_step32(const float (&y)[NF][J], float (&t)[N
         });
         if (__any(anybad && valid)) err |= kErrState;
     }
-    *reach = tube_by_class<SP>(n, valid, err != 0, k, t);
+    *reach = tube_all_packets<SP>(n, valid, err != 0, k, t);
     if (*reach > kHalo) err |= kErrReach;
     return err;
 }

@@ -112,9 +112,10 @@ hipError_t launch_init_riemann(T* Y, const Grid& g, int nf, double x_lo, double 
                                const double* left, const double* right, hipStream_t stream);
 
 // Lattice-unit state -> FP64 physical moments (divide by scale[f]; 5 values).
+// which (device memory, may be null): Y1 holds the state where *which != 0.
 template <typename T>
 hipError_t launch_export(const T* Y, double* out, int64_t nn, int nf, const double* scale,
-                         hipStream_t stream);
+                         hipStream_t stream, const T* Y1 = nullptr, const int32_t* which = nullptr);
 
 // Per-node (f_x, f_y, c'_1) with the same device function as the step.
 template <typename T>

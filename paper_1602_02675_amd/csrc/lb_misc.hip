@@ -24,9 +24,11 @@ __global__ void init_riemann_kernel(T* __restrict__ Y, int64_t nx, int64_t nn, i
 }
 
 template <typename T>
-__global__ void export_kernel(const T* __restrict__ Y, double* __restrict__ out, int64_t nn, int nf,
-                              double s0, double s1, double s2, double s3, double s4)
+__global__ void export_kernel(const T* __restrict__ Y0, const T* __restrict__ Y1, const int32_t* __restrict__ which,
+                              double* __restrict__ out, int64_t nn, int nf, double s0, double s1, double s2, double s3,
+                              double s4)
 {
+    const T* const Y = which && *which ? Y1 : Y0;
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nn) return;
     const double s[5] = {s0, s1, s2, s3, s4};
@@ -114,9 +116,9 @@ hipError_t launch_init_riemann(T* Y, const Grid& g, int nf, double x_lo, double 
 
 template <typename T>
 hipError_t launch_export(const T* Y, double* out, int64_t nn, int nf, const double* s,
-                         hipStream_t stream)
+                         hipStream_t stream, const T* Y1, const int32_t* which)
 {
-    export_kernel<T><<<blocks_for(nn, 256), 256, 0, stream>>>(Y, out, nn, nf, s[0], s[1], s[2], s[3], s[4]);
+    export_kernel<T><<<blocks_for(nn, 256), 256, 0, stream>>>(Y, Y1, which, out, nn, nf, s[0], s[1], s[2], s[3], s[4]);
     return hipGetLastError();
 }
 
@@ -153,9 +155,9 @@ template hipError_t launch_init_riemann<double>(double*, const Grid&, int, doubl
 template hipError_t launch_init_riemann<float>(float*, const Grid&, int, double, double, double,
                                                const double*, const double*, hipStream_t);
 template hipError_t launch_export<double>(const double*, double*, int64_t, int, const double*,
-                                          hipStream_t);
+                                          hipStream_t, const double*, const int32_t*);
 template hipError_t launch_export<float>(const float*, double*, int64_t, int, const double*,
-                                         hipStream_t);
+                                         hipStream_t, const float*, const int32_t*);
 template hipError_t launch_lanes<double>(const double*, const Grid&, int, const Consts&, int32_t*,
                                          int32_t*, int32_t*, hipStream_t);
 template hipError_t launch_lanes<float>(const float*, const Grid&, int, const Consts&, int32_t*,

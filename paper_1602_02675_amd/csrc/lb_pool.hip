@@ -61,6 +61,7 @@ struct lb_pool {
     int32_t max_slots = 0;
     size_t arena_bytes = 0;
     int64_t max_tiles = 0;
+    int64_t live_tiles = 0;  // most tiles the live slots can have (sum of max_tiles_of)
     // layout inside the bound buffer
     size_t off_probs = 0, off_state = 0, off_tiles = 0, off_tstate = 0, off_ntiles = 0, off_partials = 0,
            off_flags = 0, off_arena = 0, total = 0;
@@ -147,14 +148,6 @@ int64_t max_tiles_of(const lb_pool* p, int64_t nx, int64_t ny)
     const int ns = p->dim == 1 ? kPool1Shapes : kPool2Shapes;
     for (int s = 0; s < ns; ++s) m = std::max(m, tiles_of(p, nx, ny, s));
     return m;
-}
-
-int64_t live_max_tiles(const lb_pool* p)
-{
-    int64_t n = 0;
-    for (int i = 0; i < p->max_slots; ++i)
-        if (p->probs[i].active) n += max_tiles_of(p, p->probs[i].nx, p->probs[i].ny);
-    return n;
 }
 
 // Blocks (of four wavefronts) of the step launch.  Square lattice: as many as
@@ -429,7 +422,7 @@ int reserve(lb_pool* p, const lb_grid* grid, int64_t steps, int32_t* slot_out)
         if (!p->probs[(size_t)i].active) { slot = i; break; }
     if (slot < 0) return fail(LB_ENOMEM, "no free slot (%d in use)", p->max_slots);
     const int64_t nn = grid->nx * grid->ny;
-    if (live_max_tiles(p) + max_tiles_of(p, grid->nx, grid->ny) > p->max_tiles)
+    if (p->live_tiles + max_tiles_of(p, grid->nx, grid->ny) > p->max_tiles)
         return fail(LB_ENOMEM, "tile table full");
     const size_t sb = set_bytes(p, nn), bytes = 2 * sb;
     size_t off = 0;
@@ -457,6 +450,7 @@ void unreserve(lb_pool* p, int32_t slot)
 {
     PoolProb& q = p->probs[(size_t)slot];
     arena_give(p, p->info[(size_t)slot].arena_off, p->info[(size_t)slot].bytes);
+    if (q.active) p->live_tiles -= max_tiles_of(p, q.nx, q.ny);
     q = PoolProb{};
 }
 
@@ -467,7 +461,9 @@ int activate(lb_pool* p, int32_t slot)
     pool_reset_state_kernel<<<1, 64, 0, p->stream>>>((PoolState*)(p->base + p->off_state) + slot);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "reset slot state");
-    p->probs[(size_t)slot].active = 1;
+    PoolProb& q = p->probs[(size_t)slot];
+    q.active = 1;
+    p->live_tiles += max_tiles_of(p, q.nx, q.ny);
     p->gen[(size_t)slot] += 1;
     p->dirty = true;
     return LB_OK;
@@ -664,13 +660,15 @@ int lb_pool_admit_moments(lb_pool* p, const lb_grid* grid, const double* host_Y,
 
 // No wait: steps queued earlier still run the released slot with the old
 // tables; whatever reuses its memory (an admission's initial state) is
-// queued after them on the same stream.
+// queued after them on the same stream.  Rebuilding and sending the tables for
+// each release took 44 us per slot of 256 (11 K tiles).
 int lb_pool_release(lb_pool* p, int32_t slot)
 {
     int rc = check_slot(p, slot);
     if (rc != LB_OK) return rc;
     unreserve(p, slot);
-    return upload_tables(p);
+    p->dirty = true;  // (the next step sends the tables, once for all that changed)
+    return LB_OK;
 }
 
 int lb_pool_advance(lb_pool* p, int64_t n)
@@ -747,22 +745,26 @@ int lb_pool_moments(lb_pool* p, int32_t slot, double* out, int32_t on_device)
     if (!out) return fail(LB_EINVAL, "null argument");
     int rc = check_slot(p, slot);
     if (rc != LB_OK) return rc;
-    PoolState st;
-    if ((rc = read_state(p, slot, &st)) != LB_OK) return rc;
     const SlotInfo& si = p->info[(size_t)slot];
     const int64_t nn = si.grid.nx * si.grid.ny;
     double sc[5];
     field_scales(p->nf, p->dim + 1, si.lambda, sc);
-    const void* src = set_ptr(p, slot, st.set);
     hipError_t e;
     if (on_device) {
-        e = p->precision == LB_FP64 ? launch_export<double>((const double*)src, out, nn, p->nf, sc, p->stream)
-                                    : launch_export<float>((const float*)src, out, nn, p->nf, sc, p->stream);
+        // the kernel looks up the slot's set, so that the call waits once
+        const void *s0 = set_ptr(p, slot, 0), *s1 = set_ptr(p, slot, 1);
+        const int32_t* which = &view_of(p).state[slot].set;
+        e = p->precision == LB_FP64
+            ? launch_export<double>((const double*)s0, out, nn, p->nf, sc, p->stream, (const double*)s1, which)
+            : launch_export<float>((const float*)s0, out, nn, p->nf, sc, p->stream, (const float*)s1, which);
         if (e != hipSuccess) return hip_fail(e, "export kernel");
         if ((e = hipStreamSynchronize(p->stream)) != hipSuccess) return hip_fail(e, "sync");
         return LB_OK;
     }
     // host output: copy the raw set, convert with the export kernel's arithmetic
+    PoolState st;
+    if ((rc = read_state(p, slot, &st)) != LB_OK) return rc;
+    const void* src = set_ptr(p, slot, st.set);
     const size_t n = (size_t)p->nf * (size_t)nn;
     std::vector<double> d;
     std::vector<float> f;

@@ -526,7 +526,11 @@ static int create_pool(int32_t dim, double gamma, double gamma2, bool species, c
         delete p;
         return fail(LB_ENOMEM, "host allocation failed");
     }
-    p->shape = dim == 1 ? 2 : 3;  // four steps per launch / 6 tiles per block until tuned
+    // Until tuned: six steps per launch (200 tubes of 256 to 41 K nodes, a graph of
+    // ten steps, us per step with 4 / 6 / 8: FP64 21.2 / 19.8 / 20.7, FP32 15.1 /
+    // 13.8 / 14.6), with three nodes per lane four (27.6 / 28.3 / 33.5); square
+    // lattice: 6 tiles per block.
+    p->shape = dim == 1 && tube_lanes(species, precision == LB_FP64) == 3 ? 2 : 3;
     p->off_probs = 0;
     p->off_state = align256((size_t)max_slots * sizeof(PoolProb));
     p->off_tiles = p->off_state + align256((size_t)max_slots * sizeof(PoolState));

@@ -71,7 +71,8 @@ SEED = 0
 BYTES_PER_NODE = {"fp64": 64, "fp32": 32}  # read 4 moment fields + write 4 (algorithmic)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_march2d_fp64_4096.json")
 KERNEL_SOURCES = ["paper_1602_02675_amd/csrc/lb_march2d.hpp", "paper_1602_02675_amd/csrc/lb_march2d.hip",
-                  "paper_1602_02675_amd/csrc/lb_device.hpp", "paper_1602_02675_amd/csrc/lb_kernels.hpp"]
+                  "paper_1602_02675_amd/csrc/lb_wave.hpp", "paper_1602_02675_amd/csrc/lb_device.hpp",
+                  "paper_1602_02675_amd/csrc/lb_kernels.hpp"]
 
 
 def kernel_source_sha(sources=None) -> str:
@@ -481,8 +482,8 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic,
-                     "kernel": "march2d step: lean, short and full passes (march2d_lean_kernel<double>, "
-                               "march2d_kernel<double, 3>, march2d_kernel<double, 5>)",
+                     "kernel": "march2d step: lean and general passes (march2d_lean_kernel<double>, "
+                               "march2d_general_kernel<double>)",
                      "kernel_us_per_launch": round(kernel_s_per_launch * 1e6, 2),
                      "algorithmic_bytes_per_launch": BYTES_PER_NODE["fp64"] * nodes},
     }

@@ -335,8 +335,11 @@ int lb_bind(lb_solver* s, void* dev_ptr, size_t bytes, void* hip_stream)
         if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
             return hip_fail(e, "hipDeviceGetAttribute");
         const bool fp64 = s->precision == LB_FP64;
-        const int per_cu = fp64 ? march2d_blocks_per_cu<double>(false) : march2d_blocks_per_cu<float>(false);
-        const int per_cu_lean = fp64 ? march2d_blocks_per_cu<double>(true) : march2d_blocks_per_cu<float>(true);
+        const bool rest = s->k.rest_q > 0.0;
+        const int per_cu = fp64 ? march2d_blocks_per_cu<double>(false, rest, s->species)
+                                : march2d_blocks_per_cu<float>(false, rest, s->species);
+        const int per_cu_lean = fp64 ? march2d_blocks_per_cu<double>(true, rest, s->species)
+                                     : march2d_blocks_per_cu<float>(true, rest, s->species);
         s->march = march2d_geometry(s->g, cus, per_cu, per_cu_lean);
         s->nblocks = s->march.blocks();
     }
@@ -702,8 +705,8 @@ struct StaticDevice {
     char* ptr = nullptr;  // device address of `scratch` on this device
     char* ptr_march = nullptr;  // and of `scratch_march`
     int cus = 0;          // compute units
-    int per_cu[2] = {0, 0};       // resident blocks per CU of the square lattice's general pass, FP64 and FP32
-    int per_cu_lean[2] = {0, 0};  // and of its lean pass
+    int per_cu[8] = {};       // resident blocks per CU of the square lattice's general pass (see march_kind)
+    int per_cu_lean[8] = {};  // and of its lean pass
     bool ready = false;
 };
 
@@ -737,15 +740,24 @@ int static_device(StaticDevice** out)
         d.ptr_march = (char*)pm;
         if ((e = hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
             return hip_fail(e, "hipDeviceGetAttribute");
-        d.per_cu[0] = march2d_blocks_per_cu<double>(false);
-        d.per_cu[1] = march2d_blocks_per_cu<float>(false);
-        d.per_cu_lean[0] = march2d_blocks_per_cu<double>(true);
-        d.per_cu_lean[1] = march2d_blocks_per_cu<float>(true);
+        for (int i = 0; i < 8; ++i) {
+            const bool rest = i & 2, species = i & 4;
+            int* const at[2] = {&d.per_cu[i], &d.per_cu_lean[i]};
+            for (int lean = 0; lean < 2; ++lean)
+                *at[lean] = i & 1 ? march2d_blocks_per_cu<float>(lean, rest, species)
+                                  : march2d_blocks_per_cu<double>(lean, rest, species);
+        }
         d.ptr = (char*)p;
         d.ready = true;
     }
     *out = &d;
     return LB_OK;
+}
+
+// Instance of the square lattice's kernels: bit 0 FP32, 1 rest level, 2 two gases.
+int march_kind(const lb_solver* s)
+{
+    return (s->precision == LB_FP64 ? 0 : 1) | (s->k.rest_q > 0.0 ? 2 : 0) | (s->species ? 4 : 0);
 }
 
 bool is_device_ptr(const void* p)
@@ -787,8 +799,8 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
     double* partials = (double*)(base + kStaticCtlBytes);
     size_t need = 0, have = kStaticCtlBytes + kStaticRowBytes;
     if (march) {
-        const int pi = s->precision == LB_FP64 ? 0 : 1;
-        m = march2d_geometry(s->g, d->cus, d->per_cu[pi], d->per_cu_lean[pi]);
+        const int i = march_kind(s);
+        m = march2d_geometry(s->g, d->cus, d->per_cu[i], d->per_cu_lean[i]);
         rows = m.blocks();
         have = kStaticMarchBytes;
         const size_t row = (size_t)rows * kPartialStride * 8, words = march2d_word_bytes(rows);

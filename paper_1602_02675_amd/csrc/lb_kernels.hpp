@@ -66,9 +66,10 @@ struct MarchGeom {
 // general and the lean pass (march2d_blocks_per_cu).
 MarchGeom march2d_geometry(const Grid& g, int cus, int per_cu, int per_cu_lean);
 int64_t march2d_max_blocks(const Grid& g);
-// Resident blocks per CU of the general pass (lean = false) or the lean pass.
+// Resident blocks per CU of the general pass (lean = false) or the lean pass, of
+// the instance with or without a rest level and a second gas.
 template <typename T>
-int march2d_blocks_per_cu(bool lean = false);
+int march2d_blocks_per_cu(bool lean, bool rest, bool species);
 // Per-tile words of the two passes (device memory), and the row chunks the
 // general pass may cut a tile into (it then writes smax partial rows per tile).
 struct MarchWords {
@@ -213,7 +214,7 @@ template <typename T>
 hipError_t launch_pool2d(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks, hipStream_t stream);
 // Resident blocks per CU of the pool's general pass (lean = false) or lean pass.
 template <typename T>
-int pool2d_blocks_per_cu(bool lean = false);
+int pool2d_blocks_per_cu(bool lean, bool rest, bool species);
 // Per slot of a square-lattice pool: reduce its tiles' partial rows (fixed
 // order) into its state and, when commit != 0 and the step succeeded, count the
 // step.

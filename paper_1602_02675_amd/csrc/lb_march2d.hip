@@ -43,14 +43,10 @@ MarchGeom march2d_geometry(const Grid& g, int cus, int per_cu, int per_cu_lean)
 int64_t march2d_max_blocks(const Grid& g) { return x_strips(g) * ((g.ny + kMinRows - 1) / kMinRows); }
 
 template <typename T>
-int march2d_blocks_per_cu(bool lean)
+int march2d_blocks_per_cu(bool lean, bool rest, bool species)
 {
-    int nb = 0;
-    const hipError_t e = lean
-        ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, march2d_lean_kernel<T, false, false>, kMTPB, 0)
-        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, march2d_general_kernel<T, false, false>, kMTPB, 0);
-    if (e != hipSuccess) return 1;
-    return nb > 0 ? nb : 1;
+    if (species) return march2d_blocks_per_cu_species<T>(lean, rest);
+    return rest ? march_resident<T, true, false, false>(lean) : march_resident<T, false, false, false>(lean);
 }
 
 // The dual-level set runs the instances without the rest group.
@@ -63,8 +59,8 @@ hipError_t launch_march2d(const T* Y, T* Yn, const Grid& g, const MarchGeom& m, 
                           : launch_march2d_w<T, false, false>(Y, Yn, g, m, k, ctl, partials, w, step, stream);
 }
 
-template int march2d_blocks_per_cu<double>(bool);
-template int march2d_blocks_per_cu<float>(bool);
+template int march2d_blocks_per_cu<double>(bool, bool, bool);
+template int march2d_blocks_per_cu<float>(bool, bool, bool);
 template hipError_t launch_march2d<double>(const double*, double*, const Grid&, const MarchGeom&, const Consts&,
                                            StepCtl*, double*, const MarchWords&, long long, hipStream_t);
 template hipError_t launch_march2d<float>(const float*, float*, const Grid&, const MarchGeom&, const Consts&,

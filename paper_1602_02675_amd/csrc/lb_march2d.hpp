@@ -849,22 +849,20 @@ __device__ __forceinline__ bool needs_general(const int* __restrict__ flags, int
     return false;
 }
 
-// Wavefronts per SIMD the kernels are compiled for.  Lean: four in FP64, whose
-// FIFO, history and corner sums need about 110 registers (with a rest level
-// or two gases three); five in FP32.  General: two (its three rows of corner
-// sums and, for far classes, 11 destination rows).
-#ifndef LB_LEAN_WPE
-#define LB_LEAN_WPE 4
-#endif
-#ifndef LB_LEAN_WPE_EXT
-#define LB_LEAN_WPE_EXT 3
-#endif
-#ifndef LB_LEAN_WPE_F32
-#define LB_LEAN_WPE_F32 5
-#endif
-#ifndef LB_GEN_WPE
-#define LB_GEN_WPE 2
-#endif
+// Wavefronts per SIMD the kernels are compiled for: as many as leave the row loop
+// (nearly) free of spills, since a reload from scratch memory waits for the
+// moments prefetched before it.  Lean: FP64 four, whose FIFO, history and corner
+// sums need about 110 registers; two gases three; with a rest level two (4096^2
+// planar nodes 391 us per step, with three and 27 spilled registers 787; both 463,
+// with three and 126 spilled 2650).  FP32 five; two gases or a rest level four,
+// both three (226 and 288 us, with five 277 and 1157).  General: two (three rows
+// of corner sums and, for far classes, 11 destination rows), in FP64 with a rest
+// level or two gases one (2048^2 four-state nodes: rest level 409 us, with two
+// 662; two gases 383 and 576; both 487 and 1706).
+template <typename T, bool REST, bool SP>
+constexpr int kLeanWpe = sizeof(T) == 8 ? (REST ? 2 : (SP ? 3 : 4)) : (REST && SP ? 3 : (REST || SP ? 4 : 5));
+template <typename T, bool REST, bool SP>
+constexpr int kGeneralWpe = sizeof(T) == 8 && (REST || SP) ? 1 : 2;
 
 // Counters of StepCtl::next / PoolView::next: tile claims of the two passes;
 // pools: non-zero when the lean pass gave a tile up.
@@ -894,7 +892,7 @@ __device__ __forceinline__ int march_claim(int* counter)
 // general pass, that it will be: such a tile is given up at once.
 template <typename T, bool REST, bool SP>
 __global__ void __launch_bounds__(kMTPB)
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? LB_LEAN_WPE_F32 : ((REST || SP) ? LB_LEAN_WPE_EXT : LB_LEAN_WPE))))
+    __attribute__((amdgpu_waves_per_eu(kLeanWpe<T, REST, SP>)))
 march2d_lean_kernel(const T* __restrict__ Y, T* __restrict__ Yn, Grid g, Consts k, StepCtl* __restrict__ ctl,
                     double* __restrict__ partials, MarchWords w, long long step, int sy, int tiles_x, int ntiles)
 {
@@ -930,7 +928,7 @@ march2d_lean_kernel(const T* __restrict__ Y, T* __restrict__ Yn, Grid g, Consts 
 // node's value does not depend on the cut.
 constexpr int kChunkRows = 8;
 template <typename T, bool REST, bool SP>
-__global__ void __launch_bounds__(kMTPB) __attribute__((amdgpu_waves_per_eu(LB_GEN_WPE)))
+__global__ void __launch_bounds__(kMTPB) __attribute__((amdgpu_waves_per_eu(kGeneralWpe<T, REST, SP>)))
 march2d_general_kernel(const T* __restrict__ Y, T* __restrict__ Yn, Grid g, Consts k, StepCtl* __restrict__ ctl,
                        double* __restrict__ partials, MarchWords w, long long step, int sy, int tiles_x, int ntiles)
 {
@@ -970,7 +968,7 @@ march2d_general_kernel(const T* __restrict__ Y, T* __restrict__ Yn, Grid g, Cons
 // from its t0, which is how needs_general finds a tile's neighbours.
 template <typename T, bool REST, bool SP>
 __global__ void __launch_bounds__(kMTPB)
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? LB_LEAN_WPE_F32 : ((REST || SP) ? LB_LEAN_WPE_EXT : LB_LEAN_WPE))))
+    __attribute__((amdgpu_waves_per_eu(kLeanWpe<T, REST, SP>)))
 pool2d_lean_kernel(PoolView v, Consts k)
 {
     const int nt = *v.ntiles, lane = threadIdx.x & 63, nwaves = gridDim.x * kMNW;
@@ -1002,7 +1000,7 @@ pool2d_lean_kernel(PoolView v, Consts k)
 }
 
 template <typename T, bool REST, bool SP>
-__global__ void __launch_bounds__(kMTPB) __attribute__((amdgpu_waves_per_eu(LB_GEN_WPE)))
+__global__ void __launch_bounds__(kMTPB) __attribute__((amdgpu_waves_per_eu(kGeneralWpe<T, REST, SP>)))
 pool2d_general_kernel(PoolView v, Consts k)
 {
     __shared__ MarchRing ring[kMNW];
@@ -1047,6 +1045,21 @@ hipError_t launch_march2d_w(const T* Y, T* Yn, const Grid& g, const MarchGeom& m
     return hipGetLastError();
 }
 
+// Resident blocks per CU of one instance's lean or general pass.
+template <typename T, bool REST, bool SP, bool POOL>
+int march_resident(bool lean)
+{
+    int nb = 0;
+    hipError_t e;
+    if constexpr (POOL)
+        e = lean ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, pool2d_lean_kernel<T, REST, SP>, kMTPB, 0)
+                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, pool2d_general_kernel<T, REST, SP>, kMTPB, 0);
+    else
+        e = lean ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, march2d_lean_kernel<T, REST, SP>, kMTPB, 0)
+                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, march2d_general_kernel<T, REST, SP>, kMTPB, 0);
+    return e == hipSuccess && nb > 0 ? nb : 1;
+}
+
 // The two passes of one pool step.
 template <typename T, bool REST, bool SP>
 hipError_t launch_pool2d_w(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks, hipStream_t stream)
@@ -1062,6 +1075,10 @@ hipError_t launch_pool2d_w(const PoolView& v, const Consts& k, int nblocks_lean,
 
 // Two gases (lb_march2d_sp.hip, lb_pool2d_sp.hip): the instances with the
 // species field.
+template <typename T>
+int march2d_blocks_per_cu_species(bool lean, bool rest);
+template <typename T>
+int pool2d_blocks_per_cu_species(bool lean, bool rest);
 template <typename T>
 hipError_t launch_march2d_species(const T* Y, T* Yn, const Grid& g, const MarchGeom& m, const Consts& k,
                                   StepCtl* ctl, double* partials, const MarchWords& w, long long step,

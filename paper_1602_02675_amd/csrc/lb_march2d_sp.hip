@@ -8,6 +8,14 @@
 namespace lbsd {
 
 template <typename T>
+int march2d_blocks_per_cu_species(bool lean, bool rest)
+{
+    return rest ? march_resident<T, true, true, false>(lean) : march_resident<T, false, true, false>(lean);
+}
+template int march2d_blocks_per_cu_species<double>(bool, bool);
+template int march2d_blocks_per_cu_species<float>(bool, bool);
+
+template <typename T>
 hipError_t launch_march2d_species(const T* Y, T* Yn, const Grid& g, const MarchGeom& m, const Consts& k,
                                   StepCtl* ctl, double* partials, const MarchWords& w, long long step,
                                   hipStream_t stream)

@@ -157,7 +157,9 @@ int64_t max_tiles_of(const lb_pool* p, int64_t nx, int64_t ny)
 int launch_blocks(const lb_pool* p, int64_t ntiles, bool lean)
 {
     if (p->dim == 1) return (int)std::max<int64_t>(1, (ntiles + 3) / 4);
-    const int per_cu = p->precision == LB_FP64 ? pool2d_blocks_per_cu<double>(lean) : pool2d_blocks_per_cu<float>(lean);
+    const bool rest = p->k.rest_q > 0.0;
+    const int per_cu = p->precision == LB_FP64 ? pool2d_blocks_per_cu<double>(lean, rest, p->species)
+                                               : pool2d_blocks_per_cu<float>(lean, rest, p->species);
     return std::max(1, p->cus * per_cu);
 }
 

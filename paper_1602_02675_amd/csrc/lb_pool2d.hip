@@ -6,14 +6,10 @@
 namespace lbsd {
 
 template <typename T>
-int pool2d_blocks_per_cu(bool lean)
+int pool2d_blocks_per_cu(bool lean, bool rest, bool species)
 {
-    int nb = 0;
-    const hipError_t e = lean
-        ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, pool2d_lean_kernel<T, false, false>, kMTPB, 0)
-        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, pool2d_general_kernel<T, false, false>, kMTPB, 0);
-    if (e != hipSuccess) return 1;
-    return nb > 0 ? nb : 1;
+    if (species) return pool2d_blocks_per_cu_species<T>(lean, rest);
+    return rest ? march_resident<T, true, false, true>(lean) : march_resident<T, false, false, true>(lean);
 }
 
 template <typename T>
@@ -24,8 +20,8 @@ hipError_t launch_pool2d(const PoolView& v, const Consts& k, int nblocks_lean, i
                           : launch_pool2d_w<T, false, false>(v, k, nblocks_lean, nblocks, stream);
 }
 
-template int pool2d_blocks_per_cu<double>(bool);
-template int pool2d_blocks_per_cu<float>(bool);
+template int pool2d_blocks_per_cu<double>(bool, bool, bool);
+template int pool2d_blocks_per_cu<float>(bool, bool, bool);
 template hipError_t launch_pool2d<double>(const PoolView&, const Consts&, int, int, hipStream_t);
 template hipError_t launch_pool2d<float>(const PoolView&, const Consts&, int, int, hipStream_t);
 

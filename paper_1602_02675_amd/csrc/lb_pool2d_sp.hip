@@ -6,6 +6,14 @@
 namespace lbsd {
 
 template <typename T>
+int pool2d_blocks_per_cu_species(bool lean, bool rest)
+{
+    return rest ? march_resident<T, true, true, true>(lean) : march_resident<T, false, true, true>(lean);
+}
+template int pool2d_blocks_per_cu_species<double>(bool, bool);
+template int pool2d_blocks_per_cu_species<float>(bool, bool);
+
+template <typename T>
 hipError_t launch_pool2d_species(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks,
                                  hipStream_t stream)
 {

@@ -340,13 +340,6 @@ __device__ __forceinline__ int wave_max(int x)
     for (int o = 32; o > 0; o >>= 1) { int y = __shfl_xor(x, o, 64); x = y > x ? y : x; }
     return x;
 }
-__device__ __forceinline__ int wave_min(int x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { int y = __shfl_xor(x, o, 64); x = y < x ? y : x; }
-    return x;
-}
-
 __device__ __forceinline__ int64_t wrap_idx(int64_t i, int64_t n)
 {
     int64_t r = i % n;
@@ -385,18 +378,6 @@ __device__ __forceinline__ int64_t source_idx(int64_t i, int64_t n, int bc, bool
     if (bc == kBcPeriodic) return wrap_near(i, n);
     if (bc == kBcReflecting) return mirror_idx(i, n);
     return clamp_idx(i, n);
-}
-
-// Persistent blocks take tiles from a shared counter in claim order: a slow
-// tile (a transition region, a hot problem) then delays only the block that
-// holds it.  Which block computes a tile changes no result.  *s_slot is a
-// shared-memory int; every thread of the block must call this.
-__device__ __forceinline__ int claim_tile(int* counter, int* s_slot)
-{
-    __syncthreads();  // the previous claim has been read by every thread
-    if (threadIdx.x == 0) *s_slot = atomicAdd(counter, 1);
-    __syncthreads();
-    return *s_slot;
 }
 
 }  // namespace lbsd

@@ -7,7 +7,7 @@ with `--output-format csv`, and writes
   profiles/<name>.txt   the figures used, with the commands that made them
   profiles/traffic_<name>.json  HBM bytes per step, with the source hash of
                         the kernels it was measured on.
-A step may be several kernels (the square lattice's lean, short and full
+A step may be several kernels (the square lattice's lean and general
 passes): every kernel whose name contains --kernel counts, and the per-step
 figures are the sums of the per-kernel averages per dispatch.
 HBM bytes = counter KiB * 1024 / (counter KiB * 1024 per byte of a plain

@@ -13,10 +13,21 @@ namespace {
 
 int64_t x_strips(const Grid& g) { return (g.nx + kMCols - 1) / kMCols; }
 
-// Smallest strip height.  A lean tile marches 4 halo rows besides its own, so
-// low strips repeat work; but a small grid leaves most of the chip idle, and
-// its step lasts as long as one tile's march.
+// Smallest strip height.  A lean tile marches 4 halo rows besides its own (a
+// general one 10), so low strips repeat work; but a small grid leaves most of the
+// chip idle, and its step lasts as long as one tile's march.  So 2 or 4 rows where
+// that makes less than 1024 or 2048 tiles (more cost the reduction of their rows
+// what they save): us per planar step in FP64 with 8 rows / fewer, 400 x 100 26.2 /
+// 19.4 (2 rows), 800 x 200 28.9 / 24.9 (4; with 2 26.3), 1200 x 300 30.9 / 27.9 (4),
+// 500 x 500 30.0 / 29.6 (4; 2500 tiles of 4 rows and more: 28 to 31 either way);
+// four states on 200 x 200 231 / 182.
 constexpr int kMinRows = 8;
+int64_t min_rows(const Grid& g)
+{
+    for (int64_t r = 2; r < kMinRows; r *= 2)
+        if (x_strips(g) * ((g.ny + r - 1) / r) < 512 * r) return r;
+    return kMinRows;
+}
 
 }  // namespace
 
@@ -30,7 +41,7 @@ MarchGeom march2d_geometry(const Grid& g, int cus, int per_cu, int per_cu_lean)
     const int64_t resident = (int64_t)(cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1);
     const int64_t resident_lean = (int64_t)(cus > 0 ? cus : 1) * (per_cu_lean > 0 ? per_cu_lean : 1);
     const int64_t chunks = std::max<int64_t>(1, resident_lean * kMNW / xs);
-    const int64_t sy = std::max<int64_t>((g.ny + chunks - 1) / chunks, kMinRows);
+    const int64_t sy = std::max<int64_t>((g.ny + chunks - 1) / chunks, min_rows(g));
     m.sy = (int)sy;
     m.grid_x = xs;
     m.grid_y = (g.ny + sy - 1) / sy;
@@ -40,7 +51,11 @@ MarchGeom march2d_geometry(const Grid& g, int cus, int per_cu, int per_cu_lean)
     return m;
 }
 
-int64_t march2d_max_blocks(const Grid& g) { return x_strips(g) * ((g.ny + kMinRows - 1) / kMinRows); }
+int64_t march2d_max_blocks(const Grid& g)
+{
+    const int64_t r = min_rows(g);
+    return x_strips(g) * ((g.ny + r - 1) / r);
+}
 
 template <typename T>
 int march2d_blocks_per_cu(bool lean, bool rest, bool species)

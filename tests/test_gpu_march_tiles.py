@@ -108,3 +108,20 @@ def test_chunks_of_a_given_up_tile(lbsd):
     assert np.array_equal(pool.moments(slot), got)
     np.testing.assert_allclose(tot, got.reshape(4, -1).sum(axis=1), rtol=1e-12, atol=1e-8)
     pool.close()
+
+
+@pytest.mark.parametrize("kind", sorted(STATES))
+@pytest.mark.parametrize("nx,ny", [(55, 1021), (55, 1025), (109, 2725), (109, 2733)])
+def test_strip_heights(lbsd, nx, ny, kind):
+    """Either side of the lines between strips of 2, 4 and 8 rows (1024 and 2048 tiles)."""
+    Y = inputs.random_state(nx + ny, 2, nx, ny, **STATES[kind])
+    P = oracle.Problem(2, nx, ny, bc_x=BC["periodic"], bc_y=BC["transmissive"])
+    ref, st, reach = oracle.run(P, Y, 1)
+    assert st == 0 and reach <= 5
+    for prec, tol in (("fp64", TOL64), ("fp32", 2e-5)):
+        s = lbsd.Solver(2, nx, ny, precision=prec, bc_x="periodic", bc_y="transmissive")
+        s.init_moments(Y, 1.0)
+        s.step(1)
+        got = s.moments()
+        s.close()
+        assert normwise_err(got, ref, 2) <= tol, prec

@@ -443,10 +443,11 @@ __device__ __forceinline__ bool march_tile_lean(const MarchIO<T, SP ? 5 : 4>& io
         }
         if (r + 1 < nrows) io.load(Y0 - LB + r + 1, cur, &mir_y);  // arrives while this row is gathered
 
-        // stage A, class by class
+        // stage A, class by class (floor(v_x), which its conversion saturates, clamped
+        // far beyond any admissible reach)
         CSum<T> u[NS];
         int has = 0;  // speeds present in the row (bit c)
-        const int key = s.fx * 8 + min(s.c1, 7);
+        const int key = min(max(s.fx, -16), 15) * 8 + min(s.c1, 7);
         const int key0 = __builtin_amdgcn_readfirstlane(key);
         if (__all(key == key0)) {
             const int F = key0 >> 3, C = key0 & 7;

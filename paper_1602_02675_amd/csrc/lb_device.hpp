@@ -57,17 +57,18 @@ struct Src2 {   // one source node of the square lattice, as the gather uses it
     bool bad;
 };
 
-// Largest integer c with c*c <= A, for 0 <= A <= kMaxC1^2 (eq. 26: "int" of sqrt).
+// Largest integer c <= kMaxC1 with c*c <= A, for A >= 0 (eq. 26: "int" of sqrt).
 template <typename T>
 __device__ __forceinline__ int isqrt_floor(T A)
 {
 #pragma clang fp contract(off)
     // a single-precision root is within one of floor(sqrt(A)) for the clamped
-    // A <= kMaxC1^2 (relative error < 1e-7); the exact comparisons settle it
-    int c = (int)sqrtf((float)A);
+    // root (relative error < 1e-7), the exact comparisons settle it, and A beyond
+    // kMaxC1^2 leaves the whole numbers' range nowhere
+    int c = (int)fminf(sqrtf((float)A), (float)kMaxC1);
     if (c > 0 && (T)c * (T)c > A) --c;
     if ((T)(c + 1) * (T)(c + 1) <= A) ++c;
-    return c;
+    return c < kMaxC1 ? c : kMaxC1;
 }
 
 // a / b in the per-node primitives.  FAST = false (FP64 storage): the

@@ -2,8 +2,8 @@
 
 Planar states (v_y = 0, the square lattice's lean pass) whose floor(v_x) is a
 multiple of 2^29, next to one, or beyond the range of a 32-bit integer, as a
-whole field and at one node: each step must end in LB_EREACH with the state
-untouched.
+whole field and at one node, and states of huge energy (A of eq. 26 beyond
+2^62): each step must end in LB_EREACH with the state untouched.
 """
 import numpy as np
 import pytest
@@ -53,3 +53,12 @@ def field(v, e, everywhere):
 @pytest.mark.parametrize("v", SPEEDS)
 def test_fast_planar_states(lbsd, v, everywhere, prec, d0, two_gas):
     refused(lbsd, field(v, 0.0, everywhere), prec, d0, two_gas)
+
+
+@pytest.mark.parametrize("two_gas", [False, True])
+@pytest.mark.parametrize("d0", [0.0, 0.5])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("everywhere", [True, False])
+@pytest.mark.parametrize("e", [1e8, 1e22, 1e37])
+def test_hot_planar_states(lbsd, e, everywhere, prec, d0, two_gas):
+    refused(lbsd, field(0.0, e, everywhere), prec, d0, two_gas)

@@ -390,17 +390,19 @@ __device__ __forceinline__ void tube_packets(const TubePackets<SP, J>& n, int F,
 // zero mass (what a node gets from sources of one class is what tube_packets
 // gives it).
 template <int C, bool SP, int J, int NF>
-__device__ __forceinline__ void tube_packets_near(const TubePackets<SP, J>& n, int F, const Consts& k, float (&o)[NF][J])
+__device__ __forceinline__ void tube_packets_near(const TubePackets<SP, J>& n, int F, bool valid, const Consts& k,
+                                                  float (&o)[NF][J])
 {
 #pragma clang fp contract(off)
     const float delta0 = (float)k.delta0, b0 = (float)k.b0, inv_b1 = (float)k.inv_b1;
     float v[J], a1[J];  // v; 1 if c'_1 = C + 1
     int sF[J], sC[J];
     static_for<J>([&](auto j) {
-        const int f = (n.key[j] >> 5) - 32;
+        // (a lane that does not count must not ask for a displacement beyond H)
+        const int key = valid ? n.key[j] : (F + 32) << 5 | C, f = (key >> 5) - 32;
         v[j] = (float)f + n.r[j];
         sF[j] = f - F;
-        sC[j] = (n.key[j] & 31) - C;
+        sC[j] = (key & 31) - C;
         a1[j] = (float)sC[j];
     });
     static_for<NF>([&](auto f) { static_for<J>([&](auto j) { o[f][j] = 0.0f; }); });
@@ -538,8 +540,8 @@ __device__ __forceinline__ int tube_all_packets(const TubePackets<SP, J>& n, boo
     Cmin = wave_min_dpp(valid ? Cmin : INT_MAX);
     Cmax = -wave_min_dpp(valid ? -Cmax : INT_MAX);
     const bool near = Fmax - Fmin <= 1 && Cmax - Cmin <= 1;
-    if (near && Cmin == 0) tube_packets_near<0, SP>(n, Fmin, k, t);
-    else if (near && Cmin == 1) tube_packets_near<1, SP>(n, Fmin, k, t);
+    if (near && Cmin == 0) tube_packets_near<0, SP>(n, Fmin, valid, k, t);
+    else if (near && Cmin == 1) tube_packets_near<1, SP>(n, Fmin, valid, k, t);
     else tube_packets_mixed<SP>(n, Fmin, Fmax, Cmin, Cmax, k, t);
     return far;
 }
@@ -606,8 +608,10 @@ struct TubeStash {
 // A wavefront that mixes classes: for each value of floor(v), ascending, and
 // each speed, ascending, the packets of the nodes that have both (the others
 // with zero mass: a node whose sources are all of one class gets the bits of the
-// one-class form).  Returns the largest reach; beyond H, or for bad states, t is
-// not formed.
+// one-class form).  Zero mass times what a lane that does not count may hold (NaN)
+// is no zero, so nothing is moved further than H: of each floor(v) only the speeds
+// that an admissible source can have with it are taken.  Returns the largest
+// reach; beyond H, or for bad states, t is not formed.
 template <bool SP, typename T, int J, int NF>
 __device__ __forceinline__ int tube_mixed(const TubeNodes<T, SP, J>& n, bool valid, bool bad, const Consts& k,
                                           TubeStash<T, SP, J>& st, int lane, T (&t)[NF][J])
@@ -674,14 +678,15 @@ __device__ __forceinline__ int tube_mixed(const TubeNodes<T, SP, J>& n, bool val
         double d[J];
         masses();
         tube_speed<0, true, SP>(d0, r, v, m, next, o);
-        if (!STASH && cmax <= 1) {  // the usual case in one piece
+        // the usual case in one piece (two or three nodes per lane, whose halo lanes hold H + 1 nodes: next + 3 at most)
+        if (!STASH && cmax <= 1) {
             of_speed(1, d);
             tube_speed<1, false, SP>(d, r, v, m, next, o);
             of_speed(2, d);
             tube_speed<2, false, SP>(d, r, v, m, next, o);
         } else {
 #pragma unroll 1
-            for (int c = max(cmin, 1); c <= cmax + 1; ++c) {
+            for (int c = max(cmin, 1); c <= min(cmax + 1, kHalo + 1 - class_reach(next, 0)); ++c) {
                 masses();
                 of_speed(c, d);
                 if (c == 1) tube_speed<1, false, SP>(d, r, v, m, next, o);

@@ -156,7 +156,9 @@ int lb_init_moments(lb_solver* s, const double* host_Y, double lambda);
  * kernel that reduces the per-tile partial results into the interior
  * conservation totals and the largest reach.  In 1-D a kernel makes up to eight
  * steps (how the steps are split between kernels and calls does not change a
- * bit of the state), and the reduction is queued once per call.  If a step
+ * bit of the state), and the reduction is queued once per call.  Captured into a
+ * graph with an even n, the steps end in the moment set they began with, so that
+ * each replay goes on from the last one's state.  If a step
  * fails, it and every later queued step leave the state at the last good step;
  * the error is reported at the next synchronising call. */
 int lb_step(lb_solver* s, int64_t n);

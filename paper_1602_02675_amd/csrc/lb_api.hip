@@ -410,17 +410,33 @@ int lb_init_moments(lb_solver* s, const double* Y, double lambda)
     return start_state(s);
 }
 
+static bool is_capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (stream == nullptr) return false;  // (the default stream cannot be captured)
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
+}
+
 // Queue n steps: step kernels and finalize kernel each (1-D: several steps per
 // launch).  With ev != NULL, ev[2i] / ev[2i+1] are recorded right before / after
-// the i-th launch's step kernels; *launches counts them.
-static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr, int64_t* launches = nullptr)
+// the i-th launch's step kernels; *timed counts them.
+static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr, int64_t* timed = nullptr)
 {
     const bool march = s->dim == 2 && !s->hex, fp64 = s->precision == LB_FP64;
     const MarchWords words = march2d_words(flags_ptr(s), s->nblocks, kSplitMax, true);
     const int64_t group = s->dim == 1 ? tube_group(s->g, s->k, fp64) : 1;
+    // Under capture as many launches as have the parity of n: a graph of an even
+    // number of steps then ends in the set it began with, and its replays go on.
+    int64_t launches = (n + group - 1) / group;
+    if (is_capturing(s->stream)) launches += (launches ^ n) & 1;
     int64_t left = n;
-    for (int64_t i = 0; left > 0; ++i) {
-        const int in = s->cur, out = s->cur ^ 1, m = (int)std::min(left, group);
+    for (int64_t i = 0; i < launches; ++i) {
+        const int in = s->cur, out = s->cur ^ 1;
+        const int m = (int)std::min(group, left - (launches - 1 - i));
         const long long step = (long long)(s->steps_done + 1);
         const void* Y = buf_ptr(s, in);
         void* Yn = buf_ptr(s, out);
@@ -443,7 +459,7 @@ static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr, int64_
                                              s->stream);
         if (e != hipSuccess) return hip_fail(e, "step launch");
         if (ev && (e = hipEventRecord(ev[2 * i + 1], s->stream)) != hipSuccess) return hip_fail(e, "event");
-        if (launches) *launches = i + 1;
+        if (timed) *timed = i + 1;
         if (s->dim == 2) {
             e = launch_finalize(part, s->nblocks, ctl, step, in, s->stream, s->species, march ? words.nch : nullptr);
             if (e != hipSuccess) return hip_fail(e, "finalize launch");

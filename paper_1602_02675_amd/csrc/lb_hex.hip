@@ -78,22 +78,25 @@ struct HexSrc {
     int c1;
 };
 
-// Primitives as make_srchex (the same operations); tame operands take their
-// quotients from shared reciprocals, bit for bit the same.
-template <typename T, bool REST>
-__device__ __forceinline__ SrcHex<T> hex_source(T m0t, T m1t, T m2t, T m3t, const Consts& k)
+// Per-node primitives, level speeds and weights of a source (Fig. 1; eq. 15, 24-26
+// with b_1 = b_2 = 6, Consts::inv_b1 = 1/6) in FP64 whatever the storage type, and
+// the end point of v in axial coordinates, b = 2 v_y / sqrt(3), a = v_x - b / 2
+// (e_1 = (1, 0), e_2 = (1/2, sqrt(3)/2)), whose cell (f_a, f_b) + [0, 1]^2 splits
+// into the triangles below and above the diagonal r_a + r_b = 1.  REST: the set
+// with a rest group, d_0 = delta0 rho.  IEEE: any operands of a good state;
+// otherwise they are tame, and the quotients come from shared reciprocals.  Both
+// forms give the same bits: which one a wavefront takes depends on its other nodes.
+template <typename T, bool REST, bool IEEE>
+__device__ __forceinline__ SrcHex<T> hex_node(double m0, double m1, double m2, double m3, const Consts& k)
 {
 #pragma clang fp contract(off)
     constexpr bool FAST = sizeof(T) < 8;
-    if (!__all(tame(m0t, m1t, m2t, m3t) && (!REST || k.delta0 <= kTameDelta0)))
-        return make_srchex<T, REST>(m0t, m1t, m2t, m3t, k);
     SrcHex<T> s;
     s.bad = false;
-    const double m0 = m0t;
-    const Quot<FAST, false> by_rho(m0);
-    const double vx = by_rho((double)m1t), vy = by_rho((double)m2t), E = by_rho((double)m3t);
+    const Quot<FAST, IEEE> by_rho(m0);
+    const double vx = by_rho(m1), vy = by_rho(m2), E = by_rho(m3);
     const double v2 = vx * vx + vy * vy;
-    const Quot<FAST, false> by_s3(kSqrt3);
+    const Quot<FAST, IEEE> by_s3(kSqrt3);
     const double b = by_s3(2.0 * vy), a = vx - 0.5 * b;
     const double d0 = REST ? k.delta0 * m0 : 0.0, rest = m0 - k.b0 * d0;
     double e = E - 0.5 * v2;
@@ -101,10 +104,13 @@ __device__ __forceinline__ SrcHex<T> hex_source(T m0t, T m1t, T m2t, T m3t, cons
     const double Ar = k.Dg1 * e * m0;
     double A;
     if constexpr (REST) {
-        const Quot<FAST, false> by_rest(rest);
+        const Quot<FAST, IEEE> by_rest(rest);
         A = by_rest(Ar);
     } else {
         A = by_rho(Ar);
+    }
+    if constexpr (IEEE) {
+        if (!(A >= 0.0)) A = 0.0;
     }
     if (__any(A >= 9.0)) {
         if (A > (double)kMaxC1 * (double)kMaxC1) A = (double)kMaxC1 * (double)kMaxC1;
@@ -112,6 +118,7 @@ __device__ __forceinline__ SrcHex<T> hex_source(T m0t, T m1t, T m2t, T m3t, cons
     } else {
         s.c1 = (A >= 1.0 ? 1 : 0) + (A >= 4.0 ? 1 : 0);
     }
+    // floors clamped far beyond any admissible reach (the step reports those)
     const double fa = fmin(fmax(floor(a), -32.0), 31.0), fb = fmin(fmax(floor(b), -32.0), 31.0);
     s.fa = (int)fa;
     s.fb = (int)fb;
@@ -126,6 +133,16 @@ __device__ __forceinline__ SrcHex<T> hex_source(T m0t, T m1t, T m2t, T m3t, cons
     s.d1 = (T)(per - d2);
     s.d0 = (T)d0;
     s.K = (T)__builtin_fma(k.phi_coef, e, 0.5 * v2);
+    return s;
+}
+template <typename T, bool REST>
+__device__ __forceinline__ SrcHex<T> hex_source(T m0, T m1, T m2, T m3, const Consts& k)
+{
+    if (__all(tame(m0, m1, m2, m3) && (!REST || k.delta0 <= kTameDelta0)))
+        return hex_node<T, REST, false>(m0, m1, m2, m3, k);
+    const bool bad = !((double)m0 > 0.0) || !isfinite(m0) || !isfinite(m1) || !isfinite(m2) || !isfinite(m3);
+    SrcHex<T> s = hex_node<T, REST, true>(bad ? (T)1 : m0, bad ? (T)0 : m1, bad ? (T)0 : m2, bad ? (T)0 : m3, k);
+    s.bad = bad;
     return s;
 }
 

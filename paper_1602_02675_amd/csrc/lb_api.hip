@@ -241,6 +241,15 @@ static double* partials_ptr(lb_solver* s) { return (double*)(s->base + s->off_pa
 static int* flags_ptr(lb_solver* s) { return (int*)(s->base + s->off_flags); }
 static double* export_ptr(lb_solver* s) { return (double*)(s->base + s->off_export); }
 
+template <typename T>
+static hipError_t queue_lanes(const T* Y, lb_solver* s, int32_t* d)
+{
+    int32_t *const fx = d, *const fy = d + s->nn, *const c1 = d + 2 * s->nn;
+    if (s->dim == 1) return launch_lanes_tube<T>(Y, s->g, s->k, fx, fy, c1, s->stream);
+    if (s->hex) return launch_lanes_hex<T>(Y, s->g, s->k, fx, fy, c1, s->stream);
+    return launch_lanes_march<T>(Y, s->g, s->k, fx, fy, c1, s->stream);
+}
+
 extern "C" {
 
 const char* lb_last_error(void) { return g_last_error.c_str(); }
@@ -673,11 +682,8 @@ int lb_debug_lanes(lb_solver* s, int32_t* fx, int32_t* fy, int32_t* c1)
     int rc = lb_sync(s);
     if (rc != LB_OK && rc != LB_EREACH && rc != LB_ESTATE) return rc;
     int32_t* d = (int32_t*)export_ptr(s);  // 3 nn int32 fit in the nf nn FP64 staging area
-    hipError_t e = s->precision == LB_FP64
-        ? launch_lanes<double>((const double*)buf_ptr(s, s->cur), s->g, s->dim, s->k, d, d + s->nn,
-                               d + 2 * s->nn, s->stream)
-        : launch_lanes<float>((const float*)buf_ptr(s, s->cur), s->g, s->dim, s->k, d, d + s->nn,
-                              d + 2 * s->nn, s->stream);
+    hipError_t e = s->precision == LB_FP64 ? queue_lanes((const double*)buf_ptr(s, s->cur), s, d)
+                                           : queue_lanes((const float*)buf_ptr(s, s->cur), s, d);
     if (e != hipSuccess) return hip_fail(e, "lanes kernel");
     int32_t* outs[3] = {fx, fy, c1};
     for (int i = 0; i < 3; ++i) {

@@ -71,6 +71,21 @@ struct HexLds {
     int ir[kHNW][2];
 };
 
+template <typename T>
+struct SrcHex {   // one source node of the hexagonal lattice
+    int fa, fb;   // floor of the axial coordinates (a, b) of v = a e_1 + b e_2
+    int c1;
+    int tri;      // triangle of the cell that holds the end point of v: 0 has
+                  // the vertex (0, 0), 1 the vertex (1, 1) (both (1,0), (0,1))
+    T ra, rb;     // (a, b) - (f_a, f_b)
+    T vx, vy;     // Cartesian v (lattice units)
+    T K;          // |v|^2 / 2 + phi
+    T d0, d1, d2; // level weights (d0 = 0 without the rest group)
+    bool bad;
+};
+
+constexpr double kSqrt3 = 1.7320508075688772;  // sqrt(3), correctly rounded
+
 // A source as its thread holds it.
 template <typename T>
 struct HexSrc {
@@ -428,6 +443,20 @@ hex_step_kernel(const T* __restrict__ Y, T* __restrict__ Yn, Grid g, Consts k, S
     }
 }
 
+// The integer decisions of every node, as the step takes them (bad states: 0).
+template <typename T, bool REST>
+__global__ void __launch_bounds__(256)
+hex_lanes_kernel(const T* __restrict__ Y, int64_t nn, Consts k, int32_t* __restrict__ fa, int32_t* __restrict__ fb,
+                 int32_t* __restrict__ c1)
+{
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x, p = min(q, nn - 1);
+    const SrcHex<T> s = hex_source<T, REST>(Y[p], Y[nn + p], Y[2 * nn + p], Y[3 * nn + p], k);
+    if (q >= nn) return;
+    fa[q] = s.bad ? 0 : s.fa;
+    fb[q] = s.bad ? 0 : s.fb;
+    c1[q] = s.bad ? 0 : s.c1;
+}
+
 }  // namespace
 
 int64_t hex_blocks(const Grid& g)
@@ -449,6 +478,21 @@ hipError_t launch_hex(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_lanes_hex(const T* Y, const Grid& g, const Consts& k, int32_t* fa, int32_t* fb, int32_t* c1,
+                            hipStream_t stream)
+{
+    const int64_t nn = g.nx * g.ny;
+    const unsigned nb = (unsigned)((nn + 255) / 256);
+    if (k.b0 > 0.0) hex_lanes_kernel<T, true><<<nb, 256, 0, stream>>>(Y, nn, k, fa, fb, c1);
+    else hex_lanes_kernel<T, false><<<nb, 256, 0, stream>>>(Y, nn, k, fa, fb, c1);
+    return hipGetLastError();
+}
+
+template hipError_t launch_lanes_hex<double>(const double*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
+                                             hipStream_t);
+template hipError_t launch_lanes_hex<float>(const float*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
+                                            hipStream_t);
 template hipError_t launch_hex<double>(const double*, double*, const Grid&, const Consts&, StepCtl*, double*,
                                        long long, hipStream_t);
 template hipError_t launch_hex<float>(const float*, float*, const Grid&, const Consts&, StepCtl*, double*,

@@ -118,10 +118,17 @@ template <typename T>
 hipError_t launch_export(const T* Y, double* out, int64_t nn, int nf, const double* scale,
                          hipStream_t stream, const T* Y1 = nullptr, const int32_t* which = nullptr);
 
-// Per-node (f_x, f_y, c'_1) with the same device function as the step.
+// Per-node (f_x, f_y, c'_1) by the node functions of each lattice's step (a
+// wavefront of 64 consecutive nodes takes the tame or the general form for all).
 template <typename T>
-hipError_t launch_lanes(const T* Y, const Grid& g, int dim, const Consts& k, int32_t* fx,
-                        int32_t* fy, int32_t* c1, hipStream_t stream);
+hipError_t launch_lanes_tube(const T* Y, const Grid& g, const Consts& k, int32_t* fx, int32_t* fy, int32_t* c1,
+                             hipStream_t stream);
+template <typename T>
+hipError_t launch_lanes_march(const T* Y, const Grid& g, const Consts& k, int32_t* fx, int32_t* fy, int32_t* c1,
+                              hipStream_t stream);
+template <typename T>
+hipError_t launch_lanes_hex(const T* Y, const Grid& g, const Consts& k, int32_t* fa, int32_t* fb, int32_t* c1,
+                            hipStream_t stream);
 
 hipError_t launch_reset_ctl(StepCtl* ctl, hipStream_t stream);
 

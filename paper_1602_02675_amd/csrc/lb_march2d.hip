@@ -74,11 +74,24 @@ hipError_t launch_march2d(const T* Y, T* Yn, const Grid& g, const MarchGeom& m, 
                           : launch_march2d_w<T, false, false>(Y, Yn, g, m, k, ctl, partials, w, step, stream);
 }
 
+template <typename T>
+hipError_t launch_lanes_march(const T* Y, const Grid& g, const Consts& k, int32_t* fx, int32_t* fy, int32_t* c1,
+                              hipStream_t stream)
+{
+    if (k.species) return launch_lanes_species<T>(Y, g, k, fx, fy, c1, stream);
+    return k.rest_q > 0.0 ? launch_lanes_w<T, true, false>(Y, g, k, fx, fy, c1, stream)
+                          : launch_lanes_w<T, false, false>(Y, g, k, fx, fy, c1, stream);
+}
+
 template int march2d_blocks_per_cu<double>(bool, bool, bool);
 template int march2d_blocks_per_cu<float>(bool, bool, bool);
 template hipError_t launch_march2d<double>(const double*, double*, const Grid&, const MarchGeom&, const Consts&,
                                            StepCtl*, double*, const MarchWords&, long long, hipStream_t);
 template hipError_t launch_march2d<float>(const float*, float*, const Grid&, const MarchGeom&, const Consts&,
                                           StepCtl*, double*, const MarchWords&, long long, hipStream_t);
+template hipError_t launch_lanes_march<double>(const double*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
+                                               hipStream_t);
+template hipError_t launch_lanes_march<float>(const float*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
+                                              hipStream_t);
 
 }  // namespace lbsd

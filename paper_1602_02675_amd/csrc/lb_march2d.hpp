@@ -72,8 +72,12 @@ struct MNode {
 };
 
 // Per-node primitives (eq. 15, 24-26, 28-29) in FP64 whatever the storage
-// type, as make_src2.  IEEE: any operands, bad states included (they get zero
-// mass); otherwise the operands are tame.  NOVY: v_y is +-0.
+// type: in FP32 storage the energy bookkeeping (E -> e, A, the d_1 / d_2 split
+// near a switch of c'_1) is where FP32 arithmetic would lose the most, and FP64
+// costs the same VALU issue rate on this chip.  IEEE: any operands, bad states
+// included (they get zero mass); otherwise the operands are tame.  NOVY: v_y is
+// +-0.  SP: the node's gas is the mixture of the two by mass fraction (c_v
+// weighted, one gas constant).
 template <typename T, bool REST, bool SP, bool NOVY, bool IEEE>
 __device__ __forceinline__ MNode<T, REST, SP> march_node(double m0, double m1, double m2, double m3, double m4,
                                                          const Consts& kc, bool bad)
@@ -1033,6 +1037,41 @@ pool2d_general_kernel(PoolView v, Consts k)
     }
 }
 
+// The integer decisions of every node, as the passes take them: rows of 64 nodes
+// without v_y by the lean pass's form, others by the general one (bad states: 0).
+template <typename T, bool REST, bool SP>
+__global__ void __launch_bounds__(kMTPB)
+march_lanes_kernel(const T* __restrict__ Y, int64_t nn, Consts k, int32_t* __restrict__ fx, int32_t* __restrict__ fy,
+                   int32_t* __restrict__ c1)
+{
+    const int64_t q = (int64_t)blockIdx.x * kMTPB + threadIdx.x, p = min(q, nn - 1);
+    const T r0 = Y[p], r1 = Y[nn + p], r2 = Y[2 * nn + p], r3 = Y[3 * nn + p], r4 = SP ? Y[(SP ? 4 : 0) * nn + p] : (T)0;
+    bool ok = tame(r0, r1, r2, r3) && (!REST || k.delta0 <= kTameDelta0);
+    bool bad = !((double)r0 > 0.0) || !isfinite(r0) || !isfinite(r1) || !isfinite(r2) || !isfinite(r3);
+    if constexpr (SP) {
+        ok = ok && zero_or_normal(r4);
+        bad = bad || !isfinite(r4);
+    }
+    const bool tame_all = __all(ok), lean = __all(r2 == (T)0 && !bad);
+    MNode<T, REST, SP> s;
+    if (lean) s = tame_all ? march_node<T, REST, SP, true, false>(r0, r1, 0.0, r3, r4, k, false)
+                           : march_node<T, REST, SP, true, true>(r0, r1, 0.0, r3, r4, k, false);
+    else s = tame_all ? march_node<T, REST, SP, false, false>(r0, r1, r2, r3, r4, k, false)
+                      : march_node<T, REST, SP, false, true>(r0, r1, r2, r3, r4, k, bad);
+    if (q >= nn) return;
+    fx[q] = bad ? 0 : s.fx;
+    fy[q] = bad ? 0 : s.fy;
+    c1[q] = bad ? 0 : s.c1;
+}
+template <typename T, bool REST, bool SP>
+hipError_t launch_lanes_w(const T* Y, const Grid& g, const Consts& k, int32_t* fx, int32_t* fy, int32_t* c1,
+                          hipStream_t stream)
+{
+    const int64_t nn = g.nx * g.ny;
+    march_lanes_kernel<T, REST, SP><<<(unsigned)((nn + kMTPB - 1) / kMTPB), kMTPB, 0, stream>>>(Y, nn, k, fx, fy, c1);
+    return hipGetLastError();
+}
+
 // The two passes of one step.
 template <typename T, bool REST, bool SP>
 hipError_t launch_march2d_w(const T* Y, T* Yn, const Grid& g, const MarchGeom& m, const Consts& k,
@@ -1086,6 +1125,9 @@ template <typename T>
 hipError_t launch_march2d_species(const T* Y, T* Yn, const Grid& g, const MarchGeom& m, const Consts& k,
                                   StepCtl* ctl, double* partials, const MarchWords& w, long long step,
                                   hipStream_t stream);
+template <typename T>
+hipError_t launch_lanes_species(const T* Y, const Grid& g, const Consts& k, int32_t* fx, int32_t* fy, int32_t* c1,
+                                hipStream_t stream);
 template <typename T>
 hipError_t launch_pool2d_species(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks,
                                  hipStream_t stream);

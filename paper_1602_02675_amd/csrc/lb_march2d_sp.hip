@@ -24,6 +24,18 @@ hipError_t launch_march2d_species(const T* Y, T* Yn, const Grid& g, const MarchG
                           : launch_march2d_w<T, false, true>(Y, Yn, g, m, k, ctl, partials, w, step, stream);
 }
 
+template <typename T>
+hipError_t launch_lanes_species(const T* Y, const Grid& g, const Consts& k, int32_t* fx, int32_t* fy, int32_t* c1,
+                                hipStream_t stream)
+{
+    return k.rest_q > 0.0 ? launch_lanes_w<T, true, true>(Y, g, k, fx, fy, c1, stream)
+                          : launch_lanes_w<T, false, true>(Y, g, k, fx, fy, c1, stream);
+}
+
+template hipError_t launch_lanes_species<double>(const double*, const Grid&, const Consts&, int32_t*, int32_t*,
+                                                 int32_t*, hipStream_t);
+template hipError_t launch_lanes_species<float>(const float*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
+                                                hipStream_t);
 template hipError_t launch_march2d_species<double>(const double*, double*, const Grid&, const MarchGeom&,
                                                    const Consts&, StepCtl*, double*, const MarchWords&, long long,
                                                    hipStream_t);

@@ -1,5 +1,5 @@
-// Small kernels around the step: Riemann initial state, moment export,
-// per-node lane dump and control-block reset.
+// Small kernels around the step: Riemann initial state, moment export and
+// control-block reset.
 #include <climits>
 
 #include "lb_kernels.hpp"
@@ -33,42 +33,6 @@ __global__ void export_kernel(const T* __restrict__ Y0, const T* __restrict__ Y1
     if (q >= nn) return;
     const double s[5] = {s0, s1, s2, s3, s4};
     for (int f = 0; f < nf; ++f) out[(int64_t)f * nn + q] = (double)Y[(int64_t)f * nn + q] / s[f];
-}
-
-template <typename T>
-__global__ void lanes_kernel(const T* __restrict__ Y, int64_t nn, int dim, Consts k,
-                             int32_t* __restrict__ fx, int32_t* __restrict__ fy,
-                             int32_t* __restrict__ c1)
-{
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nn) return;
-    if (dim == 1) {
-        // the same device function the step uses (one gas, or the mixture of two)
-        const Src1<T> s = k.species ? make_src1<T, true>(Y[q], Y[nn + q], Y[2 * nn + q], k, Y[3 * nn + q])
-                                    : make_src1<T, false>(Y[q], Y[nn + q], Y[2 * nn + q], k);
-        fx[q] = s.f;
-        fy[q] = 0;
-        c1[q] = s.c1;
-    } else if (k.hex) {
-        // hexagonal lattice: the floors of the axial coordinates of v
-        const T m0 = Y[q], m1 = Y[nn + q], m2 = Y[2 * nn + q], m3 = Y[3 * nn + q];
-        const SrcHex<T> s = k.b0 > 0.0 ? make_srchex<T, true>(m0, m1, m2, m3, k)
-                                       : make_srchex<T, false>(m0, m1, m2, m3, k);
-        fx[q] = s.fa;
-        fy[q] = s.fb;
-        c1[q] = s.c1;
-    } else {
-        // the same device function the step uses (with or without the rest group)
-        const T m0 = Y[q], m1 = Y[nn + q], m2 = Y[2 * nn + q], m3 = Y[3 * nn + q];
-        const bool rest = k.rest_q > 0.0;
-        const Src2<T> s = k.species ? (rest ? make_src2<T, true, true>(m0, m1, m2, m3, k, Y[4 * nn + q])
-                                            : make_src2<T, false, true>(m0, m1, m2, m3, k, Y[4 * nn + q]))
-                                    : (rest ? make_src2<T, true>(m0, m1, m2, m3, k)
-                                            : make_src2<T, false>(m0, m1, m2, m3, k));
-        fx[q] = s.fx;
-        fy[q] = s.fy;
-        c1[q] = s.c1;
-    }
 }
 
 __global__ void reset_ctl_kernel(StepCtl* ctl)
@@ -122,15 +86,6 @@ hipError_t launch_export(const T* Y, double* out, int64_t nn, int nf, const doub
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_lanes(const T* Y, const Grid& g, int dim, const Consts& k, int32_t* fx,
-                        int32_t* fy, int32_t* c1, hipStream_t stream)
-{
-    const int64_t nn = g.nx * g.ny;
-    lanes_kernel<T><<<blocks_for(nn, 256), 256, 0, stream>>>(Y, nn, dim, k, fx, fy, c1);
-    return hipGetLastError();
-}
-
 hipError_t launch_reset_ctl(StepCtl* ctl, hipStream_t stream)
 {
     reset_ctl_kernel<<<1, 64, 0, stream>>>(ctl);
@@ -158,9 +113,4 @@ template hipError_t launch_export<double>(const double*, double*, int64_t, int, 
                                           hipStream_t, const double*, const int32_t*);
 template hipError_t launch_export<float>(const float*, double*, int64_t, int, const double*,
                                          hipStream_t, const float*, const int32_t*);
-template hipError_t launch_lanes<double>(const double*, const Grid&, int, const Consts&, int32_t*,
-                                         int32_t*, int32_t*, hipStream_t);
-template hipError_t launch_lanes<float>(const float*, const Grid&, int, const Consts&, int32_t*,
-                                        int32_t*, int32_t*, hipStream_t);
-
 }  // namespace lbsd

@@ -322,6 +322,23 @@ tube_finalize_kernel(const double* __restrict__ partials, int64_t nb, int64_t st
     }
 }
 
+// floor(v) and c'_1 of every node (a spare lane repeats the last node).
+template <typename T, bool SP>
+__global__ void __launch_bounds__(kTubeTPB)
+tube_lanes_kernel(const T* __restrict__ Y, int64_t nx, Consts k, int32_t* __restrict__ fx, int32_t* __restrict__ fy,
+                  int32_t* __restrict__ c1)
+{
+    const int64_t q = (int64_t)blockIdx.x * kTubeTPB + threadIdx.x, x = min(q, nx - 1);
+    T y[SP ? 4 : 3][1];
+    static_for<(SP ? 4 : 3)>([&](auto f) { y[f][0] = Y[f * nx + x]; });
+    int f, c;
+    tube_decisions<T, SP>(y, k, &f, &c);
+    if (q >= nx) return;
+    fx[q] = f;
+    fy[q] = 0;
+    c1[q] = c;
+}
+
 // Pool form: one wavefront per tile of the tile table.  A tile belongs to one
 // slot; its word says whether the slot still steps, how many steps it has left
 // and which moment set holds its state.
@@ -535,6 +552,16 @@ hipError_t launch_tube(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCt
 }
 
 template <typename T>
+hipError_t launch_lanes_tube(const T* Y, const Grid& g, const Consts& k, int32_t* fx, int32_t* fy, int32_t* c1,
+                             hipStream_t stream)
+{
+    const unsigned nb = (unsigned)((g.nx + kTubeTPB - 1) / kTubeTPB);
+    if (k.species) tube_lanes_kernel<T, true><<<nb, kTubeTPB, 0, stream>>>(Y, g.nx, k, fx, fy, c1);
+    else tube_lanes_kernel<T, false><<<nb, kTubeTPB, 0, stream>>>(Y, g.nx, k, fx, fy, c1);
+    return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_pool1d(const PoolView& v, const Consts& k, int K, int steps, int nblocks, int nslots, int commit,
                          hipStream_t stream)
 {
@@ -577,6 +604,10 @@ template hipError_t launch_tube<double>(const double*, double*, const Grid&, con
                                         int, int, bool, hipStream_t);
 template hipError_t launch_tube<float>(const float*, float*, const Grid&, const Consts&, StepCtl*, double*, long long,
                                        int, int, bool, hipStream_t);
+template hipError_t launch_lanes_tube<double>(const double*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
+                                              hipStream_t);
+template hipError_t launch_lanes_tube<float>(const float*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
+                                             hipStream_t);
 template hipError_t launch_pool1d<double>(const PoolView&, const Consts&, int, int, int, int, int, hipStream_t);
 template hipError_t launch_pool1d<float>(const PoolView&, const Consts&, int, int, int, int, int, hipStream_t);
 

@@ -58,9 +58,9 @@ struct TubeNodes {
     T chi[SP ? J : 1];
 };
 
-// Per-node primitives (eq. 15, 26) in FP64 whatever the storage type, as
-// make_src1.  IEEE: any operands, bad states included; otherwise the operands
-// are tame.  A = e D (gamma - 1) / (1 - delta0) takes one product instead of the
+// Per-node primitives (eq. 15, 26) in FP64 whatever the storage type, as on the
+// square lattice (march_node).  IEEE: any operands, bad states included; otherwise
+// the operands are tame.  A = e D (gamma - 1) / (1 - delta0) takes one product instead of the
 // quotient by rho - d_0; the two differ by rounding alone, so they agree on c'_1
 // except next to a switch, where (FP64, whose c'_1 matches the plain definition
 // bit for bit) a node takes the quotient after all.
@@ -107,13 +107,16 @@ __device__ __forceinline__ void tube_node(TubeNodes<T, SP, J>& n, int j, T r0, d
     n.K[j] = (T)__builtin_fma(phi, e, 0.5 * v2);
 }
 
-// Class of a node: floor(v) + 32 (clamped far beyond any admissible reach) and c'_1.
+// c'_1 (eq. 26): exact comparisons for the usual values, the integer root elsewhere.
+__device__ __forceinline__ int tube_c1(double A)
+{
+    if (__any(A >= 9.0)) return isqrt_floor<double>(A);
+    return (A >= 1.0 ? 1 : 0) + (A >= 4.0 ? 1 : 0);
+}
+// Class of a node: floor(v) + 32 and c'_1, clamped far beyond any admissible reach.
 __device__ __forceinline__ int tube_key(double v, double A)
 {
-    int c1;
-    if (__any(A >= 9.0)) c1 = min(isqrt_floor<double>(fmin(A, 1e6)), 31);
-    else c1 = (A >= 1.0 ? 1 : 0) + (A >= 4.0 ? 1 : 0);
-    return (min(max((int)floor(v), -32), 31) + 32) << 5 | c1;
+    return (min(max((int)floor(v), -32), 31) + 32) << 5 | min(tube_c1(A), 31);
 }
 
 // Whether all of a lane's nodes are tame (see tame()).
@@ -135,6 +138,15 @@ __device__ __forceinline__ bool tube_tame(const T (&y)[NF][J])
     }
     if constexpr (SP) static_for<J>([&](auto j) { ok = ok && zero_or_normal(y[NF - 1][j]); });
     return ok;
+}
+
+// rho <= 0 or a non-finite moment.
+template <bool SP, typename T, int J, int NF>
+__device__ __forceinline__ bool tube_bad(const T (&y)[NF][J], int j)
+{
+    bool bad = !((double)y[0][j] > 0.0) || !isfinite(y[0][j]) || !isfinite(y[1][j]) || !isfinite(y[2][j]);
+    if constexpr (SP) bad = bad || !isfinite(y[NF - 1][j]);
+    return bad;
 }
 
 // Shifts of a wavefront's 64 J values by N nodes up (node x gets node x - N's
@@ -261,7 +273,7 @@ __device__ __forceinline__ void tube_speed(const double (&d)[J], const double (&
 }
 
 // The packets of a wavefront of one class (F, C).  r = v - F and g = A - C^2 of the
-// nodes; the level weights (eq. 24-25 rewritten, as make_src1) are formed here,
+// nodes; the level weights (eq. 24-25 rewritten, see level_w) are formed here,
 // where c'_1 is a constant.
 template <int C, bool SP, typename T, int J, int NF>
 __device__ __forceinline__ void tube_class(const TubeNodes<T, SP, J>& n, const double (&r)[J], const double (&g)[J],
@@ -293,6 +305,26 @@ __device__ __forceinline__ void tube_class(const TubeNodes<T, SP, J>& n, const d
     }
     static_for<J>([&](auto j) { d[j] = level(2, j); });
     tube_speed<C + 1, false, SP>(d, r, v, n, F, t);
+}
+
+// The integer decisions of one node of each lane, as the step takes them (bad
+// states: 0).
+template <typename T, bool SP>
+__device__ __forceinline__ void tube_decisions(const T (&y)[SP ? 4 : 3][1], const Consts& k, int* f, int* c1)
+{
+    constexpr int NF = SP ? 4 : 3;
+    const TubeConsts tc = tube_consts(k, SP);
+    TubeNodes<T, SP, 1> n;
+    bool bad = false;
+    if (__all(tube_tame<SP>(y) && k.delta0 <= kTameDelta0)) {
+        tube_node<false>(n, 0, y[0][0], y[1][0], y[2][0], y[NF - 1][0], k, tc, false);
+    } else {
+        bad = tube_bad<SP>(y, 0);
+        tube_node<true>(n, 0, y[0][0], y[1][0], y[2][0], y[NF - 1][0], k, tc, bad);
+    }
+    const int c = tube_c1(n.A[0]);
+    *f = bad ? 0 : (int)floor(n.v[0]);
+    *c1 = bad ? 0 : c;
 }
 
 // ---- FP32 ----
@@ -576,8 +608,7 @@ __device__ __forceinline__ int tube_step32(const float (&y)[NF][J], float (&t)[N
         });
     } else {
         static_for<J>([&](auto j) {
-            bool bad = !((double)y[0][j] > 0.0) || !isfinite(y[0][j]) || !isfinite(y[1][j]) || !isfinite(y[2][j]);
-            if constexpr (SP) bad = bad || !isfinite(y[NF - 1][j]);
+            const bool bad = tube_bad<SP>(y, j);
             anybad = anybad || bad;
             TubeNodes<float, SP, 1> q;
             tube_node<true>(q, 0, y[0][j], y[1][j], y[2][j], y[NF - 1][j], k, tc, bad);
@@ -738,8 +769,7 @@ __device__ __forceinline__ int tube_step(const T (&y)[NF][J], T (&t)[NF][J], con
         } else {
             bool anybad = false;
             static_for<J>([&](auto j) {
-                bool bad = !((double)y[0][j] > 0.0) || !isfinite(y[0][j]) || !isfinite(y[1][j]) || !isfinite(y[2][j]);
-                if constexpr (SP) bad = bad || !isfinite(y[NF - 1][j]);
+                const bool bad = tube_bad<SP>(y, j);
                 anybad = anybad || bad;
                 tube_node<true>(n, j, y[0][j], y[1][j], y[2][j], y[NF - 1][j], k, tc, bad);
             });

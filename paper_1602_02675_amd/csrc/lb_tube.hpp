@@ -94,7 +94,8 @@ __device__ __forceinline__ void tube_node(TubeNodes<T, SP, J>& n, int j, T r0, d
     if (e < 0.0) e = 0.0;
     double A = e * cA;
     if constexpr (!FAST) {
-        const bool near = fabs(A - 1.0) < tc.near || fabs(A - 4.0) < 4.0 * tc.near || A > 8.0;
+        bool near = fabs(A - 1.0) < tc.near || fabs(A - 4.0) < 4.0 * tc.near || A > 8.0;
+        if constexpr (IEEE) near = near || m0 < 1e-290;  // (rho - d_0 is short of bits there)
         if (__any(near)) A = near ? Dg1 * e * m0 / (m0 - kc.b0 * (kc.delta0 * m0)) : A;
     }
     if constexpr (IEEE) {

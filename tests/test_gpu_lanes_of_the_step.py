@@ -5,8 +5,9 @@
   for the state, on every lattice, in FP64 and FP32; in FP64 both are the
   oracle's.
 * Random states on switches, with a node here and there whose momentum is tiny
-  (1e-170), so that its wavefront takes the general form of the quotients:
-  floors and c'_1 bit-exact against the oracle.
+  (1e-170), so that its wavefront takes the general form of the quotients, and
+  states of densities around the smallest numbers: floors and c'_1 bit-exact
+  against the oracle.
 """
 import numpy as np
 import pytest
@@ -106,5 +107,22 @@ def test_both_forms_bit_exact(lbsd, name, planar, two_gas):
         s = solver(lbsd, name, d0, nx, ny, gamma, "fp64", g2)
         s.init_moments(Y, 1.0)
         for got, ref in zip(s.lanes(), oracle.lanes(P, Y)):
+            assert np.array_equal(np.asarray(got).reshape(-1), np.asarray(ref).reshape(-1))
+        s.close()
+
+
+@pytest.mark.parametrize("name", sorted(LATTICES))
+def test_tiny_densities_bit_exact(lbsd, name):
+    dim, _, d0s = LATTICES[name]
+    nx, ny, gamma = (4000, 1, 1.4) if dim == 1 else (250, 16, 1.4)
+    r = np.random.default_rng(9)
+    for d0 in d0s:
+        shp = (ny, nx)
+        rho = 10.0 ** r.uniform(-322.0, -300.0, shp)
+        e = r.uniform(0.0, 12.0, shp) * (1.0 - d0) / (dim * (gamma - 1.0))
+        Y = np.stack([rho, *[rho * r.uniform(-1.9, 1.9, shp) for _ in range(dim)], rho * (e + 1.0)])
+        s = solver(lbsd, name, d0, nx, ny, gamma, "fp64")
+        s.init_moments(Y, 1.0)
+        for got, ref in zip(s.lanes(), oracle.lanes(problem(name, d0, nx, ny, gamma), Y)):
             assert np.array_equal(np.asarray(got).reshape(-1), np.asarray(ref).reshape(-1))
         s.close()

@@ -344,7 +344,7 @@ tube_lanes_kernel(const T* __restrict__ Y, int64_t nx, Consts k, int32_t* __rest
 // and which moment set holds its state.
 template <typename T, bool SP, int J>
 __global__ void __launch_bounds__(kTubeTPB) __attribute__((amdgpu_waves_per_eu(kTubeWpe<T, SP, J>)))
-pool_tube_kernel(PoolView v, Consts k, int K, int steps)
+pool_tube_kernel(PoolView v, Consts k, int K, int steps, int commit)
 {
     __shared__ TubeEdges<T> s_edges[kTubeNW];
     __shared__ TubeStash<T, SP, J> s_stash[kTubeNW];
@@ -358,8 +358,10 @@ pool_tube_kernel(PoolView v, Consts k, int K, int steps)
     const int64_t o0 = tl.off[0], o1 = tl.off[1];
     const int64_t from = (ts & kTileSet) ? o1 : o0, to = (ts & kTileSet) ? o0 : o1;
     double tot[SP ? 4 : 3] = {};
-    const TubeOut o = tube_run<T, SP, J>(arena + from, arena + to, tl.nx, tl.bc_x, tl.x0, K,
-                                      min(steps, ts >> kTileLeftShift), k, s_edges[wid], s_stash[wid], tot);
+    // (a trial launch, whose steps do not count, makes all of them)
+    const int n = commit ? min(steps, ts >> kTileLeftShift) : steps;
+    const TubeOut o = tube_run<T, SP, J>(arena + from, arena + to, tl.nx, tl.bc_x, tl.x0, K, n, k, s_edges[wid],
+                                      s_stash[wid], tot);
     double s[4] = {tot[0], tot[1], tot[2], SP ? tot[SP ? 3 : 0] : 0.0};
 #pragma unroll
     for (int f = 0; f < 4; ++f) s[f] = wave_sum(s[f]);
@@ -566,8 +568,8 @@ hipError_t launch_pool1d(const PoolView& v, const Consts& k, int K, int steps, i
                          hipStream_t stream)
 {
     constexpr int J = kLongJ<T, false>, JS = kLongJ<T, true>;
-    if (k.species) pool_tube_kernel<T, true, JS><<<nblocks, kTubeTPB, 0, stream>>>(v, k, K, steps);
-    else pool_tube_kernel<T, false, J><<<nblocks, kTubeTPB, 0, stream>>>(v, k, K, steps);
+    if (k.species) pool_tube_kernel<T, true, JS><<<nblocks, kTubeTPB, 0, stream>>>(v, k, K, steps, commit);
+    else pool_tube_kernel<T, false, J><<<nblocks, kTubeTPB, 0, stream>>>(v, k, K, steps, commit);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (k.species) pool_tube_finalize_kernel<T, true, JS><<<nslots, kFinTPB, 0, stream>>>(v, k, K, steps, commit);

@@ -454,10 +454,8 @@ static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr, int64_
         hipError_t e;
         if (ev && (e = hipEventRecord(ev[2 * i], s->stream)) != hipSuccess) return hip_fail(e, "event");
         if (s->dim == 1)
-            e = fp64 ? launch_tube<double>((const double*)Y, (double*)Yn, s->g, s->k, ctl, part, step, m, in, m == left,
-                                           s->stream)
-                     : launch_tube<float>((const float*)Y, (float*)Yn, s->g, s->k, ctl, part, step, m, in, m == left,
-                                          s->stream);
+            e = fp64 ? launch_tube<double>((const double*)Y, (double*)Yn, s->g, s->k, ctl, part, step, m, in, s->stream)
+                     : launch_tube<float>((const float*)Y, (float*)Yn, s->g, s->k, ctl, part, step, m, in, s->stream);
         else if (s->hex)
             e = fp64 ? launch_hex<double>((const double*)Y, (double*)Yn, s->g, s->k, ctl, part, step, s->stream)
                      : launch_hex<float>((const float*)Y, (float*)Yn, s->g, s->k, ctl, part, step, s->stream);
@@ -471,8 +469,12 @@ static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr, int64_
         if (timed) *timed = i + 1;
         if (s->dim == 2) {
             e = launch_finalize(part, s->nblocks, ctl, step, in, s->stream, s->species, march ? words.nch : nullptr);
-            if (e != hipSuccess) return hip_fail(e, "finalize launch");
+        } else if (m == left) {
+            void *const y0 = buf_ptr(s, 0), *const y1 = buf_ptr(s, 1);
+            e = fp64 ? launch_tube_finalize<double>((double*)y0, (double*)y1, s->g, s->k, ctl, part, step, m, s->stream)
+                     : launch_tube_finalize<float>((float*)y0, (float*)y1, s->g, s->k, ctl, part, step, m, s->stream);
         }
+        if (e != hipSuccess) return hip_fail(e, "finalize launch");
         s->cur = out;
         s->steps_done += m;
         left -= m;
@@ -847,8 +849,8 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
     if (e != hipSuccess) return hip_fail(e, "reset");
     if (s->dim == 1) {
         e = s->precision == LB_FP64
-            ? launch_tube<double>((const double*)Y_in, (double*)Y_out, s->g, s->k, ctl, partials, 1, 1, 0, true, st)
-            : launch_tube<float>((const float*)Y_in, (float*)Y_out, s->g, s->k, ctl, partials, 1, 1, 0, true, st);
+            ? launch_tube<double>((const double*)Y_in, (double*)Y_out, s->g, s->k, ctl, partials, 1, 1, 0, st)
+            : launch_tube<float>((const float*)Y_in, (float*)Y_out, s->g, s->k, ctl, partials, 1, 1, 0, st);
     } else if (s->hex) {
         e = s->precision == LB_FP64
             ? launch_hex<double>((const double*)Y_in, (double*)Y_out, s->g, s->k, ctl, partials, 1, st)
@@ -859,8 +861,13 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
             : launch_march2d<float>((const float*)Y_in, (float*)Y_out, s->g, m, s->k, ctl, partials, w, 1, st);
     }
     if (e != hipSuccess) return hip_fail(e, "step launch");
-    if (s->dim == 2 && (e = launch_finalize(partials, rows, ctl, 1, 0, st, s->species, w.nch)) != hipSuccess)
-        return hip_fail(e, "finalize launch");
+    if (s->dim == 2)
+        e = launch_finalize(partials, rows, ctl, 1, 0, st, s->species, w.nch);
+    else  // (one step: its input is the last good state, and is only read)
+        e = s->precision == LB_FP64
+            ? launch_tube_finalize<double>((double*)Y_in, (double*)Y_out, s->g, s->k, ctl, partials, 1, 1, st)
+            : launch_tube_finalize<float>((float*)Y_in, (float*)Y_out, s->g, s->k, ctl, partials, 1, 1, st);
+    if (e != hipSuccess) return hip_fail(e, "finalize launch");
     if (status_dev && (e = launch_status(ctl, status_dev, st)) != hipSuccess) return hip_fail(e, "status launch");
     return LB_OK;
 }

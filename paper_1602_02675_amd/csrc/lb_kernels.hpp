@@ -40,13 +40,17 @@ struct Grid {
 };
 
 // 1-D: `steps` <= tube_group steps in one launch, step0 the first, from the
-// moment set Y (set in_buf) to Yn (SoA [nf][nx] of T).  The last launch of a call
-// also queues the reduction of its partial rows (step_blocks_1d of them at most)
-// and, if a step of any of the call's launches failed, the return to the last
-// good state, in the set that ctl then names.
+// moment set Y (set in_buf) to Yn (SoA [nf][nx] of T).
 template <typename T>
 hipError_t launch_tube(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
-                       long long step0, int steps, int in_buf, bool last, hipStream_t stream);
+                       long long step0, int steps, int in_buf, hipStream_t stream);
+// Behind the launches of a call, the last of them `steps` steps from step0, on the
+// moment sets Y0 and Y1: the reduction of its partial rows (step_blocks_1d of them
+// at most) and, if a step of any of the launches failed, the return to the last
+// good state, in the set that ctl then names.
+template <typename T>
+hipError_t launch_tube_finalize(T* Y0, T* Y1, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
+                                long long step0, int steps, hipStream_t stream);
 int tube_group(const Grid& g, const Consts& k, bool fp64);
 int64_t step_blocks_1d(const Grid& g);
 

@@ -517,40 +517,57 @@ int tube_group(const Grid& g, const Consts& k, bool fp64) { return tube_shape(g.
 
 template <typename T, bool SP, int J>
 static hipError_t launch_tube_j(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
-                                long long step0, int steps, int in_buf, bool last, hipStream_t stream)
+                                long long step0, int steps, int in_buf, hipStream_t stream)
+{
+    tube_kernel<T, SP, J><<<(unsigned)tube_blocks(g.nx, J, steps), kTubeTPB, 0, stream>>>(
+        Y, Yn, g.nx, g.bc_x, k, ctl, partials, step0, steps, tube_tiles(g.nx, J, steps), in_buf);
+    return hipGetLastError();
+}
+
+template <typename T, bool SP, int J>
+static hipError_t launch_tube_finalize_j(T* Y0, T* Y1, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
+                                         long long step0, int steps, hipStream_t stream)
 {
     int64_t nb = tube_blocks(g.nx, J, steps), stride = 1;
-    tube_kernel<T, SP, J><<<(unsigned)nb, kTubeTPB, 0, stream>>>(Y, Yn, g.nx, g.bc_x, k, ctl, partials, step0, steps,
-                                                                 tube_tiles(g.nx, J, steps), in_buf);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !last) return e;
     if (nb > 16 * kChunk) {  // many rows: fold each chunk first, on many CUs
         const int64_t n = (nb + kChunk - 1) / kChunk;
         tube_chunk_kernel<<<(unsigned)n, kChunk, 0, stream>>>(partials, nb, ctl);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
         nb = n;
         stride = kChunk;
     }
-    T* const set[2] = {in_buf ? Yn : const_cast<T*>(Y), in_buf ? const_cast<T*>(Y) : Yn};
     if (nb >= kFinManyRows)
-        tube_finalize_kernel<T, SP, J, kFinMaxTPB><<<1, kFinMaxTPB, 0, stream>>>(
-            partials, nb, stride, ctl, step0, steps, set[0], set[1], g.nx, g.bc_x, k);
+        tube_finalize_kernel<T, SP, J, kFinMaxTPB><<<1, kFinMaxTPB, 0, stream>>>(partials, nb, stride, ctl, step0,
+                                                                               steps, Y0, Y1, g.nx, g.bc_x, k);
     else
-        tube_finalize_kernel<T, SP, J, kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, nb, stride, ctl, step0, steps,
-                                                                         set[0], set[1], g.nx, g.bc_x, k);
+        tube_finalize_kernel<T, SP, J, kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, nb, stride, ctl, step0, steps, Y0,
+                                                                         Y1, g.nx, g.bc_x, k);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_tube(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
-                       long long step0, int steps, int in_buf, bool last, hipStream_t stream)
+                       long long step0, int steps, int in_buf, hipStream_t stream)
 {
     const bool shrt = tube_shape(g.nx, k.species, sizeof(T) == 8).J == 2;
     if (k.species)
-        return shrt ? launch_tube_j<T, true, 2>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, last, stream)
-                    : launch_tube_j<T, true, kLongJ<T, true>>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, last, stream);
-    return shrt ? launch_tube_j<T, false, 2>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, last, stream)
-                : launch_tube_j<T, false, kLongJ<T, false>>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, last, stream);
+        return shrt ? launch_tube_j<T, true, 2>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, stream)
+                    : launch_tube_j<T, true, kLongJ<T, true>>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, stream);
+    return shrt ? launch_tube_j<T, false, 2>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, stream)
+                : launch_tube_j<T, false, kLongJ<T, false>>(Y, Yn, g, k, ctl, partials, step0, steps, in_buf, stream);
+}
+
+template <typename T>
+hipError_t launch_tube_finalize(T* Y0, T* Y1, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
+                                long long step0, int steps, hipStream_t stream)
+{
+    const bool shrt = tube_shape(g.nx, k.species, sizeof(T) == 8).J == 2;
+    if (k.species)
+        return shrt ? launch_tube_finalize_j<T, true, 2>(Y0, Y1, g, k, ctl, partials, step0, steps, stream)
+                    : launch_tube_finalize_j<T, true, kLongJ<T, true>>(Y0, Y1, g, k, ctl, partials, step0, steps, stream);
+    return shrt ? launch_tube_finalize_j<T, false, 2>(Y0, Y1, g, k, ctl, partials, step0, steps, stream)
+                : launch_tube_finalize_j<T, false, kLongJ<T, false>>(Y0, Y1, g, k, ctl, partials, step0, steps, stream);
 }
 
 template <typename T>
@@ -603,9 +620,13 @@ hipError_t launch_finalize(double* partials, int64_t nb, StepCtl* ctl, long long
 }
 
 template hipError_t launch_tube<double>(const double*, double*, const Grid&, const Consts&, StepCtl*, double*, long long,
-                                        int, int, bool, hipStream_t);
+                                        int, int, hipStream_t);
 template hipError_t launch_tube<float>(const float*, float*, const Grid&, const Consts&, StepCtl*, double*, long long,
-                                       int, int, bool, hipStream_t);
+                                       int, int, hipStream_t);
+template hipError_t launch_tube_finalize<double>(double*, double*, const Grid&, const Consts&, StepCtl*, double*,
+                                                 long long, int, hipStream_t);
+template hipError_t launch_tube_finalize<float>(float*, float*, const Grid&, const Consts&, StepCtl*, double*,
+                                                long long, int, hipStream_t);
 template hipError_t launch_lanes_tube<double>(const double*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
                                               hipStream_t);
 template hipError_t launch_lanes_tube<float>(const float*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,

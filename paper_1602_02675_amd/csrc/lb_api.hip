@@ -231,6 +231,7 @@ struct lb_solver {
     int cur;               // buffer holding the state after `steps_done` steps
     int64_t steps_done;    // steps queued since init (optimistic until synced)
     int pending_err;       // error already known on the host
+    bool restored;         // 1-D: the last good state before it has been made again
     hipEvent_t ev0, ev1;
     bool events;
 };
@@ -378,6 +379,7 @@ static int start_state(lb_solver* s)
     s->cur = 0;
     s->steps_done = 0;
     s->pending_err = 0;
+    s->restored = false;
     s->initialized = true;
     hipError_t e = launch_reset_ctl(ctl_ptr(s), s->stream);
     // square lattice: the passes' per-tile words start clear
@@ -470,9 +472,7 @@ static int queue_steps(lb_solver* s, int64_t n, hipEvent_t* ev = nullptr, int64_
         if (s->dim == 2) {
             e = launch_finalize(part, s->nblocks, ctl, step, in, s->stream, s->species, march ? words.nch : nullptr);
         } else if (m == left) {
-            void *const y0 = buf_ptr(s, 0), *const y1 = buf_ptr(s, 1);
-            e = fp64 ? launch_tube_finalize<double>((double*)y0, (double*)y1, s->g, s->k, ctl, part, step, m, s->stream)
-                     : launch_tube_finalize<float>((float*)y0, (float*)y1, s->g, s->k, ctl, part, step, m, s->stream);
+            e = launch_tube_finalize(s->g, s->k, fp64, ctl, part, step, m, s->stream);
         }
         if (e != hipSuccess) return hip_fail(e, "finalize launch");
         s->cur = out;
@@ -490,17 +490,42 @@ int lb_step(lb_solver* s, int64_t n)
     return queue_steps(s, n);
 }
 
+// The control block once the queued work is done.  1-D: if a step failed, first
+// the good steps of its launch again and the step's reach (ctl->max_reach).
+static int read_ctl(lb_solver* s, StepCtl* c)
+{
+    hipError_t e = hipStreamSynchronize(s->stream);
+    if (e != hipSuccess) return hip_fail(e, "sync");
+    if ((e = hipMemcpy(c, ctl_ptr(s), sizeof *c, hipMemcpyDeviceToHost)) != hipSuccess)
+        return hip_fail(e, "read control block");
+    if (s->dim != 1 || !c->err_code || s->restored) return LB_OK;
+    const int good = (int)(c->err_step - c->fail_step0), in = c->fail_in;
+    const void* Y = buf_ptr(s, in);
+    void* Yn = buf_ptr(s, in ^ 1);
+    e = s->precision == LB_FP64 ? launch_tube_again<double>((const double*)Y, (double*)Yn, s->g, s->k, ctl_ptr(s),
+                                                            c->fail_steps, good, s->stream)
+                                : launch_tube_again<float>((const float*)Y, (float*)Yn, s->g, s->k, ctl_ptr(s),
+                                                           c->fail_steps, good, s->stream);
+    if (e != hipSuccess) return hip_fail(e, "step launch");
+    if ((e = hipStreamSynchronize(s->stream)) != hipSuccess) return hip_fail(e, "sync");
+    if ((e = hipMemcpy(c, ctl_ptr(s), sizeof *c, hipMemcpyDeviceToHost)) != hipSuccess)
+        return hip_fail(e, "read control block");
+    s->restored = true;
+    return LB_OK;
+}
+
 // Wait, then roll the host view back to the last good step if one failed.
 int lb_sync(lb_solver* s)
 {
     if (!s || !s->bound) return fail(LB_EINVAL, "solver not bound");
-    hipError_t e = hipStreamSynchronize(s->stream);
-    if (e != hipSuccess) return hip_fail(e, "sync");
-    if (s->pending_err) return fail(s->pending_err, "an earlier step failed; re-initialise");
-    if (!s->initialized) return LB_OK;
+    if (s->pending_err || !s->initialized) {
+        const hipError_t e = hipStreamSynchronize(s->stream);
+        if (e != hipSuccess) return hip_fail(e, "sync");
+        return s->pending_err ? fail(s->pending_err, "an earlier step failed; re-initialise") : LB_OK;
+    }
     StepCtl c;
-    if ((e = hipMemcpy(&c, ctl_ptr(s), sizeof c, hipMemcpyDeviceToHost)) != hipSuccess)
-        return hip_fail(e, "read control block");
+    const int rc = read_ctl(s, &c);
+    if (rc != LB_OK) return rc;
     if (c.err_code) {
         // step err_step (1-based since init) failed; its input, the state
         // after err_step - 1 steps, sits in buffer err_buf
@@ -671,10 +696,8 @@ int64_t lb_steps_done(const lb_solver* s) { return s ? s->steps_done : 0; }
 int32_t lb_max_reach(lb_solver* s)
 {
     if (!s || !s->bound) return -1;
-    if (hipStreamSynchronize(s->stream) != hipSuccess) return -1;
     StepCtl c;
-    if (hipMemcpy(&c, ctl_ptr(s), sizeof c, hipMemcpyDeviceToHost) != hipSuccess) return -1;
-    return c.max_reach;
+    return read_ctl(s, &c) == LB_OK ? c.max_reach : -1;
 }
 
 int lb_debug_lanes(lb_solver* s, int32_t* fx, int32_t* fy, int32_t* c1)
@@ -863,10 +886,8 @@ int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream
     if (e != hipSuccess) return hip_fail(e, "step launch");
     if (s->dim == 2)
         e = launch_finalize(partials, rows, ctl, 1, 0, st, s->species, w.nch);
-    else  // (one step: its input is the last good state, and is only read)
-        e = s->precision == LB_FP64
-            ? launch_tube_finalize<double>((double*)Y_in, (double*)Y_out, s->g, s->k, ctl, partials, 1, 1, st)
-            : launch_tube_finalize<float>((float*)Y_in, (float*)Y_out, s->g, s->k, ctl, partials, 1, 1, st);
+    else
+        e = launch_tube_finalize(s->g, s->k, s->precision == LB_FP64, ctl, partials, 1, 1, st);
     if (e != hipSuccess) return hip_fail(e, "finalize launch");
     if (status_dev && (e = launch_status(ctl, status_dev, st)) != hipSuccess) return hip_fail(e, "status launch");
     return LB_OK;

@@ -26,7 +26,7 @@ struct StepCtl {
     int err_buf;            // moment set (0 or 1) that holds the last good state after a failed step
     double totals_sp;       // square lattice with two gases: interior sum of rho chi
     long long fail_step0;   // 1-D: the launch a step of which failed: its first step,
-    int fail_steps, fail_in;  // its steps and the set it read
+    int fail_steps, fail_in;  // its steps and the set it read (which it leaves intact)
     int given_up[kGivenUp * kGivenUpStride];  // square lattice: see kGivenUp (cleared by finalize)
 };
 
@@ -44,13 +44,17 @@ struct Grid {
 template <typename T>
 hipError_t launch_tube(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
                        long long step0, int steps, int in_buf, hipStream_t stream);
-// Behind the launches of a call, the last of them `steps` steps from step0, on the
-// moment sets Y0 and Y1: the reduction of its partial rows (step_blocks_1d of them
-// at most) and, if a step of any of the launches failed, the return to the last
-// good state, in the set that ctl then names.
-template <typename T>
-hipError_t launch_tube_finalize(T* Y0, T* Y1, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
+// Behind the launches of a call, the last of them `steps` steps from step0: the
+// reduction of its partial rows (step_blocks_1d of them at most) and, if a step of
+// any of the launches failed, its error and the set that ctl then names, which
+// holds the last good state once launch_tube_again has made it.
+hipError_t launch_tube_finalize(const Grid& g, const Consts& k, bool fp64, StepCtl* ctl, double* partials,
                                 long long step0, int steps, hipStream_t stream);
+// The `steps` good steps of a failed launch of K again, from its input Y to Yn, and
+// the failing step's largest reach over all nodes.
+template <typename T>
+hipError_t launch_tube_again(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, int K, int steps,
+                             hipStream_t stream);
 int tube_group(const Grid& g, const Consts& k, bool fp64);
 int64_t step_blocks_1d(const Grid& g);
 
@@ -178,8 +182,9 @@ struct PoolTile {        // one tile, with a copy of its slot's grid so a block 
 
 // Per-tile word kept by the per-slot reduction: bit 0 = the set holding the
 // slot's current moments, bit 1 = the slot still steps; 1-D: from bit 8 the
-// steps it has left (at most kTileLeftMax).
-constexpr int kTileSet = 1, kTileLive = 2, kTileLeftShift = 8, kTileLeftMax = 1 << 20;
+// steps it has left (at most kTileLeftMax), or, with bit 2, the good steps of a
+// failed launch that are to be made again.
+constexpr int kTileSet = 1, kTileLive = 2, kTileAgain = 4, kTileLeftShift = 8, kTileLeftMax = 1 << 20;
 
 struct PoolView {
     const PoolProb* probs;
@@ -219,6 +224,9 @@ constexpr int kPool2Cols = kMarchCols;  // destination columns per square-lattic
 template <typename T>
 hipError_t launch_pool1d(const PoolView& v, const Consts& k, int halo, int steps, int nblocks, int nslots, int commit,
                          hipStream_t stream);
+// Behind a call's launches: the good steps of those that failed, made again.
+template <typename T>
+hipError_t launch_pool1d_again(const PoolView& v, const Consts& k, int halo, int nblocks, hipStream_t stream);
 // Square lattice, one step of every live tile: the lean pass, then the general
 // pass over what it left (resident wavefronts take the tiles).
 template <typename T>

@@ -360,7 +360,14 @@ int queue_steps(lb_pool* p, int64_t n)
             if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
         }
     }
-    return queue_plain(p, left);
+    const int rc = queue_plain(p, left);
+    if (rc != LB_OK || p->dim != 1 || std::min<int64_t>(n, group_steps(p)) < 2) return rc;
+    // slots that failed in the midst of a launch get their last good state back
+    const PoolView v = view_of(p);
+    const int K = kPool1Steps[p->shape];
+    const hipError_t e = p->precision == LB_FP64 ? launch_pool1d_again<double>(v, p->k, K, p->nblocks, p->stream)
+                                                 : launch_pool1d_again<float>(v, p->k, K, p->nblocks, p->stream);
+    return e == hipSuccess ? LB_OK : hip_fail(e, "pool step launch");
 }
 
 int read_state(lb_pool* p, int32_t slot, PoolState* st)

@@ -253,45 +253,19 @@ __host__ __device__ constexpr int64_t tube_blocks(int64_t nx, int J, int K)
     return (tube_tiles(nx, J, K) + kTubeNW - 1) / kTubeNW;
 }
 
-// After a failed launch of K-step tiles the block makes the `steps` steps before
-// the failing one again, tile by tile.  Returns the largest reach of the failing
-// step (every tile makes that step too: one that it fails on writes nothing, the
-// others' moments are overwritten or, where steps is 0, left in the spare set).
-template <typename T, bool SP, int J, int NW>
-__device__ int tube_again(const T* Y, T* Yn, int64_t nx, int bc, int64_t ntiles, int K, int steps, const Consts& k,
-                          TubeEdges<T> (&edges)[NW], TubeStash<T, SP, J> (&stash)[NW])
-{
-    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    int reach = 0;
-#pragma unroll 1
-    for (int64_t tile = wid; wid < NW && tile < ntiles; tile += NW) {
-        double tot[SP ? 4 : 3] = {};
-        const int64_t X0 = tile * tube_cols(J, K);
-        const TubeOut o = tube_run<T, SP, J>(Y, Yn, nx, bc, X0, K, steps + 1, k, edges[wid], stash[wid], tot);
-        reach = max(reach, o.reach);
-        if (steps > 0) tube_run<T, SP, J>(Y, Yn, nx, bc, X0, K, steps, k, edges[wid], stash[wid], tot);
-    }
-    return reach;
-}
-
-// Behind the launches of one call, the last of them `steps` steps from step0:
-// its rows (stride as in finalize_kernel) -> totals and reach.  Where a step of
-// any of the launches failed, the steps before it are made again from that
-// launch's input (by this block: rare), so that the last good state exists: in
-// the launch's output set, or in its input set if its first step failed.
-template <typename T, bool SP, int J, int TPB>
+// Behind the launches of one call, the last of them `steps` steps from step0, of J
+// nodes per lane: its rows (stride as in finalize_kernel) -> totals and reach.
+// Where a step of any of the launches failed, its error: the first of its rows'.
+template <int TPB>
 __global__ void __launch_bounds__(TPB)
 tube_finalize_kernel(const double* __restrict__ partials, int64_t nb, int64_t stride, StepCtl* __restrict__ ctl,
-                     long long step0, int steps, T* Y0, T* Y1, int64_t nx, int bc, Consts k)
+                     long long step0, int steps, int64_t nx, int J)
 {
-    constexpr int NA = kTubeNW;  // wavefronts that make steps again
-    __shared__ TubeEdges<T> s_edges[NA];
-    __shared__ TubeStash<T, SP, J> s_stash[NA];
     if (ctl->err_code) return;  // a failure that is dealt with
     const bool failed = ctl->err_step != LLONG_MAX;
-    const int K = failed ? ctl->fail_steps : steps, in = failed ? ctl->fail_in : 0;
+    const int in = ctl->fail_in;
     if (failed) {
-        nb = tube_blocks(nx, J, K);
+        nb = tube_blocks(nx, J, ctl->fail_steps);
         stride = 1;
     }
     double s[4] = {0.0, 0.0, 0.0, 0.0};
@@ -303,15 +277,8 @@ tube_finalize_kernel(const double* __restrict__ partials, int64_t nb, int64_t st
         o = worse(o, row_out(p));
     }
     o = block_rows<TPB / 64>(s, o);
-    int reach = o.reach;
-    if (failed) {
-        double none[4] = {0.0, 0.0, 0.0, 0.0};
-        reach = tube_again<T, SP, J, NA>(in ? Y1 : Y0, in ? Y0 : Y1, nx, bc, tube_tiles(nx, J, K), K, o.errsub - 1, k,
-                                         s_edges, s_stash);
-        reach = block_rows<TPB / 64>(none, TubeOut{reach, 0, 0}).reach;
-    }
     if (threadIdx.x != 0) return;
-    ctl->max_reach = reach;
+    ctl->max_reach = o.reach;
     if (failed) {
         ctl->err_code = o.err;
         ctl->err_buf = o.errsub > 1 ? in ^ 1 : in;
@@ -320,6 +287,23 @@ tube_finalize_kernel(const double* __restrict__ partials, int64_t nb, int64_t st
         ctl->totals_sp = 0.0;
         ctl->totals_step = step0 + steps - 1;
     }
+}
+
+// After a failed launch of K-step tiles: makes the `steps` good steps before the
+// failing one again, from Y to Yn, and the failing one for its largest reach.
+template <typename T, bool SP, int J>
+__global__ void __launch_bounds__(kTubeTPB) __attribute__((amdgpu_waves_per_eu(kTubeWpe<T, SP, J>)))
+tube_again_kernel(const T* __restrict__ Y, T* __restrict__ Yn, int64_t nx, int bc, Consts k, StepCtl* __restrict__ ctl,
+                  int64_t ntiles, int K, int steps)
+{
+    __shared__ TubeEdges<T> s_edges[kTubeNW];
+    __shared__ TubeStash<T, SP, J> s_stash[kTubeNW];
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t tile = (int64_t)blockIdx.x * kTubeNW + wid, X0 = tile * tube_cols(J, K);
+    if (tile >= ntiles) return;
+    double tot[SP ? 4 : 3] = {};
+    const TubeOut o = tube_run<T, SP, J, true>(Y, Yn, nx, bc, X0, K, steps + 1, k, s_edges[wid], s_stash[wid], tot);
+    if ((threadIdx.x & 63) == 0) atomicMax(&ctl->max_reach, o.reach);
 }
 
 // floor(v) and c'_1 of every node (a spare lane repeats the last node).
@@ -369,12 +353,10 @@ pool_tube_kernel(PoolView v, Consts k, int K, int steps, int commit)
 }
 
 // Per slot of a 1-D pool (one block each): the reduction of tube_finalize_kernel
-// over the slot's tiles; commits the launch's steps.
-template <typename T, bool SP, int J>
-__global__ void __launch_bounds__(kFinTPB) pool_tube_finalize_kernel(PoolView v, Consts k, int K, int steps, int commit)
+// over the slot's tiles; commits the launch's steps.  A step that failed after good
+// ones of its launch leaves the slot's tiles marked for pool_tube_again_kernel.
+__global__ void __launch_bounds__(kFinTPB) pool_tube_finalize_kernel(PoolView v, int steps, int commit)
 {
-    __shared__ TubeEdges<T> s_edges[kFinTPB / 64];
-    __shared__ TubeStash<T, SP, J> s_stash[kFinTPB / 64];
     const PoolProb& P = v.probs[blockIdx.x];
     PoolState& S = v.state[blockIdx.x];
     const int64_t done = S.done;
@@ -390,29 +372,50 @@ __global__ void __launch_bounds__(kFinTPB) pool_tube_finalize_kernel(PoolView v,
         o = worse(o, row_out(p));
     }
     o = block_rows<kFinTPB / 64>(s, o);
-    int reach = o.reach;
-    if (o.errsub) {
-        T* arena = (T*)v.arena;
-        double none[4] = {0.0, 0.0, 0.0, 0.0};
-        reach = tube_again<T, SP, J, kFinTPB / 64>(arena + P.off[set], arena + P.off[set ^ 1], P.nx, P.bc_x, P.t1 - P.t0, K,
-                                                o.errsub - 1, k, s_edges, s_stash);
-        reach = block_rows<kFinTPB / 64>(none, TubeOut{reach, 0, 0}).reach;
-    }
-    const int64_t now = done + (o.errsub ? o.errsub - 1 : n);
-    const int nset = now > done ? set ^ 1 : set;
+    const int good = o.errsub ? o.errsub - 1 : n;
+    const int64_t now = done + good;
+    const int nset = good > 0 ? set ^ 1 : set;
     const int64_t left = P.target - now;
-    const int word = nset | (!o.errsub && left > 0 ? kTileLive | (int)min(left, (int64_t)kTileLeftMax) << kTileLeftShift : 0);
+    int word = nset;
+    if (o.errsub && good > 0) word |= kTileAgain | good << kTileLeftShift;
+    if (!o.errsub && left > 0) word |= kTileLive | (int)min(left, (int64_t)kTileLeftMax) << kTileLeftShift;
     for (int64_t t = P.t0 + threadIdx.x; t < P.t1; t += kFinTPB) v.tstate[t] = word;
     if (threadIdx.x != 0) return;
     for (int f = 0; f < 4; ++f) S.totals[f] = s[f];
-    S.max_reach = reach;
+    S.max_reach = o.reach;
     S.totals_step = done + n;
     S.done = now;
     S.set = nset;
     if (o.errsub) {
         S.err_code = o.err;
         S.err_step = now + 1;
+        if (good > 0) atomicAdd(&v.next[0], 1);
     }
+}
+
+// Behind the launches of one call, some of more than one step: the good steps of
+// launches that failed, made again.  (next[0] says whether there may be any; the
+// next upload of the tables clears it.)
+template <typename T, bool SP, int J>
+__global__ void __launch_bounds__(kTubeTPB) __attribute__((amdgpu_waves_per_eu(kTubeWpe<T, SP, J>)))
+pool_tube_again_kernel(PoolView v, Consts k, int K)
+{
+    __shared__ TubeEdges<T> s_edges[kTubeNW];
+    __shared__ TubeStash<T, SP, J> s_stash[kTubeNW];
+    if (v.next[0] == 0) return;
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int t = blockIdx.x * kTubeNW + wid;
+    if (t >= *v.ntiles) return;
+    const int ts = v.tstate[t];
+    if (!(ts & kTileAgain)) return;
+    T* arena = (T*)v.arena;
+    const PoolTile& tl = v.tiles[t];
+    const int64_t o0 = tl.off[0], o1 = tl.off[1];
+    const int64_t from = (ts & kTileSet) ? o0 : o1, to = (ts & kTileSet) ? o1 : o0;  // (the word has the new set)
+    double tot[SP ? 4 : 3] = {};
+    tube_run<T, SP, J>(arena + from, arena + to, tl.nx, tl.bc_x, tl.x0, K, ts >> kTileLeftShift, k, s_edges[wid],
+                       s_stash[wid], tot);
+    if ((threadIdx.x & 63) == 0) v.tstate[t] = ts & kTileSet;
 }
 
 // Per slot of a square-lattice pool (one block each): the same fixed-order
@@ -525,24 +528,11 @@ static hipError_t launch_tube_j(const T* Y, T* Yn, const Grid& g, const Consts& 
 }
 
 template <typename T, bool SP, int J>
-static hipError_t launch_tube_finalize_j(T* Y0, T* Y1, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
-                                         long long step0, int steps, hipStream_t stream)
+static hipError_t launch_tube_again_j(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, int K, int steps,
+                                      hipStream_t stream)
 {
-    int64_t nb = tube_blocks(g.nx, J, steps), stride = 1;
-    if (nb > 16 * kChunk) {  // many rows: fold each chunk first, on many CUs
-        const int64_t n = (nb + kChunk - 1) / kChunk;
-        tube_chunk_kernel<<<(unsigned)n, kChunk, 0, stream>>>(partials, nb, ctl);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        nb = n;
-        stride = kChunk;
-    }
-    if (nb >= kFinManyRows)
-        tube_finalize_kernel<T, SP, J, kFinMaxTPB><<<1, kFinMaxTPB, 0, stream>>>(partials, nb, stride, ctl, step0,
-                                                                               steps, Y0, Y1, g.nx, g.bc_x, k);
-    else
-        tube_finalize_kernel<T, SP, J, kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, nb, stride, ctl, step0, steps, Y0,
-                                                                         Y1, g.nx, g.bc_x, k);
+    tube_again_kernel<T, SP, J><<<(unsigned)tube_blocks(g.nx, J, K), kTubeTPB, 0, stream>>>(
+        Y, Yn, g.nx, g.bc_x, k, ctl, tube_tiles(g.nx, J, K), K, steps);
     return hipGetLastError();
 }
 
@@ -559,15 +549,35 @@ hipError_t launch_tube(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCt
 }
 
 template <typename T>
-hipError_t launch_tube_finalize(T* Y0, T* Y1, const Grid& g, const Consts& k, StepCtl* ctl, double* partials,
-                                long long step0, int steps, hipStream_t stream)
+hipError_t launch_tube_again(const T* Y, T* Yn, const Grid& g, const Consts& k, StepCtl* ctl, int K, int steps,
+                             hipStream_t stream)
 {
     const bool shrt = tube_shape(g.nx, k.species, sizeof(T) == 8).J == 2;
     if (k.species)
-        return shrt ? launch_tube_finalize_j<T, true, 2>(Y0, Y1, g, k, ctl, partials, step0, steps, stream)
-                    : launch_tube_finalize_j<T, true, kLongJ<T, true>>(Y0, Y1, g, k, ctl, partials, step0, steps, stream);
-    return shrt ? launch_tube_finalize_j<T, false, 2>(Y0, Y1, g, k, ctl, partials, step0, steps, stream)
-                : launch_tube_finalize_j<T, false, kLongJ<T, false>>(Y0, Y1, g, k, ctl, partials, step0, steps, stream);
+        return shrt ? launch_tube_again_j<T, true, 2>(Y, Yn, g, k, ctl, K, steps, stream)
+                    : launch_tube_again_j<T, true, kLongJ<T, true>>(Y, Yn, g, k, ctl, K, steps, stream);
+    return shrt ? launch_tube_again_j<T, false, 2>(Y, Yn, g, k, ctl, K, steps, stream)
+                : launch_tube_again_j<T, false, kLongJ<T, false>>(Y, Yn, g, k, ctl, K, steps, stream);
+}
+
+hipError_t launch_tube_finalize(const Grid& g, const Consts& k, bool fp64, StepCtl* ctl, double* partials,
+                                long long step0, int steps, hipStream_t stream)
+{
+    const int J = tube_shape(g.nx, k.species, fp64).J;
+    int64_t nb = tube_blocks(g.nx, J, steps), stride = 1;
+    if (nb > 16 * kChunk) {  // many rows: fold each chunk first, on many CUs
+        const int64_t n = (nb + kChunk - 1) / kChunk;
+        tube_chunk_kernel<<<(unsigned)n, kChunk, 0, stream>>>(partials, nb, ctl);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        nb = n;
+        stride = kChunk;
+    }
+    if (nb >= kFinManyRows)
+        tube_finalize_kernel<kFinMaxTPB><<<1, kFinMaxTPB, 0, stream>>>(partials, nb, stride, ctl, step0, steps, g.nx, J);
+    else
+        tube_finalize_kernel<kFinTPB><<<1, kFinTPB, 0, stream>>>(partials, nb, stride, ctl, step0, steps, g.nx, J);
+    return hipGetLastError();
 }
 
 template <typename T>
@@ -589,8 +599,16 @@ hipError_t launch_pool1d(const PoolView& v, const Consts& k, int K, int steps, i
     else pool_tube_kernel<T, false, J><<<nblocks, kTubeTPB, 0, stream>>>(v, k, K, steps, commit);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (k.species) pool_tube_finalize_kernel<T, true, JS><<<nslots, kFinTPB, 0, stream>>>(v, k, K, steps, commit);
-    else pool_tube_finalize_kernel<T, false, J><<<nslots, kFinTPB, 0, stream>>>(v, k, K, steps, commit);
+    pool_tube_finalize_kernel<<<nslots, kFinTPB, 0, stream>>>(v, steps, commit);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_pool1d_again(const PoolView& v, const Consts& k, int K, int nblocks, hipStream_t stream)
+{
+    constexpr int J = kLongJ<T, false>, JS = kLongJ<T, true>;
+    if (k.species) pool_tube_again_kernel<T, true, JS><<<nblocks, kTubeTPB, 0, stream>>>(v, k, K);
+    else pool_tube_again_kernel<T, false, J><<<nblocks, kTubeTPB, 0, stream>>>(v, k, K);
     return hipGetLastError();
 }
 
@@ -623,15 +641,17 @@ template hipError_t launch_tube<double>(const double*, double*, const Grid&, con
                                         int, int, hipStream_t);
 template hipError_t launch_tube<float>(const float*, float*, const Grid&, const Consts&, StepCtl*, double*, long long,
                                        int, int, hipStream_t);
-template hipError_t launch_tube_finalize<double>(double*, double*, const Grid&, const Consts&, StepCtl*, double*,
-                                                 long long, int, hipStream_t);
-template hipError_t launch_tube_finalize<float>(float*, float*, const Grid&, const Consts&, StepCtl*, double*,
-                                                long long, int, hipStream_t);
+template hipError_t launch_tube_again<double>(const double*, double*, const Grid&, const Consts&, StepCtl*, int, int,
+                                              hipStream_t);
+template hipError_t launch_tube_again<float>(const float*, float*, const Grid&, const Consts&, StepCtl*, int, int,
+                                             hipStream_t);
 template hipError_t launch_lanes_tube<double>(const double*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
                                               hipStream_t);
 template hipError_t launch_lanes_tube<float>(const float*, const Grid&, const Consts&, int32_t*, int32_t*, int32_t*,
                                              hipStream_t);
 template hipError_t launch_pool1d<double>(const PoolView&, const Consts&, int, int, int, int, int, hipStream_t);
 template hipError_t launch_pool1d<float>(const PoolView&, const Consts&, int, int, int, int, int, hipStream_t);
+template hipError_t launch_pool1d_again<double>(const PoolView&, const Consts&, int, int, hipStream_t);
+template hipError_t launch_pool1d_again<float>(const PoolView&, const Consts&, int, int, hipStream_t);
 
 }  // namespace lbsd

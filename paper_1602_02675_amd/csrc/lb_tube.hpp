@@ -895,7 +895,9 @@ struct TubeOut {
 // `steps` <= K steps of the destination nodes [X0, X0 + tube_cols(J, K)), from Y
 // to Yn, with the halo lanes of K steps; adds the new moments to tot.  Stops at
 // the first step with a bad source or a reach beyond H (Yn is then not written).
-template <typename T, bool SP, int J>
+// AGAIN: the last step is made for its outcome alone, and Yn gets the state before
+// it (unless it is the first).
+template <typename T, bool SP, int J, bool AGAIN = false>
 __device__ __forceinline__ TubeOut tube_run(const T* __restrict__ Y, T* __restrict__ Yn, int64_t nx, int bc,
                                             int64_t X0, int K, int steps, const Consts& k, TubeEdges<T>& edges,
                                             TubeStash<T, SP, J>& st, double (&tot)[SP ? 4 : 3])
@@ -920,6 +922,9 @@ __device__ __forceinline__ TubeOut tube_run(const T* __restrict__ Y, T* __restri
             edges_get(edges, y, xb, nx, bc);
             wave_sync();
         }
+        if constexpr (AGAIN) {
+            if (i > 0 && i == steps - 1) tube_store(Yn, y, xb, nx, lane >= halo && lane < 64 - halo, tot);
+        }
         out.err = tube_step<T, SP>(y, t, k, tc, st, max(i * LOST, first), min(64 - i * LOST, top), lane, &out.reach);
         if (out.err) {
             out.errsub = i + 1;
@@ -927,7 +932,7 @@ __device__ __forceinline__ TubeOut tube_run(const T* __restrict__ Y, T* __restri
         }
         static_for<NF>([&](auto f) { static_for<J>([&](auto j) { y[f][j] = t[f][j]; }); });
     }
-    tube_store(Yn, y, xb, nx, lane >= halo && lane < 64 - halo, tot);
+    if constexpr (!AGAIN) tube_store(Yn, y, xb, nx, lane >= halo && lane < 64 - halo, tot);
     return out;
 }
 

@@ -339,6 +339,177 @@ struct LaneHist {
     }
 };
 
+// LaneHist in LDS (the lane's own columns): a ring by row for each speed, LB + c
+// values.
+template <int LB>
+struct LaneHistLds {
+    static constexpr int N = LB * LB + LB * (LB + 1) / 2;  // sum over c = 1 .. LB of LB + c
+    double* h;        // this lane's column, rows 64 apart
+    int at[LB + 1];   // the current row's place (so far: the row LB + c before it)
+    double now[LB + 1];
+    static constexpr int off(int c) { return (c - 1) * LB + c * (c - 1) / 2; }
+    __device__ __forceinline__ void init(double* column)
+    {
+        h = column;
+        static_for<N>([&](auto i) { h[i * 64] = 0.0; });
+        static_for<LB>([&](auto i) { at[i + 1] = 0; });
+    }
+    __device__ __forceinline__ void set(int c, double m) { now[c] = m; }
+    __device__ __forceinline__ double lane_py() const
+    {
+        bool eq = true;
+        double up[LB + 1], dn[LB + 1];
+        static_for<LB>([&](auto i) {
+            constexpr int c = i + 1;
+            up[c] = h[(off(c) + at[c]) * 64];
+            const int k = at[c] - (LB - c);
+            dn[c] = c == LB ? now[c] : h[(off(c) + (k < 0 ? k + LB + c : k)) * 64];
+            eq = eq && up[c] == dn[c];
+        });
+        if (__all(eq)) return 0.0;
+        double a = 0.0, l = 0.0;
+        static_for<LB>([&](auto i) { dd_add(a, l, (double)(LB - i) * up[LB - i]); });
+        static_for<LB>([&](auto i) { dd_add(a, l, -((double)(i + 1) * dn[i + 1])); });
+        return eq ? 0.0 : a + l;
+    }
+    __device__ __forceinline__ void shift()
+    {
+        static_for<LB>([&](auto i) {
+            constexpr int c = i + 1;
+            h[(off(c) + at[c]) * 64] = now[c];
+            at[c] = at[c] + 1 == LB + c ? 0 : at[c] + 1;
+        });
+    }
+};
+
+// Fields of a pass over a tile: rho, rho v_x and rho E; rho v_y; rho chi.
+constexpr int kMPE = 1, kVy = 2, kChi = 4, kAllFields = 7;
+constexpr bool has_field(int fields, int c) { return fields >> (c == 2 ? 1 : (c == 4 ? 2 : 0)) & 1; }
+constexpr int field_count(int fields)
+{
+    return (fields & kMPE ? 3 : 0) + (fields & kVy ? 1 : 0) + (fields & kChi ? 1 : 0);
+}
+// Place of field c of Dest (m, p, w, e, x) among them, -1 if it is none.
+constexpr int field_place(int fields, int c)
+{
+    int n = 0;
+    for (int i = 0; i < c; ++i) n += has_field(fields, i) ? 1 : 0;
+    return has_field(fields, c) ? n : -1;
+}
+
+// The 2 H + 1 pending rows of a far march (a ring by row): those of its fields that
+// are kept in LDS and, with rho v_y, the lane momentum that far-reaching classes
+// bring, in double-length sums.
+template <typename T, int FIELDS, int LDS>
+struct FarRows {
+    static constexpr int NR = 2 * kMH + 1;
+    static constexpr int NV = field_count(FIELDS & LDS);
+    double hl[(FIELDS & kVy) ? NR : 1][2][(FIELDS & kVy) ? 64 : 1];
+    T v[NV ? NR : 1][NV ? NV : 1][NV ? 64 : 1];
+};
+// The other fields of a lane, in scratch memory (an array of its own: in one struct
+// with a pointer to the rows, that pointer would be in memory too, and the rows'
+// accesses would not know that they are LDS).
+template <typename T, int OUT>
+struct FarOwn {
+    T v[2 * kMH + 1][OUT ? field_count(OUT) : 1];
+};
+template <typename T, int FIELDS, int LDS>
+__device__ __forceinline__ Dest<T> far_get(const FarRows<T, FIELDS, LDS>& rows, const FarOwn<T, FIELDS & ~LDS>& own,
+                                           int j, int lane)
+{
+    T f[5] = {};
+    static_for<5>([&](auto c) {
+        constexpr int in = field_place(FIELDS & LDS, c), out = field_place(FIELDS & ~LDS, c);
+        if constexpr (in >= 0) f[c] = rows.v[j][in][lane];
+        if constexpr (out >= 0) f[c] = own.v[j][out];
+    });
+    Dest<T> d;
+    d.m = f[0], d.p = f[1], d.w = f[2], d.e = f[3], d.x = f[4];
+    return d;
+}
+template <typename T, int FIELDS, int LDS>
+__device__ __forceinline__ void far_put(FarRows<T, FIELDS, LDS>& rows, FarOwn<T, FIELDS & ~LDS>& own, int j, int lane,
+                                        const Dest<T>& d)
+{
+    const T f[5] = {d.m, d.p, d.w, d.e, d.x};
+    static_for<5>([&](auto c) {
+        constexpr int in = field_place(FIELDS & LDS, c), out = field_place(FIELDS & ~LDS, c);
+        if constexpr (in >= 0) rows.v[j][in][lane] = f[c];
+        if constexpr (out >= 0) own.v[j][out] = f[c];
+    });
+}
+template <typename T, int FIELDS, int LDS>
+__device__ __forceinline__ void far_zero(FarRows<T, FIELDS, LDS>& rows, FarOwn<T, FIELDS & ~LDS>& own, int j, int lane)
+{
+    Dest<T> d;
+    d.zero();
+    far_put(rows, own, j, lane, d);
+    if constexpr ((FIELDS & kVy) != 0) rows.hl[j][0][lane] = rows.hl[j][1][lane] = 0.0;
+}
+template <typename T, int FIELDS, int LDS>
+__device__ __forceinline__ void far_add(FarRows<T, FIELDS, LDS>& rows, FarOwn<T, FIELDS & ~LDS>& own, int j, int lane,
+                                        const Dest<T>& d)
+{
+#pragma clang fp contract(off)
+    Dest<T> q = far_get(rows, own, j, lane);
+    q.m += d.m;
+    q.p += d.p;
+    q.w += d.w;
+    q.e += d.e;
+    q.x += d.x;
+    far_put(rows, own, j, lane, q);
+}
+// Lane momentum g to row j.
+template <typename T, int FIELDS, int LDS>
+__device__ __forceinline__ void far_add_lane(FarRows<T, FIELDS, LDS>& rows, int j, int lane, double g)
+{
+    if constexpr ((FIELDS & kVy) != 0) {
+        double h = rows.hl[j][0][lane], l = rows.hl[j][1][lane];
+        dd_add(h, l, g);
+        rows.hl[j][0][lane] = h;
+        rows.hl[j][1][lane] = l;
+    }
+}
+
+// What a wavefront of the general pass keeps in LDS: the rows of a far march or,
+// with NEAR, the near form's destination FIFO and lane momentum history (they take
+// 86 registers in FP64 with a rest level, 64 with two gases, and without them two
+// wavefronts fit a SIMD: four states on 2048^2 nodes 325 and 306 us per step, with
+// one wavefront and all of it in registers 407 and 382).  A far march's 11 rows of
+// four or five fields do not fit scratch memory's way to the L2 (flows with |v_y|
+// around 1.5 waited for it 76 % of the time) and in FP64 not a wavefront's 20 KB of
+// LDS either, so FP64 marches a far tile twice, for some of the fields each
+// (2048^2 nodes 804 -> 433 us per step, rest level 1090 -> 554, two gases, rho chi
+// in scratch memory, 1666 -> 874).  With both a rest level and two gases one
+// wavefront fits a SIMD either way, and the LDS holds all fields (1448 -> 670).
+// FP32 keeps its rows in scratch memory, half the size: in LDS they would cost the
+// pools' third block per CU (409 -> 412; two gases 779 -> 627).
+template <typename T, bool REST, bool SP>
+struct MarchStash {
+    static constexpr bool FP64 = sizeof(T) == 8, NEAR = FP64 && REST != SP;
+    static constexpr int LB = kSpeeds<REST> - 1, ND = SP ? 5 : 4;
+    // fields of the far marches (F2 = 0: all in the first), and those of them in LDS
+    static constexpr int ALL = kMPE | kVy | (SP ? kChi : 0);
+    static constexpr int F1 = FP64 && !(REST && SP) ? kMPE : ALL, F2 = ALL & ~F1;
+    static constexpr int L1 = FP64 ? kAllFields : 0, L2 = kVy;
+    struct Near {
+        double hist[NEAR ? LaneHistLds<LB>::N : 1][NEAR ? 64 : 1], fifo[NEAR ? 2 * LB * ND : 1][NEAR ? 64 : 1];
+    };
+    union {
+        Near near;
+        FarRows<T, F1, L1> far1;
+        FarRows<T, F2, L2> far2;
+    };
+    template <int FIELDS>
+    __device__ __forceinline__ auto& far()
+    {
+        if constexpr (FIELDS == F2) return far2;
+        else if constexpr (FIELDS == F1) return far1;
+        else return near;  // (the near form, which has none)
+    }
+};
+
 template <typename T, int NF>
 struct MarchIO {  // a tile's source columns and destination columns of one lane
     const T* Y;
@@ -373,29 +544,34 @@ struct MarchIO {  // a tile's source columns and destination columns of one lane
 #pragma unroll
         for (int c = 0; c < NF; ++c) m[c] = *(const T*)((const char*)(row + (int64_t)c * nn) + sxb);
     }
+    template <int FIELDS = kAllFields>
     __device__ __forceinline__ void store(int64_t row, T r, T p, T py, T e, T x) const
     {
         T* o = Yn + row * nx;
-        *(T*)((char*)o + gxb) = r;
-        *(T*)((char*)(o + nn) + gxb) = p;
-        *(T*)((char*)(o + 2 * nn) + gxb) = py;
-        *(T*)((char*)(o + 3 * nn) + gxb) = e;
-        if constexpr (NF > 4) *(T*)((char*)(o + 4 * nn) + gxb) = x;
+        const T v[5] = {r, p, py, e, x};
+        static_for<NF>([&](auto c) {
+            if constexpr (has_field(FIELDS, c)) *(T*)((char*)(o + c * nn) + gxb) = v[c];
+        });
     }
 };
 
-// A tile's row of partials: field sums (rho chi at index 6), reach, error bits.
-template <int NF>
+// A tile's row of partials: field sums (rho chi at index 6), reach, error bits;
+// of a march for some of the fields, theirs.
+template <int NF, int FIELDS = kAllFields>
 __device__ __forceinline__ void march_partials(double (&tot)[NF], int reach, bool bad, double* __restrict__ prow,
                                                int lane)
 {
-#pragma unroll
-    for (int c = 0; c < NF; ++c) tot[c] = wave_sum(tot[c]);
+    static_for<NF>([&](auto c) {
+        if constexpr (has_field(FIELDS, c)) tot[c] = wave_sum(tot[c]);
+    });
     if (lane == 0) {
-#pragma unroll
-        for (int c = 0; c < NF; ++c) prow[c < 4 ? c : 6] = tot[c];
-        prow[4] = (double)reach;
-        prow[5] = (double)((reach > kMH ? kErrReach : 0) | (bad ? kErrState : 0));
+        static_for<NF>([&](auto c) {
+            if constexpr (has_field(FIELDS, c)) prow[c < 4 ? c : 6] = tot[c];
+        });
+        if constexpr ((FIELDS & kMPE) != 0) {
+            prow[4] = (double)reach;
+            prow[5] = (double)((reach > kMH ? kErrReach : 0) | (bad ? kErrState : 0));
+        }
     }
 }
 
@@ -563,13 +739,6 @@ __device__ __forceinline__ bool march_tile_lean(const MarchIO<T, SP ? 5 : 4>& io
     return true;
 }
 
-// LDS of one wavefront of the general pass: the lane momentum of rho v_y that
-// far-reaching classes (below) bring to the 2 H + 1 pending rows, in
-// double-length sums (a ring by row).
-struct MarchRing {
-    double h[2 * kMH + 1][64], l[2 * kMH + 1][64];
-};
-
 // The general pass, rows [Y0, ylast) of one tile: any flow within the halo.
 // Near classes (floor(v_y) in {-1, 0}, c'_1 <= kSpeeds - 2) go through the two
 // stages: their corners reach the rows -1 .. 1 from the source, so the corner
@@ -579,27 +748,29 @@ struct MarchRing {
 // destinations (the rows further out than the packets of near classes come
 // from are looked at for that only).  FAR = true takes every class: the others
 // add their packets, class by class and corner row by corner row, straight to
-// the 2 H + 1 destination rows they can reach (rare, so those rows may live in
-// scratch memory; in registers they would halve the pass's occupancy).  A node that no far
-// source reaches gets the same bits either way.
+// the 2 H + 1 destination rows they can reach (FarRows), for the fields FIELDS (what
+// the others alone need falls away; the first march, with rho, reports reach and
+// errors).  A node that no far source reaches gets the same bits either way.
 // Returns 1 when complete, 0 when a far class was met (FAR = false only).
 // *unlean: some source within LB rows is beyond the lean pass.
-template <typename T, bool REST, bool SP, bool FAR>
+template <typename T, bool REST, bool SP, bool FAR, int FIELDS>
 __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>& io, const Consts& k, int64_t Y0,
-                                                   int64_t ylast, double* __restrict__ prow, MarchRing* ring,
-                                                   bool* unlean)
+                                                   int64_t ylast, double* __restrict__ prow,
+                                                   MarchStash<T, REST, SP>& st, bool* unlean)
 {
 #pragma clang fp contract(off)
     constexpr int NF = SP ? 5 : 4, NS = kSpeeds<REST>, LB = NS - 1;
     constexpr int NSL = 2 * LB + 1;         // destination FIFO: slot j + LB is row (current) - 1 + j
     constexpr int LD = FAR ? kMH : LB + 1;  // row (current) - LD is written out
     constexpr int EDGE = kMH - LB - 1;      // rows looked at only (FAR = false)
-    constexpr int NR = 2 * kMH + 1;
-    Dest<T> far[FAR ? NR : 1];  // FAR: pending rows (a ring by row, in scratch memory)
-    const auto ring_row = [](int r, int o) { return (r + o + 2 * NR) % NR; };  // of row (current) + o
+    constexpr bool VY = (FIELDS & kVy) != 0;
+    using S = MarchStash<T, REST, SP>;
+    auto& far = st.template far<FIELDS>();
+    FarOwn<T, FIELDS & ~(FIELDS == S::F2 ? S::L2 : S::L1)> own;
+    const auto far_row = [](int r, int o) { return (r + o + 2 * (2 * kMH + 1)) % (2 * kMH + 1); };  // row (current) + o
     const int lane = threadIdx.x & 63;
     const int nrows = (int)(ylast - Y0) + 2 * kMH;
-    Dest<T> f[NSL];
+    Dest<T> f[NSL];  // (with FIFO: in LDS)
     static_for<NSL>([&](auto j) { f[j].zero(); });
     CSum<T> u[3][NS];  // corner sums of rows (current) - 1, 0, + 1
     static_for<NS>([&](auto c) {
@@ -608,14 +779,18 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
         u[2][c].zero();
     });
     int has0 = 0, has1 = 0, has2 = 0;  // speeds present in them
-    LaneHist<LB, T> hist;
-    hist.zero();
+    constexpr bool FIFO = S::NEAR && !FAR;
+    constexpr int ND = S::ND;
+    std::conditional_t<FIFO, LaneHistLds<LB>, LaneHist<LB, T>> hist;
+    if constexpr (FIFO) {
+        hist.init(&st.near.hist[0][lane]);
+        static_for<2 * LB * ND>([&](auto j) { st.near.fifo[j][lane] = 0.0; });
+    } else {
+        hist.zero();
+    }
     if constexpr (FAR) {
 #pragma unroll 1
-        for (int j = 0; j < NR; ++j) {
-            far[j].zero();
-            ring->h[j][lane] = ring->l[j][lane] = 0.0;
-        }
+        for (int j = 0; j <= 2 * kMH; ++j) far_zero(far, own, j, lane);
     }
     double tot[NF] = {};
     int reach = 0;
@@ -703,21 +878,8 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
                     if (row == 1) put(u[2], has2, std::integral_constant<int, 2>{});
                 } else if constexpr (FAR) {
                     // add d to row (current) + o, and the lane momentum g
-                    auto fadd = [&](int o, const Dest<T>& d) {
-                        Dest<T>& q = far[ring_row(r, o)];
-                        q.m += d.m;
-                        q.p += d.p;
-                        q.w += d.w;
-                        q.e += d.e;
-                        if constexpr (SP) q.x += d.x;
-                    };
-                    auto gadd = [&](int o, T g) {
-                        const int j = ring_row(r, o);
-                        double h = ring->h[j][lane], l = ring->l[j][lane];
-                        dd_add(h, l, (double)g);
-                        ring->h[j][lane] = h;
-                        ring->l[j][lane] = l;
-                    };
+                    auto fadd = [&](int o, const Dest<T>& d) { far_add(far, own, far_row(r, o), lane, d); };
+                    auto gadd = [&](int o, T g) { far_add_lane(far, far_row(r, o), lane, (double)g); };
                     Dest<T> t;
                     t.zero();
                     if (C == 0) add_here<true, SP>(t, ua);
@@ -756,27 +918,59 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
         }
 
         // stage B of row (current) - 1, whose corner sums are complete
+        if constexpr (FIFO) asm volatile("" ::: "memory");
         Dest<T> t;
         t.zero();
         if (has0 & 1) add_here<true, SP>(t, u[0][0]);
         static_for<LB>([&](auto cm) {
             constexpr int c = cm + 1;
-            CSum<T> q = u[0][c];
-            hist.h[c][0] = q.m;
+            CSum<T>& q = u[0][c];
+            if constexpr (FIFO) hist.set(c, q.m);
+            else hist.h[c][0] = q.m;
             if (!(has0 >> c & 1)) return;
             q.e = fmaT((T)(0.5 * c * c), q.m, q.e);
             add_xlanes<c, true, SP>(t, q);
-            add_ylane<true, SP>(f[LB - c], q, (T)-c);
-            add_ylane<true, SP>(f[LB + c], q, (T)c);
+            if constexpr (!FIFO) {
+                add_ylane<true, SP>(f[LB - c], q, (T)-c);
+                add_ylane<true, SP>(f[LB + c], q, (T)c);
+            }
         });
-        f[LB].m += t.m;
-        f[LB].p += t.p;
-        f[LB].w += t.w;
-        f[LB].e += t.e;
-        if constexpr (SP) f[LB].x += t.x;
+        Dest<T> o;
+        const auto add_t = [&](Dest<T>& d) {
+            d.m += t.m;
+            d.p += t.p;
+            d.w += t.w;
+            d.e += t.e;
+            if constexpr (SP) d.x += t.x;
+        };
+        if constexpr (FIFO) {  // row by row, each one place on
+            static_for<NSL>([&](auto j) {
+                constexpr int c = j < LB ? LB - j : j - LB;
+                Dest<T> q;
+                q.zero();
+                if constexpr (j < 2 * LB) {
+                    const double* const p = &st.near.fifo[j * ND][lane];
+                    q.m = p[0], q.p = p[64], q.w = p[128], q.e = p[192];
+                    if constexpr (SP) q.x = p[256];
+                }
+                if constexpr (c == 0) add_t(q);
+                else if (has0 >> c & 1) add_ylane<true, SP>(q, u[0][c], (T)(j < LB ? -c : c));
+                if constexpr (j == 0) {
+                    o = q;
+                } else {
+                    double* const p = &st.near.fifo[(j - 1) * ND][lane];
+                    p[0] = q.m, p[64] = q.p, p[128] = q.w, p[192] = q.e;
+                    if constexpr (SP) p[256] = q.x;
+                }
+            });
+        } else {
+            add_t(f[LB]);
+            o = f[0];
+        }
         // row (current) - 1 - LB has all it gets from near classes
-        f[0].w = (T)((double)f[0].w + hist.lane_py());
+        if constexpr (VY) o.w = (T)((double)o.w + hist.lane_py());
         hist.shift();
+        if constexpr (FIFO) asm volatile("" ::: "memory");
         static_for<NS>([&](auto c) {
             u[0][c] = u[1][c];
             u[1][c] = u[2][c];
@@ -788,32 +982,27 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
 
         // row (current) - LD is complete
         const int64_t d = Y0 - kMH + r - LD;
-        Dest<T> o = f[0];
         if constexpr (FAR) {
-            Dest<T>& q = far[ring_row(r, -1 - LB)];
-            q.m += o.m;
-            q.p += o.p;
-            q.w += o.w;
-            q.e += o.e;
-            if constexpr (SP) q.x += o.x;
-            const int j = ring_row(r, -kMH);
-            o = far[j];
-            far[j].zero();
-            o.w = (T)((double)o.w + (ring->h[j][lane] + ring->l[j][lane]));
-            ring->h[j][lane] = ring->l[j][lane] = 0.0;
+            far_add(far, own, far_row(r, -1 - LB), lane, o);
+            const int j = far_row(r, -kMH);
+            o = far_get(far, own, j, lane);
+            if constexpr (VY) o.w = (T)((double)o.w + (far.hl[j][0][lane] + far.hl[j][1][lane]));
+            far_zero(far, own, j, lane);
         }
         if (d >= Y0 && d < ylast && io.dest) {
-            io.store(d, o.m, o.p, o.w, o.e, o.x);
+            io.template store<FIELDS>(d, o.m, o.p, o.w, o.e, o.x);
             tot[0] += (double)o.m;
             tot[1] += (double)o.p;
             tot[2] += (double)o.w;
             tot[3] += (double)o.e;
             if constexpr (SP) tot[NF - 1] += (double)o.x;
         }
-        static_for<NSL - 1>([&](auto j) { f[j] = f[j + 1]; });
-        f[NSL - 1].zero();
+        if constexpr (!FIFO) {
+            static_for<NSL - 1>([&](auto j) { f[j] = f[j + 1]; });
+            f[NSL - 1].zero();
+        }
     }
-    march_partials<NF>(tot, reach, anybad, prow, lane);
+    march_partials<NF, FIELDS>(tot, reach, anybad, prow, lane);
     *unlean = notlean;
     return true;
 }
@@ -821,11 +1010,14 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
 // Either form of the general pass on rows [Y0, ylast) of a tile.
 template <typename T, bool REST, bool SP>
 __device__ __forceinline__ bool march_rows_general(const MarchIO<T, SP ? 5 : 4>& io, const Consts& k, int64_t Y0,
-                                                   int64_t ylast, double* __restrict__ prow, MarchRing* ring)
+                                                   int64_t ylast, double* __restrict__ prow, MarchStash<T, REST, SP>& st)
 {
+    using S = MarchStash<T, REST, SP>;
     bool unlean = false;
-    if (!march_tile_general<T, REST, SP, false>(io, k, Y0, ylast, prow, ring, &unlean))
-        march_tile_general<T, REST, SP, true>(io, k, Y0, ylast, prow, ring, &unlean);
+    if (!march_tile_general<T, REST, SP, false, kAllFields>(io, k, Y0, ylast, prow, st, &unlean)) {
+        march_tile_general<T, REST, SP, true, S::F1>(io, k, Y0, ylast, prow, st, &unlean);
+        if constexpr (S::F2 != 0) march_tile_general<T, REST, SP, true, S::F2>(io, k, Y0, ylast, prow, st, &unlean);
+    }
     return unlean;
 }
 
@@ -862,14 +1054,13 @@ __device__ __forceinline__ bool needs_general(const int* __restrict__ flags, int
 // sums need about 110 registers; two gases three; with a rest level two (4096^2
 // planar nodes 391 us per step, with three and 27 spilled registers 787; both 463,
 // with three and 126 spilled 2650).  FP32 five; two gases or a rest level four,
-// both three (226 and 288 us, with five 277 and 1157).  General: two (three rows
-// of corner sums and, for far classes, 11 destination rows), in FP64 with a rest
-// level or two gases one (2048^2 four-state nodes: rest level 409 us, with two
-// 662; two gases 383 and 576; both 487 and 1706).
+// both three (226 and 288 us, with five 277 and 1157).  General: two, in FP64 with
+// both a rest level and two gases one (424 registers; with two 139 of them are
+// spilled, and 2048^2 four-state nodes take 718 us per step instead of 487).
 template <typename T, bool REST, bool SP>
 constexpr int kLeanWpe = sizeof(T) == 8 ? (REST ? 2 : (SP ? 3 : 4)) : (REST && SP ? 3 : (REST || SP ? 4 : 5));
 template <typename T, bool REST, bool SP>
-constexpr int kGeneralWpe = sizeof(T) == 8 && (REST || SP) ? 1 : 2;
+constexpr int kGeneralWpe = sizeof(T) == 8 && REST && SP ? 1 : 2;
 
 // Counters of StepCtl::next / PoolView::next: tile claims of the two passes;
 // pools: non-zero when the lean pass gave a tile up.
@@ -939,7 +1130,7 @@ __global__ void __launch_bounds__(kMTPB) __attribute__((amdgpu_waves_per_eu(kGen
 march2d_general_kernel(const T* __restrict__ Y, T* __restrict__ Yn, Grid g, Consts k, StepCtl* __restrict__ ctl,
                        double* __restrict__ partials, MarchWords w, long long step, int sy, int tiles_x, int ntiles)
 {
-    __shared__ MarchRing ring[kMNW];
+    __shared__ MarchStash<T, REST, SP> stash[kMNW];
     if (ctl->err_step < step) return;
     const int lane = threadIdx.x & 63;
     const int given = wave_sum(lane < kGivenUp ? ctl->given_up[lane * kGivenUpStride] : 0);
@@ -959,7 +1150,7 @@ march2d_general_kernel(const T* __restrict__ Y, T* __restrict__ Yn, Grid g, Cons
             MarchIO<T, SP ? 5 : 4> io;
             io.set(Y, Yn, g, tx * kMCols, lane);
             const bool unlean = march_rows_general<T, REST, SP>(
-                io, k, c0, c1, partials + ((int64_t)p * ntiles + t) * kPartialStride, &ring[threadIdx.x >> 6]);
+                io, k, c0, c1, partials + ((int64_t)p * ntiles + t) * kPartialStride, stash[threadIdx.x >> 6]);
             if (lane == 0) {
                 if (unlean && w.keep) w.keep[t] = 1;
                 if (p == 0) w.nch[t] = (int)((ylast - Y0 + h - 1) / h);
@@ -1010,7 +1201,7 @@ template <typename T, bool REST, bool SP>
 __global__ void __launch_bounds__(kMTPB) __attribute__((amdgpu_waves_per_eu(kGeneralWpe<T, REST, SP>)))
 pool2d_general_kernel(PoolView v, Consts k)
 {
-    __shared__ MarchRing ring[kMNW];
+    __shared__ MarchStash<T, REST, SP> stash[kMNW];
     if (v.next[kNextGiven] == 0) return;  // nothing left to it
     const int nt = *v.ntiles, lane = threadIdx.x & 63, nwaves = gridDim.x * kMNW;
     T* arena = (T*)v.arena;
@@ -1029,7 +1220,7 @@ pool2d_general_kernel(PoolView v, Consts k)
                 MarchIO<T, SP ? 5 : 4> io;
                 io.set(arena + from, arena + to, g, tl.x0, lane);
                 const bool unlean = march_rows_general<T, REST, SP>(
-                    io, k, tl.y0, ylast, v.partials + (int64_t)t * kPartialStride, &ring[threadIdx.x >> 6]);
+                    io, k, tl.y0, ylast, v.partials + (int64_t)t * kPartialStride, stash[threadIdx.x >> 6]);
                 if (lane == 0 && unlean) v.flags[t] = 1;
             }
         }

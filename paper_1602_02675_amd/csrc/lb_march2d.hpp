@@ -1066,14 +1066,23 @@ constexpr int kGeneralWpe = sizeof(T) == 8 && REST && SP ? 1 : 2;
 // pools: non-zero when the lean pass gave a tile up.
 enum { kNextLean = 0, kNextGeneral = 1, kNextGiven = 2 };
 
-// This wavefront's index among those of the launch's first nb blocks, with the
-// blocks of one XCD (the hardware deals blocks out to the 8 XCDs in turn) on
-// neighbouring tiles, whose halo columns and rows are then in that XCD's L2.
+// Index of block b among nb, with the blocks of one XCD (the hardware deals blocks
+// out to the 8 XCDs in turn) on neighbouring tiles, whose halo columns and rows are
+// then in that XCD's L2.
+__device__ __forceinline__ int march_block(int b, int nb)
+{
+    return (nb & 7) == 0 ? (b & 7) * (nb >> 3) + (b >> 3) : b;
+}
+// This wavefront's index among those of the launch, or of its first nb blocks (the
+// test for these in the lean pass's one cost it 1 % in FP32).
+__device__ __forceinline__ int march_wave()
+{
+    return __builtin_amdgcn_readfirstlane(march_block(blockIdx.x, gridDim.x) * kMNW + (int)(threadIdx.x >> 6));
+}
 __device__ __forceinline__ int march_wave(int nb)
 {
     const int b = blockIdx.x;
-    const int bb = (nb & 7) == 0 && b < nb ? (b & 7) * (nb >> 3) + (b >> 3) : b;
-    return __builtin_amdgcn_readfirstlane(bb * kMNW + (int)(threadIdx.x >> 6));
+    return __builtin_amdgcn_readfirstlane((b < nb ? march_block(b, nb) : b) * kMNW + (int)(threadIdx.x >> 6));
 }
 // As many of the launch's blocks as njobs jobs need, over all XCDs (the jobs of a
 // small grid would else all fall to the blocks of one or two: us per step without /
@@ -1105,7 +1114,7 @@ march2d_lean_kernel(const T* __restrict__ Y, T* __restrict__ Yn, Grid g, Consts 
     if (ctl->err_step < step) return;
     const int lane = threadIdx.x & 63;
     const int nwaves = gridDim.x * kMNW;
-    for (int t = march_wave(gridDim.x); t < ntiles;) {
+    for (int t = march_wave(); t < ntiles;) {
         bool done = false;
         if (!(w.keep && w.keep[t])) {
             const int64_t tx = t % tiles_x, ty = t / tiles_x;

@@ -61,7 +61,6 @@ struct lb_pool {
     int32_t max_slots = 0;
     size_t arena_bytes = 0;
     int64_t max_tiles = 0;
-    int64_t live_tiles = 0;  // most tiles the live slots can have (sum of max_tiles_of)
     // layout inside the bound buffer
     size_t off_probs = 0, off_state = 0, off_tiles = 0, off_tstate = 0, off_ntiles = 0, off_partials = 0,
            off_flags = 0, off_arena = 0, total = 0;
@@ -115,39 +114,30 @@ int64_t tube_tile(const lb_pool* p, int shape)
     return tube_cols(tube_lanes(p->species, p->precision == LB_FP64), kPool1Steps[shape]);
 }
 int64_t tile_cols(const lb_pool* p) { return p->dim == 1 ? tube_tile(p, p->shape) : kPool2Cols; }
-int64_t tiles_of(const lb_pool* p, int64_t nx, int64_t ny, int shape)
-{
-    if (p->dim == 1) {
-        const int64_t t = tube_tile(p, shape);
-        return (nx + t - 1) / t;
-    }
-    return ((nx + kPool2Cols - 1) / kPool2Cols) * ((ny + kPool2MinRows - 1) / kPool2MinRows);  // at most
-}
-
 int launch_blocks(const lb_pool* p, int64_t ntiles, bool lean = false);
 
 // Rows per tile: 1 in 1-D; on the square lattice about
-// kPool2TilesPerBlock[shape] tiles per resident block over the live problems.
+// kPool2TilesPerBlock[shape] tiles per resident block over the live problems, but
+// no more than the tile table holds (many narrow or flat grids).
 int64_t tile_rows(const lb_pool* p)
 {
     if (p->dim == 1) return 1;
-    int64_t strip_rows = 0;  // rows of all column strips of the live problems
-    for (int i = 0; i < p->max_slots; ++i) {
-        const PoolProb& q = p->probs[(size_t)i];
-        if (q.active) strip_rows += ((q.nx + kPool2Cols - 1) / kPool2Cols) * q.ny;
-    }
+    int64_t strip_rows = 0, top = 1;  // rows of all column strips of the live problems; most rows of one
+    for (const PoolProb& q : p->probs)
+        if (q.active) {
+            strip_rows += ((q.nx + kPool2Cols - 1) / kPool2Cols) * q.ny;
+            top = std::max(top, q.ny);
+        }
     const int64_t want = (int64_t)kPool2TilesPerBlock[p->shape] * launch_blocks(p, 0, true);
-    const int64_t rows = (strip_rows + want - 1) / std::max<int64_t>(want, 1);
-    return std::max<int64_t>(rows, kPool2MinRows);
-}
-
-// Worst case over the shapes, so that a later shape change always fits.
-int64_t max_tiles_of(const lb_pool* p, int64_t nx, int64_t ny)
-{
-    int64_t m = 0;
-    const int ns = p->dim == 1 ? kPool1Shapes : kPool2Shapes;
-    for (int s = 0; s < ns; ++s) m = std::max(m, tiles_of(p, nx, ny, s));
-    return m;
+    int64_t rows = std::max<int64_t>((strip_rows + want - 1) / std::max<int64_t>(want, 1), kPool2MinRows);
+    const auto tiles = [&](int64_t r) {
+        int64_t n = 0;
+        for (const PoolProb& q : p->probs)
+            if (q.active) n += ((q.nx + kPool2Cols - 1) / kPool2Cols) * ((q.ny + r - 1) / r);
+        return n;
+    };
+    while (rows < top && tiles(rows) > p->max_tiles) rows *= 2;
+    return std::min<int64_t>(rows, (int64_t)1 << 30);
 }
 
 // Blocks (of four wavefronts) of the step launch.  Square lattice: as many as
@@ -431,8 +421,6 @@ int reserve(lb_pool* p, const lb_grid* grid, int64_t steps, int32_t* slot_out)
         if (!p->probs[(size_t)i].active) { slot = i; break; }
     if (slot < 0) return fail(LB_ENOMEM, "no free slot (%d in use)", p->max_slots);
     const int64_t nn = grid->nx * grid->ny;
-    if (p->live_tiles + max_tiles_of(p, grid->nx, grid->ny) > p->max_tiles)
-        return fail(LB_ENOMEM, "tile table full");
     const size_t sb = set_bytes(p, nn), bytes = 2 * sb;
     size_t off = 0;
     if (!arena_take(p, bytes, &off))
@@ -459,7 +447,6 @@ void unreserve(lb_pool* p, int32_t slot)
 {
     PoolProb& q = p->probs[(size_t)slot];
     arena_give(p, p->info[(size_t)slot].arena_off, p->info[(size_t)slot].bytes);
-    if (q.active) p->live_tiles -= max_tiles_of(p, q.nx, q.ny);
     q = PoolProb{};
 }
 
@@ -470,9 +457,7 @@ int activate(lb_pool* p, int32_t slot)
     pool_reset_state_kernel<<<1, 64, 0, p->stream>>>((PoolState*)(p->base + p->off_state) + slot);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "reset slot state");
-    PoolProb& q = p->probs[(size_t)slot];
-    q.active = 1;
-    p->live_tiles += max_tiles_of(p, q.nx, q.ny);
+    p->probs[(size_t)slot].active = 1;
     p->gen[(size_t)slot] += 1;
     p->dirty = true;
     return LB_OK;
@@ -522,11 +507,13 @@ static int create_pool(int32_t dim, double gamma, double gamma2, bool species, c
     p->k.species = species ? 1 : 0;
     p->max_slots = max_slots;
     p->arena_bytes = arena_bytes & ~(size_t)255;
-    // every live slot has at most one partly filled tile row/column per
-    // shape; the rest of its tiles are full (>= 96 nodes in 1-D, >= 54 x 16
-    // on the square lattice)
+    // Tiles of the slots that the arena can hold at once: in 1-D a tile has 96 nodes
+    // at least, and one per slot may be partly filled.  On the square lattice a slot
+    // has a tile per column strip at least (again one partly filled per slot), and
+    // tile_rows makes tiles as tall as the table asks for; 64 tiles per slot and one
+    // per 49 nodes leave it the strip heights it wants but for many narrow grids.
     const int64_t cap_nodes = (int64_t)(p->arena_bytes / (2 * (size_t)p->nf * p->elem));
-    p->max_tiles = (int64_t)max_slots * (dim == 1 ? 3 : 320) + cap_nodes / (dim == 1 ? 85 : 49) + (dim == 1 ? 128 : 320);
+    p->max_tiles = (int64_t)max_slots * (dim == 1 ? 1 : 64) + cap_nodes / (dim == 1 ? 85 : 49) + (dim == 1 ? 128 : 64);
     try {
         p->probs.assign((size_t)max_slots, PoolProb{});
         p->info.assign((size_t)max_slots, SlotInfo{});

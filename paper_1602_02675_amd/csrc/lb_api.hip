@@ -102,9 +102,7 @@ Consts make_consts(int dim, double gamma, const lb_velset* vs)
     k.delta0 = rest ? vs->d0_frac : 0.0;
     k.b0 = rest ? 1.0 : 0.0;
     k.inv_b1 = dim == 1 ? 0.5 : (k.hex ? 1.0 / 6.0 : 0.25);
-    // square lattice with a rest level: d_0 = q (d_1 + d_2), q = b_1 delta0 / (1 - delta0),
-    // so that a rest packet's mass follows from the staged level masses
-    k.rest_q = (dim == 2 && rest && !k.hex) ? 4.0 * vs->d0_frac / (1.0 - vs->d0_frac) : 0.0;
+    k.rest = dim == 2 && rest && !k.hex;
     return k;
 }
 
@@ -345,7 +343,7 @@ int lb_bind(lb_solver* s, void* dev_ptr, size_t bytes, void* hip_stream)
         if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
             return hip_fail(e, "hipDeviceGetAttribute");
         const bool fp64 = s->precision == LB_FP64;
-        const bool rest = s->k.rest_q > 0.0;
+        const bool rest = s->k.rest;
         const int per_cu = fp64 ? march2d_blocks_per_cu<double>(false, rest, s->species)
                                 : march2d_blocks_per_cu<float>(false, rest, s->species);
         const int per_cu_lean = fp64 ? march2d_blocks_per_cu<double>(true, rest, s->species)
@@ -804,7 +802,7 @@ int static_device(StaticDevice** out)
 // Instance of the square lattice's kernels: bit 0 FP32, 1 rest level, 2 two gases.
 int march_kind(const lb_solver* s)
 {
-    return (s->precision == LB_FP64 ? 0 : 1) | (s->k.rest_q > 0.0 ? 2 : 0) | (s->species ? 4 : 0);
+    return (s->precision == LB_FP64 ? 0 : 1) | (s->k.rest ? 2 : 0) | (s->species ? 4 : 0);
 }
 
 bool is_device_ptr(const void* p)

@@ -32,11 +32,11 @@ struct Consts {
     double delta0;    // d_0 / rho on the triple-level sets (0 on the square dual-level set)
     double b0;        // rest-lane multiplicity b_0 (1 with a rest level, else 0)
     double inv_b1;    // 1 / b_1
-    double rest_q;    // square lattice with a rest level: d_0 / (d_1 + d_2) = b_1 delta0 / (1 - delta0)
     double g1m1;      // two gases: gamma_1 - 1 (gas 1, the species field's gas)
     double g2m1;      // two gases: gamma_2 - 1
     int species;      // 1: two gases, a species moment rho chi after rho E
     int hex;          // 1: the hexagonal lattice (2-D)
+    int rest;         // 1: the square lattice with a rest level
 };
 
 // Largest integer c <= kMaxC1 with c*c <= A, for A >= 0 (eq. 26: "int" of sqrt).
@@ -44,9 +44,8 @@ template <typename T>
 __device__ __forceinline__ int isqrt_floor(T A)
 {
 #pragma clang fp contract(off)
-    // a single-precision root is within one of floor(sqrt(A)) for the clamped
-    // root (relative error < 1e-7), the exact comparisons settle it, and A beyond
-    // kMaxC1^2 leaves the whole numbers' range nowhere
+    // a single-precision root (relative error < 1e-7), capped before it becomes a
+    // whole number, is within one of the answer, and the exact comparisons settle it
     int c = (int)fminf(sqrtf((float)A), (float)kMaxC1);
     if (c > 0 && (T)c * (T)c > A) --c;
     if ((T)(c + 1) * (T)(c + 1) <= A) ++c;

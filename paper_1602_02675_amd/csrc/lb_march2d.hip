@@ -70,7 +70,7 @@ hipError_t launch_march2d(const T* Y, T* Yn, const Grid& g, const MarchGeom& m, 
                           StepCtl* ctl, double* partials, const MarchWords& w, long long step, hipStream_t stream)
 {
     if (k.species) return launch_march2d_species<T>(Y, Yn, g, m, k, ctl, partials, w, step, stream);
-    return k.rest_q > 0.0 ? launch_march2d_w<T, true, false>(Y, Yn, g, m, k, ctl, partials, w, step, stream)
+    return k.rest ? launch_march2d_w<T, true, false>(Y, Yn, g, m, k, ctl, partials, w, step, stream)
                           : launch_march2d_w<T, false, false>(Y, Yn, g, m, k, ctl, partials, w, step, stream);
 }
 
@@ -79,7 +79,7 @@ hipError_t launch_lanes_march(const T* Y, const Grid& g, const Consts& k, int32_
                               hipStream_t stream)
 {
     if (k.species) return launch_lanes_species<T>(Y, g, k, fx, fy, c1, stream);
-    return k.rest_q > 0.0 ? launch_lanes_w<T, true, false>(Y, g, k, fx, fy, c1, stream)
+    return k.rest ? launch_lanes_w<T, true, false>(Y, g, k, fx, fy, c1, stream)
                           : launch_lanes_w<T, false, false>(Y, g, k, fx, fy, c1, stream);
 }
 

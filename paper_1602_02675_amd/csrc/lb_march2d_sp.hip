@@ -20,7 +20,7 @@ hipError_t launch_march2d_species(const T* Y, T* Yn, const Grid& g, const MarchG
                                   StepCtl* ctl, double* partials, const MarchWords& w, long long step,
                                   hipStream_t stream)
 {
-    return k.rest_q > 0.0 ? launch_march2d_w<T, true, true>(Y, Yn, g, m, k, ctl, partials, w, step, stream)
+    return k.rest ? launch_march2d_w<T, true, true>(Y, Yn, g, m, k, ctl, partials, w, step, stream)
                           : launch_march2d_w<T, false, true>(Y, Yn, g, m, k, ctl, partials, w, step, stream);
 }
 
@@ -28,7 +28,7 @@ template <typename T>
 hipError_t launch_lanes_species(const T* Y, const Grid& g, const Consts& k, int32_t* fx, int32_t* fy, int32_t* c1,
                                 hipStream_t stream)
 {
-    return k.rest_q > 0.0 ? launch_lanes_w<T, true, true>(Y, g, k, fx, fy, c1, stream)
+    return k.rest ? launch_lanes_w<T, true, true>(Y, g, k, fx, fy, c1, stream)
                           : launch_lanes_w<T, false, true>(Y, g, k, fx, fy, c1, stream);
 }
 

@@ -147,7 +147,7 @@ int64_t tile_rows(const lb_pool* p)
 int launch_blocks(const lb_pool* p, int64_t ntiles, bool lean)
 {
     if (p->dim == 1) return (int)std::max<int64_t>(1, (ntiles + 3) / 4);
-    const bool rest = p->k.rest_q > 0.0;
+    const bool rest = p->k.rest;
     const int per_cu = p->precision == LB_FP64 ? pool2d_blocks_per_cu<double>(lean, rest, p->species)
                                                : pool2d_blocks_per_cu<float>(lean, rest, p->species);
     return std::max(1, p->cus * per_cu);

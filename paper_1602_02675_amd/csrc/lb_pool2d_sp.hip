@@ -17,7 +17,7 @@ template <typename T>
 hipError_t launch_pool2d_species(const PoolView& v, const Consts& k, int nblocks_lean, int nblocks,
                                  hipStream_t stream)
 {
-    return k.rest_q > 0.0 ? launch_pool2d_w<T, true, true>(v, k, nblocks_lean, nblocks, stream)
+    return k.rest ? launch_pool2d_w<T, true, true>(v, k, nblocks_lean, nblocks, stream)
                           : launch_pool2d_w<T, false, true>(v, k, nblocks_lean, nblocks, stream);
 }
 

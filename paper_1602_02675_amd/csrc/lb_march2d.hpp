@@ -21,10 +21,9 @@
 // One wavefront owns a tile of kMCols destination columns (64 lanes less the
 // halo of H = 5 on each side) by a strip of rows and marches down the strip,
 // one source column per lane.  Columns exchange by wavefront shifts (DPP
-// moves between neighbouring lanes), rows through register FIFOs: no LDS, no
-// barriers, and wavefronts never wait for each other.  At 4096^2 in FP64 the
-// earlier form (256-column tiles, packets rebuilt from LDS rows, one barrier
-// per row) issued about 380 VALU instructions per wavefront and row.
+// moves between neighbouring lanes), rows through FIFOs in registers or, for the
+// largest instances of the general pass, in LDS of the wavefront's own
+// (MarchStash): no barriers, and wavefronts never wait for each other.
 //
 // Sources of one row that share floor(v) and c'_1 form a class; a row's
 // classes are taken one after another, the lanes of other classes with zero
@@ -397,116 +396,140 @@ constexpr int field_place(int fields, int c)
     return has_field(fields, c) ? n : -1;
 }
 
-// The 2 H + 1 pending rows of a far march (a ring by row): those of its fields that
-// are kept in LDS and, with rho v_y, the lane momentum that far-reaching classes
-// bring, in double-length sums.
-template <typename T, int FIELDS, int LDS>
+// The 2 H + 1 pending rows of a far march for the fields FIELDS (a ring by row):
+// those of them that are kept in LDS (LDS) and, with rho v_y, the lane momentum that
+// far-reaching classes bring, in double-length sums (in LDS with HL).  COLS: 64, or
+// the destination columns and one more, where the halo lanes put what they form.
+template <typename T_, int FIELDS_, int LDS, bool HL_, int COLS>
 struct FarRows {
-    static constexpr int NR = 2 * kMH + 1;
-    static constexpr int NV = field_count(FIELDS & LDS);
-    double hl[(FIELDS & kVy) ? NR : 1][2][(FIELDS & kVy) ? 64 : 1];
-    T v[NV ? NR : 1][NV ? NV : 1][NV ? 64 : 1];
+    using T = T_;
+    static constexpr int NR = 2 * kMH + 1, FIELDS = FIELDS_, IN = FIELDS & LDS, OUT = FIELDS & ~LDS;
+    static constexpr int NV = field_count(IN);
+    static constexpr bool HL = HL_, L = (FIELDS & kVy) != 0;
+    double hl[L && HL ? NR : 1][2][L && HL ? COLS : 1];
+    T v[NV ? NR : 1][NV ? NV : 1][NV ? COLS : 1];
+    // The rest of a lane's rows, in scratch memory (an array of its own: in one struct
+    // with a pointer to the rows, that pointer would be in memory too, and the rows'
+    // accesses would not know that they are LDS).
+    struct Own {
+        T v[NR][OUT ? field_count(OUT) : 1];
+        double hl[L && !HL ? NR : 1][2];
+    };
+    static __device__ __forceinline__ int col(int lane)
+    {
+        return COLS == 64 ? lane : (int)min((unsigned)(lane - kMH), (unsigned)kMCols);
+    }
 };
-// The other fields of a lane, in scratch memory (an array of its own: in one struct
-// with a pointer to the rows, that pointer would be in memory too, and the rows'
-// accesses would not know that they are LDS).
-template <typename T, int OUT>
-struct FarOwn {
-    T v[2 * kMH + 1][OUT ? field_count(OUT) : 1];
-};
-template <typename T, int FIELDS, int LDS>
-__device__ __forceinline__ Dest<T> far_get(const FarRows<T, FIELDS, LDS>& rows, const FarOwn<T, FIELDS & ~LDS>& own,
-                                           int j, int lane)
+template <typename R>
+__device__ __forceinline__ Dest<typename R::T> far_get(const R& rows, const typename R::Own& own, int j, int col)
 {
-    T f[5] = {};
+    typename R::T f[5] = {};
     static_for<5>([&](auto c) {
-        constexpr int in = field_place(FIELDS & LDS, c), out = field_place(FIELDS & ~LDS, c);
-        if constexpr (in >= 0) f[c] = rows.v[j][in][lane];
+        constexpr int in = field_place(R::IN, c), out = field_place(R::OUT, c);
+        if constexpr (in >= 0) f[c] = rows.v[j][in][col];
         if constexpr (out >= 0) f[c] = own.v[j][out];
     });
-    Dest<T> d;
+    Dest<typename R::T> d;
     d.m = f[0], d.p = f[1], d.w = f[2], d.e = f[3], d.x = f[4];
     return d;
 }
-template <typename T, int FIELDS, int LDS>
-__device__ __forceinline__ void far_put(FarRows<T, FIELDS, LDS>& rows, FarOwn<T, FIELDS & ~LDS>& own, int j, int lane,
-                                        const Dest<T>& d)
+template <typename R>
+__device__ __forceinline__ void far_put(R& rows, typename R::Own& own, int j, int col, const Dest<typename R::T>& d)
 {
-    const T f[5] = {d.m, d.p, d.w, d.e, d.x};
+    const typename R::T f[5] = {d.m, d.p, d.w, d.e, d.x};
     static_for<5>([&](auto c) {
-        constexpr int in = field_place(FIELDS & LDS, c), out = field_place(FIELDS & ~LDS, c);
-        if constexpr (in >= 0) rows.v[j][in][lane] = f[c];
+        constexpr int in = field_place(R::IN, c), out = field_place(R::OUT, c);
+        if constexpr (in >= 0) rows.v[j][in][col] = f[c];
         if constexpr (out >= 0) own.v[j][out] = f[c];
     });
 }
-template <typename T, int FIELDS, int LDS>
-__device__ __forceinline__ void far_zero(FarRows<T, FIELDS, LDS>& rows, FarOwn<T, FIELDS & ~LDS>& own, int j, int lane)
+// The lane momentum of row j: its two parts.
+template <typename R>
+__device__ __forceinline__ void far_get_lane(const R& rows, const typename R::Own& own, int j, int col, double& h, double& l)
 {
-    Dest<T> d;
-    d.zero();
-    far_put(rows, own, j, lane, d);
-    if constexpr ((FIELDS & kVy) != 0) rows.hl[j][0][lane] = rows.hl[j][1][lane] = 0.0;
+    if constexpr (R::HL) h = rows.hl[j][0][col], l = rows.hl[j][1][col];
+    else h = own.hl[j][0], l = own.hl[j][1];
 }
-template <typename T, int FIELDS, int LDS>
-__device__ __forceinline__ void far_add(FarRows<T, FIELDS, LDS>& rows, FarOwn<T, FIELDS & ~LDS>& own, int j, int lane,
-                                        const Dest<T>& d)
+template <typename R>
+__device__ __forceinline__ void far_put_lane(R& rows, typename R::Own& own, int j, int col, double h, double l)
+{
+    if constexpr (R::HL) rows.hl[j][0][col] = h, rows.hl[j][1][col] = l;
+    else own.hl[j][0] = h, own.hl[j][1] = l;
+}
+template <typename R>
+__device__ __forceinline__ void far_zero(R& rows, typename R::Own& own, int j, int col)
+{
+    Dest<typename R::T> d;
+    d.zero();
+    far_put(rows, own, j, col, d);
+    if constexpr (R::L) far_put_lane(rows, own, j, col, 0.0, 0.0);
+}
+template <typename R>
+__device__ __forceinline__ void far_add(R& rows, typename R::Own& own, int j, int col, const Dest<typename R::T>& d)
 {
 #pragma clang fp contract(off)
-    Dest<T> q = far_get(rows, own, j, lane);
+    Dest<typename R::T> q = far_get(rows, own, j, col);
     q.m += d.m;
     q.p += d.p;
     q.w += d.w;
     q.e += d.e;
     q.x += d.x;
-    far_put(rows, own, j, lane, q);
+    far_put(rows, own, j, col, q);
 }
 // Lane momentum g to row j.
-template <typename T, int FIELDS, int LDS>
-__device__ __forceinline__ void far_add_lane(FarRows<T, FIELDS, LDS>& rows, int j, int lane, double g)
+template <typename R>
+__device__ __forceinline__ void far_add_lane(R& rows, typename R::Own& own, int j, int col, double g)
 {
-    if constexpr ((FIELDS & kVy) != 0) {
-        double h = rows.hl[j][0][lane], l = rows.hl[j][1][lane];
+    if constexpr (R::L) {
+        double h, l;
+        far_get_lane(rows, own, j, col, h, l);
         dd_add(h, l, g);
-        rows.hl[j][0][lane] = h;
-        rows.hl[j][1][lane] = l;
+        far_put_lane(rows, own, j, col, h, l);
     }
 }
 
 // What a wavefront of the general pass keeps in LDS: the rows of a far march or,
 // with NEAR, the near form's destination FIFO and lane momentum history (they take
 // 86 registers in FP64 with a rest level, 64 with two gases, and without them two
-// wavefronts fit a SIMD: four states on 2048^2 nodes 325 and 306 us per step, with
-// one wavefront and all of it in registers 407 and 382).  A far march's 11 rows of
-// four or five fields do not fit scratch memory's way to the L2 (flows with |v_y|
-// around 1.5 waited for it 76 % of the time) and in FP64 not a wavefront's 20 KB of
-// LDS either, so FP64 marches a far tile twice, for some of the fields each
-// (2048^2 nodes 804 -> 433 us per step, rest level 1090 -> 554, two gases, rho chi
-// in scratch memory, 1666 -> 874).  With both a rest level and two gases one
-// wavefront fits a SIMD either way, and the LDS holds all fields (1448 -> 670).
-// FP32 keeps its rows in scratch memory, half the size: in LDS they would cost the
-// pools' third block per CU (409 -> 412; two gases 779 -> 627).
+// wavefronts fit a SIMD: four states on 2048^2 nodes 309 and 310 us per step, with
+// one wavefront and all of it in registers 407 and 382).
+//
+// A far march's 11 rows of four or five fields do not fit scratch memory's way to the
+// L2 (flows with |v_y| around 1.5 waited for it 76 % of the time), nor does all of
+// it fit a wavefront's 20 KB of LDS in FP64: what is read and written most is there,
+// the lane momentum's two parts and rho chi in scratch memory.  us per step on 2048^2
+// nodes, all in scratch memory / so: |v_y| around 1.5 804 / 370, two gases 1664 /
+// 1043; four states after 200 steps, when a few nodes in some tiles are far, 548 /
+// 510, two gases 683 / 549.  (Two marches, each with all it needs in LDS: 417, 769,
+// 666 and 668.)  With a rest level, one march would spill 116 registers, and far tiles
+// are marched twice, for some of the fields each (1090 / 531).  With a rest level and
+// two gases one wavefront fits a SIMD, and the LDS holds all fields (1448 / 637).
+// FP32 keeps its fields, half the size, in scratch memory: in LDS they would cost
+// the pools' third block per CU (409 / 369; two gases 779 / 627).
 template <typename T, bool REST, bool SP>
 struct MarchStash {
     static constexpr bool FP64 = sizeof(T) == 8, NEAR = FP64 && REST != SP;
     static constexpr int LB = kSpeeds<REST> - 1, ND = SP ? 5 : 4;
-    // fields of the far marches (F2 = 0: all in the first), and those of them in LDS
+    // fields of the far marches (F2 = 0: all in the first), those of them in LDS, and
+    // whether the lane momentum is
     static constexpr int ALL = kMPE | kVy | (SP ? kChi : 0);
-    static constexpr int F1 = FP64 && !(REST && SP) ? kMPE : ALL, F2 = ALL & ~F1;
-    static constexpr int L1 = FP64 ? kAllFields : 0, L2 = kVy;
+    static constexpr int F1 = FP64 && REST && !SP ? kMPE : ALL, F2 = ALL & ~F1;
+    static constexpr int LDS = !FP64 ? 0 : SP && !REST ? kMPE | kVy : ALL;
+    static constexpr bool HL = !FP64 || REST;
+    static constexpr int COLS = FP64 && REST && SP ? 64 : kMCols + 1;
     struct Near {
         double hist[NEAR ? LaneHistLds<LB>::N : 1][NEAR ? 64 : 1], fifo[NEAR ? 2 * LB * ND : 1][NEAR ? 64 : 1];
     };
     union {
         Near near;
-        FarRows<T, F1, L1> far1;
-        FarRows<T, F2, L2> far2;
+        FarRows<T, F1, LDS, HL, COLS> far1;
+        FarRows<T, F2, LDS, HL, COLS> far2;
     };
     template <int FIELDS>
     __device__ __forceinline__ auto& far()
     {
-        if constexpr (FIELDS == F2) return far2;
-        else if constexpr (FIELDS == F1) return far1;
-        else return near;  // (the near form, which has none)
+        if constexpr (FIELDS != F1 && FIELDS == F2) return far2;
+        else return far1;  // (unused by the near form)
     }
 };
 
@@ -766,9 +789,10 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
     constexpr bool VY = (FIELDS & kVy) != 0;
     using S = MarchStash<T, REST, SP>;
     auto& far = st.template far<FIELDS>();
-    FarOwn<T, FIELDS & ~(FIELDS == S::F2 ? S::L2 : S::L1)> own;
+    using Rows = std::remove_reference_t<decltype(far)>;
+    typename Rows::Own own;
     const auto far_row = [](int r, int o) { return (r + o + 2 * (2 * kMH + 1)) % (2 * kMH + 1); };  // row (current) + o
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, col = Rows::col(lane);
     const int nrows = (int)(ylast - Y0) + 2 * kMH;
     Dest<T> f[NSL];  // (with FIFO: in LDS)
     static_for<NSL>([&](auto j) { f[j].zero(); });
@@ -790,7 +814,7 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
     }
     if constexpr (FAR) {
 #pragma unroll 1
-        for (int j = 0; j <= 2 * kMH; ++j) far_zero(far, own, j, lane);
+        for (int j = 0; j <= 2 * kMH; ++j) far_zero(far, own, j, col);
     }
     double tot[NF] = {};
     int reach = 0;
@@ -878,8 +902,8 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
                     if (row == 1) put(u[2], has2, std::integral_constant<int, 2>{});
                 } else if constexpr (FAR) {
                     // add d to row (current) + o, and the lane momentum g
-                    auto fadd = [&](int o, const Dest<T>& d) { far_add(far, own, far_row(r, o), lane, d); };
-                    auto gadd = [&](int o, T g) { far_add_lane(far, far_row(r, o), lane, (double)g); };
+                    auto fadd = [&](int o, const Dest<T>& d) { far_add(far, own, far_row(r, o), col, d); };
+                    auto gadd = [&](int o, T g) { far_add_lane(far, own, far_row(r, o), col, (double)g); };
                     Dest<T> t;
                     t.zero();
                     if (C == 0) add_here<true, SP>(t, ua);
@@ -983,11 +1007,15 @@ __device__ __forceinline__ bool march_tile_general(const MarchIO<T, SP ? 5 : 4>&
         // row (current) - LD is complete
         const int64_t d = Y0 - kMH + r - LD;
         if constexpr (FAR) {
-            far_add(far, own, far_row(r, -1 - LB), lane, o);
+            far_add(far, own, far_row(r, -1 - LB), col, o);
             const int j = far_row(r, -kMH);
-            o = far_get(far, own, j, lane);
-            if constexpr (VY) o.w = (T)((double)o.w + (far.hl[j][0][lane] + far.hl[j][1][lane]));
-            far_zero(far, own, j, lane);
+            o = far_get(far, own, j, col);
+            if constexpr (VY) {
+                double h, l;
+                far_get_lane(far, own, j, col, h, l);
+                o.w = (T)((double)o.w + (h + l));
+            }
+            far_zero(far, own, j, col);
         }
         if (d >= Y0 && d < ylast && io.dest) {
             io.template store<FIELDS>(d, o.m, o.p, o.w, o.e, o.x);
@@ -1056,7 +1084,7 @@ __device__ __forceinline__ bool needs_general(const int* __restrict__ flags, int
 // with three and 126 spilled 2650).  FP32 five; two gases or a rest level four,
 // both three (226 and 288 us, with five 277 and 1157).  General: two, in FP64 with
 // both a rest level and two gases one (424 registers; with two 139 of them are
-// spilled, and 2048^2 four-state nodes take 718 us per step instead of 487).
+// spilled, and 2048^2 four-state nodes take 718 us per step instead of 447).
 template <typename T, bool REST, bool SP>
 constexpr int kLeanWpe = sizeof(T) == 8 ? (REST ? 2 : (SP ? 3 : 4)) : (REST && SP ? 3 : (REST || SP ? 4 : 5));
 template <typename T, bool REST, bool SP>

@@ -5,16 +5,15 @@ Headline: a 2-D planar shock tube on the square dual-level lattice,
 4096 x 4096 nodes, seeded Riemann state (rho_L = 1, p_L = 1, u = 0; pressure
 ratio log-uniform in [2, 100], density ratio in [1, 10], diaphragm in
 [0.3, 0.7]; seed 0), lambda from the CFL bound of the initial states,
-transmissive in x, periodic in y; FP64 plain form, one step = the fused
-gather kernel plus its totals reduction.  Alongside, in the same JSON line:
+transmissive in x, periodic in y; FP64 plain form, one step = the two
+passes of the march plus the totals reduction.  Alongside, in the same JSON line:
 
 * fp32:  the same workload in the FP32 form (node-updates/s and relative L1
   density error against FP64 after the timed steps);
 * batch: 512 independent 1-D tubes, lengths log-uniform in [256, 65536],
-  seeded states, 1000 steps, one persistent launch per step over all tubes,
+  seeded states, 1000 steps, one launch per several steps over all tubes,
   HIP-graph captured, tile shape autotuned, FP32 and FP64;
-* walls: the headline tube between reflecting walls at both x ends (FP64;
-  the kernel instances that handle walls);
+* walls: the headline tube between reflecting walls at both x ends (FP64);
 * nonplanar: a seeded four-state 2-D Riemann problem (both velocity
   components of both signs) on 2048 x 2048 nodes, FP64;
 * hex: the headline tube on the hexagonal lattice (4096 x 4096 nodes, state

@@ -204,7 +204,7 @@ int64_t lb_steps_done(const lb_solver* s);    /* good steps since the last init 
 int32_t lb_max_reach(lb_solver* s);           /* largest reach of the latest step (synchronises) */
 
 /* Per-node floor(v_x), floor(v_y) (0 in 1-D) and c'_1 (eq. 26) of the current
- * state, computed by the same device function the step uses; host int32
+ * state, computed by the node functions of the step; host int32
  * arrays of nx*ny entries.  Synchronises. */
 int lb_debug_lanes(lb_solver* s, int32_t* floor_x, int32_t* floor_y, int32_t* c1);
 
@@ -234,15 +234,14 @@ const char* lb_last_error(void);
  * threads) race and must be serialised by the caller. */
 int lb_step_static(lb_solver* s, const void* Y_in, void* Y_out, void* hip_stream, int32_t* status_dev);
 
-/* ---- pools: many independent problems, one persistent launch per step ----
+/* ---- pools: many independent problems, advanced together ----
  *
  * The batching and serving forms.  A pool holds up to max_slots problems of one
  * lattice, gamma and precision (each with its own grid, lambda, boundary
  * conditions and step target) in an arena of arena_bytes inside the caller's
- * device memory.  One pool step is one kernel launch over a tile table in
- * device memory (square lattice: resident wavefronts that take tiles, plus a
- * second pass over the tiles the first left to it) and a per-slot reduction
- * kernel; every live, unfinished slot advances by one step (eq. 10 / 30 with
+ * device memory.  A pool step is a launch over a tile table in device memory
+ * (square lattice: resident wavefronts that take tiles, plus a second pass over
+ * the tiles the first left to it) and a per-slot reduction kernel; every live, unfinished slot advances by one step (eq. 10 / 30 with
  * tau = 1, as lb_step).  In 1-D a launch has one wavefront per tile and makes as
  * many steps as the tile shape says, fewer where the call asks for fewer.
  * Admissions and releases rewrite the tables between launches, in stream

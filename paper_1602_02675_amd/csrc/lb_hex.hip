@@ -14,8 +14,8 @@
 // that speed, and the lanes: the new moments of x take U_c at x - c u_d for the
 // six d.  (The rest group and both speeds' lanes at c = 0 stay where the
 // vertices put them.)  That is 3 packets per speed and node where the lanes
-// taken one by one make 18, each looked up in LDS: 2048^2 nodes in FP64 took
-// 864 us so.
+// taken one by one make 18, each looked up in LDS: 4096^2 nodes in FP64 took
+// 1697 us so.
 //
 // A block computes tiles of kHX x kHY destinations, one per thread.  A tile's
 // sources, a halo of H = kHalo nodes included, are held by the threads in
@@ -25,9 +25,9 @@
 // velocity, triangle), and each adds its six lanes.  The order of every sum is
 // that of the classes, whatever else a tile holds: results do not depend on the
 // tiling.  Two blocks share a CU's LDS (80 KB each in FP64), so that one
-// computes while the other waits at a barrier: 2048^2 nodes in FP64 take 189 us,
-// half of it VALU issue (700 instructions per node, a third of them the
-// primitives of 2.1 sources per destination), a third LDS reads.
+// computes while the other waits at a barrier: 4096^2 nodes in FP64 take 632 us,
+// half of it VALU issue (685 instructions per node, a third of them the
+// primitives of 2.1 sources per destination), the rest barriers and LDS reads.
 #include "lb_wave.hpp"
 
 namespace lbsd {

@@ -148,8 +148,8 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t stream)
 constexpr int kStatusOk = 0, kStatusState = -4, kStatusReach = -5;
 hipError_t launch_status(const StepCtl* ctl, int32_t* out, hipStream_t stream);
 
-// ---- pools: many independent problems advanced by one persistent launch per
-// step over a device-resident tile table (lb_pool.hip) ----
+// ---- pools: many independent problems advanced together by launches over a
+// device-resident tile table (lb_pool.hip) ----
 
 struct PoolProb {       // one slot, written by the host between launches
     int64_t off[2];     // element offsets of the two SoA moment sets in the arena

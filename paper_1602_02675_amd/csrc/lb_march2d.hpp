@@ -607,7 +607,7 @@ __device__ __forceinline__ void march_partials(double (&tot)[NF], int reach, boo
 //
 // Bound by HBM at large sizes: 4 loads and 4 stores per lane and row against
 // about 200 VALU instructions (FP64), in four wavefronts per SIMD: 4096^2 nodes
-// take 262 us (84 % of the rate of a copy), where packets rebuilt from LDS rows
+// take 262 us (4.5 TB/s, a copy 5.1), where packets rebuilt from LDS rows
 // took 352; in FP32 VALU issue bounds it, 158 us against 452.
 template <typename T, bool REST, bool SP>
 __device__ __forceinline__ bool march_tile_lean(const MarchIO<T, SP ? 5 : 4>& io, const Consts& k, int64_t Y0,
@@ -1083,7 +1083,7 @@ __device__ __forceinline__ bool needs_general(const int* __restrict__ flags, int
 // planar nodes 391 us per step, with three and 27 spilled registers 787; both 463,
 // with three and 126 spilled 2650).  FP32 five; two gases or a rest level four,
 // both three (226 and 288 us, with five 277 and 1157).  General: two, in FP64 with
-// both a rest level and two gases one (424 registers; with two 139 of them are
+// both a rest level and two gases one (391 registers; with two 139 of them are
 // spilled, and 2048^2 four-state nodes take 718 us per step instead of 447).
 template <typename T, bool REST, bool SP>
 constexpr int kLeanWpe = sizeof(T) == 8 ? (REST ? 2 : (SP ? 3 : 4)) : (REST && SP ? 3 : (REST || SP ? 4 : 5));

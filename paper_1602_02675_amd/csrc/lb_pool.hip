@@ -1,7 +1,9 @@
 // Pool runtime behind the lb_pool_* calls of include/lbsd.h: many independent
 // problems (same lattice, gamma and precision; own grid, lambda, boundary
 // conditions and step target) resident in one arena of the caller's device
-// memory, advanced together by one persistent launch per step.
+// memory, advanced together by launches over one tile table: in 1-D several steps
+// per launch, on the square lattice a step per pair of launches, and each followed
+// by the slots' reduction.
 //
 // Device-resident tables (rewritten by the host between launches, read by the
 // kernels): one PoolProb per slot and the tile table (slot, first column,

@@ -311,8 +311,8 @@ class Solver:
 
 
 class Pool:
-    """Many independent problems of one lattice and precision, advanced by one
-    persistent launch per step (include/lbsd.h, lb_pool_*).  Memory: one
+    """Many independent problems of one lattice and precision, advanced
+    together by launches over one tile table (include/lbsd.h, lb_pool_*).  Memory: one
     uint8 torch tensor; stream: a dedicated torch stream (graph capture needs
     a non-default stream)."""
 

@@ -4,7 +4,7 @@ Requests (grid side, step count, Riemann states) arrive over wall-clock time.
 The loop admits every arrived request that fits (a free slot and room for its
 footprint in the pool's arena; first come, first served, so a large request at
 the head waits for memory rather than being overtaken), advances all admitted
-solves together by `tick` pool steps (one persistent launch per step, HIP-graph
+solves together by `tick` pool steps (launches over one tile table, HIP-graph
 captured), then collects the finished ones, whose slots and memory go to the
 next arrivals.  Work of different requests overlaps inside each launch.
 
